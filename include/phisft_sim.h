@@ -11,6 +11,8 @@
  *     corrective forces F_t;
  *   * per step one linearised backward-Euler update (Eq. 4 with the force
  *     linearisation of Eq. 5, df/dv = 0), solved for Delta v by a
+ *     multifrontal factorisation (rebuilt every step, reused by the step's
+ *     adjoint) or, where that is not used or its solution misses the tolerance, by a
  *     preconditioned conjugate gradient (pipelined; three-level additive
  *     preconditioner: 3x3 block Jacobi, the rigid motions of runs of 16
  *     vertices, and a coarse space of the rigid motions of larger aggregates;
@@ -171,7 +173,12 @@ typedef struct {
                                trajectory, element arithmetic and solver vectors are
                                always FP64                                              */
   double cg_tol;            /* stop at ||r||_2 <= cg_tol * ||b||_2 (relative residual)  */
-  int32_t cg_max_iter;      /* cap per solve                                            */
+  int32_t cg_max_iter;      /* cap per solve. Steps are solved directly when the solver
+                               is left to the library: rows_per_block, matrix_home,
+                               matrix_precision and coarse_size at their defaults,
+                               cg_tol >= 1e-12, cg_max_iter not below
+                               min(20000, 3 x the largest sheet's vertices), and at
+                               most 16 GB for one factorisation                         */
   int32_t checkpoint_every; /* k > 0: keep every k-th state, recompute in the adjoint;
                                0: keep every state                                      */
   double gravity[3];        /* m/s^2                                                    */
@@ -229,7 +236,7 @@ typedef struct {
 typedef struct {
   int32_t n_steps;
   int32_t n_instances;
-  int64_t cg_iters_forward;   /* summed over steps and instances */
+  int64_t cg_iters_forward;   /* summed over steps and instances; a direct solve is one */
   int64_t cg_iters_recompute; /* forward solves repeated by checkpoint recompute */
   int64_t cg_iters_adjoint;
   int32_t cg_iters_max;       /* largest single solve */
@@ -242,7 +249,7 @@ typedef struct {
   int32_t solver_matrix_home; /* sim_matrix_home of the launch shape in use (never AUTO) */
   int32_t solver_launches_per_solve; /* batches split into sets of co-resident sheets */
   int64_t nnz_blocks;         /* non-zero 3x3 blocks of the system matrix */
-  int64_t solver_launches;    /* timed solver launches since timing was enabled */
+  int64_t solver_launches;    /* timed solves since timing was enabled */
   double solver_ms;           /* their summed duration (HIP events on the call's stream) */
   int32_t coarse_aggregates;  /* aggregates of the coarse space over all sheets (0: none) */
   int32_t coarse_max_dim;     /* largest per-sheet coarse dimension (6 x aggregates) */
@@ -254,7 +261,9 @@ typedef struct {
   int64_t graph_captures;     /* rollout / adjoint graphs captured (graph option) */
   int64_t graph_replays;      /* calls served by replaying a captured graph */
   int64_t device_bytes;       /* device memory the handle holds (workspace, trajectory or
-                                 checkpoints, kept coarse operators, tables) */
+                                 checkpoints, kept coarse operators, tables; after the
+                                 first adjoint also kept factors, at most 32 GB and at
+                                 most a fifth of the memory then free) */
   int32_t coarse_store_slots; /* steps whose coarse operators are kept for the adjoint */
   int32_t material_params;    /* n_mat of the material arrays (3 or SIM_WANG_PARAMS) */
   int32_t solver_row_teams;   /* 2: register-resident rows split over two wavefront teams

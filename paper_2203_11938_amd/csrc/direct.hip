@@ -1,0 +1,1040 @@
+// direct.hip -- direct solution of the step matrix A on gfx950: a multifrontal
+// factorisation over the elimination plan of direct_prep.cpp and its two triangular
+// passes, all in FP64, in one launch of k_ds_run.
+//
+// Work is cut into tasks of one front each. With F_pp and F_bp the front's pivot and
+// border blocks (both from A plus the children's updates):
+//   pivot     X = F_pp^-1              symmetric block sweep in registers
+//   border    W = F_bp X               32 border rows
+//   Schur     S = (children) - W F_bp^T    a 64x64 tile of the lower triangle
+//   forward   t = b_p + (children), g = (children) - W t    64 border rows
+//   backward  x_p = X t - W^T x_b      32 pivot unknowns, top down
+// Keeping the inverse of every pivot block instead of its triangular factor is what lets
+// both passes run as matrix-vector products without a serial substitution inside a front;
+// pivot blocks are at most 96 wide, and a solve is accepted only on its true residual
+// (k_ds_resid). A later solve with the same factor runs the forward and backward tasks
+// alone.
+//
+// What bounds it: the chain of fronts from a leaf to the root (15 of a 64x64 sheet), each
+// a pivot sweep and three hand-offs between workgroups, not the arithmetic (1.3 GFLOP).
+// A forward and adjoint of 60 steps on that sheet took 140 ms with the iterative solver
+// (100 to 300 iterations of 5 to 12 us a solve) and take 54 ms with this one; 40 solves of a
+// 17x17 sheet 67 and 12 ms, 30 forward and adjoint steps of a 200x200 sheet 427 and 233 ms.
+// Workgroups take the tasks in a topological order from one queue and wait on per-front
+// counters, so the only tasks ever waited for have been taken by workgroups that run:
+// no co-residency is needed, and a launch per level and kind (75 launches of at least
+// 4 us each on that sheet) is saved. Every array that one task writes and another reads
+// is written once per launch, on cache lines of its own, with write-through stores, and
+// read only after its counter, so ordinary cached loads see it. All waits are bounded: a
+// time-out ends the launch, the residual test fails and the iterative solver takes over.
+// Every sum has a fixed order, so results do not depend on which workgroup ran what,
+// nor on the other sheets of a batch.
+
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cmath>
+
+#include "direct.h"
+#include "direct_kernels.h"
+
+namespace phisft {
+namespace {
+
+typedef double dbl4 __attribute__((ext_vector_type(4)));
+
+constexpr int kThreads = 512;
+constexpr int kWaves = kThreads / 64;
+constexpr int kSide = 3 * kDsMaxPiv / kDsTile;   // tiles of the largest pivot block
+constexpr int kLd = 3 * kDsMaxPiv + 2;           // LDS row stride of the blocks
+constexpr int kLdK = 50;                         // LDS row stride of a Schur operand's half
+constexpr int kLds = 3 * kDsMaxPiv * kLd;        // doubles of dynamic LDS
+constexpr int kSpinLimit = 1 << 22;              // polls of a wait (seconds)
+static_assert(kDsMaxBorder + 3 * kDsMaxPiv + 16 * 33 <= kLds, "backward task's vectors");
+static_assert(2 * kDsSchurTile * kLdK <= kLds, "Schur operands");
+static_assert((5 * kSide + 1) * 256 <= kLds, "pivot sweep panels and diagonal");
+
+__device__ __forceinline__ dbl4 mfma4(double a, double b, dbl4 c) {
+  // A operand: lane l holds row l % 16, column l / 16; B: row l / 16, column l % 16;
+  // C/D: register q holds row 4 q + l / 16, column l % 16
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const int2 t = *reinterpret_cast<const int2*>(&v);
+  int2 r;
+  r.x = __builtin_amdgcn_readlane(t.x, lane);
+  r.y = __builtin_amdgcn_readlane(t.y, lane);
+  return *reinterpret_cast<double*>(&r);
+}
+
+// Reciprocal by Newton-Raphson refinement of the hardware estimate (two steps of
+// x <- x + x (1 - a x), each squaring the relative error).
+__device__ __forceinline__ double recip(double a) {
+  double x = __builtin_amdgcn_rcp(a);
+  x = fma(x, fma(-a, x, 1.0), x);
+  return fma(x, fma(-a, x, 1.0), x);
+}
+
+// Symmetric sweep of a symmetric 16x16 tile in the matrix cores' C layout on one
+// wavefront, four pivots at a time: with Q the inverse of the 4x4 pivot block and R the
+// four pivot rows (register kb),
+//   M_ij -= R_i^T Q R_j,  M_kj = Q R_j,  M_ik = R_i^T Q,  M_kk = -Q,
+// which after all pivots leaves -M^-1. By symmetry the pivot rows in C layout are at once
+// the A operand (R^T) and the B operand of a rank-4 update, so each step is two matrix
+// instructions; the pivot columns come out of the same update with -Q in their place of
+// the B operand and zero in the accumulator (nothing cancels). The 4x4 blocks are
+// inverted by LDL^T from lane broadcasts, every lane solving for one column. False if a
+// pivot is not positive.
+__device__ __forceinline__ bool sweep16(dbl4& d, int lane) {
+  const int g = lane >> 4, c = lane & 15;
+  bool good = true;
+#pragma unroll
+  for (int kb = 0; kb < 4; ++kb) {
+    const double R = d[kb];
+    const double p00 = lane_value(R, 4 * kb);
+    const double p10 = lane_value(R, 16 + 4 * kb), p11 = lane_value(R, 16 + 4 * kb + 1);
+    const double p20 = lane_value(R, 32 + 4 * kb), p21 = lane_value(R, 32 + 4 * kb + 1),
+                 p22 = lane_value(R, 32 + 4 * kb + 2);
+    const double p30 = lane_value(R, 48 + 4 * kb), p31 = lane_value(R, 48 + 4 * kb + 1),
+                 p32 = lane_value(R, 48 + 4 * kb + 2), p33 = lane_value(R, 48 + 4 * kb + 3);
+    const double r0 = recip(p00);
+    const double l10 = p10 * r0, l20 = p20 * r0, l30 = p30 * r0;
+    const double d1 = fma(-l10, p10, p11);
+    const double u21 = fma(-l20, p10, p21), u31 = fma(-l30, p10, p31);
+    const double r1 = recip(d1);
+    const double l21 = u21 * r1, l31 = u31 * r1;
+    const double d2 = fma(-l21, u21, fma(-l20, p20, p22));
+    const double u32 = fma(-l31, u21, fma(-l30, p20, p32));
+    const double r2 = recip(d2);
+    const double l32 = u32 * r2;
+    const double d3 = fma(-l32, u32, fma(-l31, u31, fma(-l30, p30, p33)));
+    const double r3 = recip(d3);
+    good = good && p00 > 0.0 && d1 > 0.0 && d2 > 0.0 && d3 > 0.0 && isfinite(p00) &&
+           isfinite(d1) && isfinite(d2) && isfinite(d3);
+    // column g of Q
+    const double y0 = g == 0 ? 1.0 : 0.0;
+    const double y1 = fma(-l10, y0, g == 1 ? 1.0 : 0.0);
+    const double y2 = fma(-l21, y1, fma(-l20, y0, g == 2 ? 1.0 : 0.0));
+    const double y3 = fma(-l32, y2, fma(-l31, y1, fma(-l30, y0, g == 3 ? 1.0 : 0.0)));
+    const double q3 = y3 * r3;
+    const double q2 = fma(-l32, q3, y2 * r2);
+    const double q1 = fma(-l31, q3, fma(-l21, q2, y1 * r1));
+    const double q0 = fma(-l30, q3, fma(-l20, q2, fma(-l10, q1, y0 * r0)));
+    const double lo = (c & 1) ? q1 : q0, hi = (c & 1) ? q3 : q2;
+    const double sel = (c & 2) ? hi : lo;             // Q[c % 4][g]
+    const dbl4 zero = {0.0, 0.0, 0.0, 0.0};
+    const dbl4 v = mfma4(c < 4 ? sel : 0.0, R, zero);  // rows 0..3: Q R
+    const bool piv = (c >> 2) == kb;
+    const double V = piv ? -sel : v[0];
+    dbl4 a;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) a[q] = piv ? 0.0 : d[q];
+    d = mfma4(-R, V, a);
+    d[kb] = V;
+  }
+  return good;
+}
+
+// Sum over the 16 lanes of a DPP row, the same in each.
+__device__ __forceinline__ double row_sum(double v) {
+#define PHISFT_ROW_STEP(ctrl)                                                        \
+  {                                                                                  \
+    int2 t = *reinterpret_cast<int2*>(&v);                                           \
+    t.x = __builtin_amdgcn_update_dpp(0, t.x, ctrl, 0xf, 0xf, false);                \
+    t.y = __builtin_amdgcn_update_dpp(0, t.y, ctrl, 0xf, 0xf, false);                \
+    v += *reinterpret_cast<double*>(&t);                                             \
+  }
+  PHISFT_ROW_STEP(0x140)   // row mirror
+  PHISFT_ROW_STEP(0x141)   // half mirror
+  PHISFT_ROW_STEP(0x4E)    // quad_perm [2,3,0,1]
+  PHISFT_ROW_STEP(0xB1)    // quad_perm [1,0,3,2]
+#undef PHISFT_ROW_STEP
+  return v;
+}
+
+// Stores that reach memory, for data other workgroups of the launch read.
+__device__ __forceinline__ void put(double* p, double v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ double2 get2(const double* p) {
+  return *reinterpret_cast<const double2*>(p);
+}
+
+// The workgroup's barrier. The wait for this wavefront's own LDS accesses is written out:
+// hipcc leaves it away at the head of the task loop, where the access in flight is on the
+// loop's back edge (a wavefront then reads the last task's number and does that again).
+__device__ __forceinline__ void sync() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __syncthreads();
+}
+
+// Tables that no task writes, read at uniform addresses through the scalar cache.
+template <class T>
+using Table = const __attribute__((address_space(4))) T*;
+
+template <class T>
+__device__ __forceinline__ Table<T> table(const T* p) {
+  return (Table<T>)reinterpret_cast<uintptr_t>(p);
+}
+
+struct Shared {
+  int next, go, bad;
+  int map[2][3 * kDsMaxPiv];   // local unknowns of the first children's pivot rows
+};
+
+// The thread's number, opaque to the optimiser: what each task derives from it would
+// otherwise be moved out of the task loop and stay in registers across all tasks.
+__device__ __forceinline__ int thread_id() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
+// Waits (bounded) until every lane's counter of wavefront 0 reaches the lane's target (0:
+// nothing to wait for). Every thread calls; false when the launch is to end. Also a
+// barrier of the workgroup.
+__device__ __forceinline__ bool wait_lanes(Table<DsArgs> a, int c, int target, Shared& sh) {
+  if (threadIdx.x < 64) {
+    int go = 1;
+    for (int spins = 0;;) {
+      const bool ok = target <= 0 || __hip_atomic_load(a->count + c, __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_AGENT) >= target;
+      if (__all(ok)) break;
+      __builtin_amdgcn_s_sleep(1);
+      if ((++spins & 255) == 0) {
+        if (spins > kSpinLimit)
+          __hip_atomic_store(a->abort_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (__hip_atomic_load(a->abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+          go = 0;
+          break;
+        }
+      }
+    }
+    if (threadIdx.x == 0) sh.go = go;
+  }
+  sync();
+  return __builtin_amdgcn_readfirstlane(sh.go) != 0;
+}
+
+__device__ __forceinline__ bool wait_one(Table<DsArgs> a, int c, int target, Shared& sh) {
+  return wait_lanes(a, c, threadIdx.x == 0 ? target : 0, sh);
+}
+
+// Waits for the children's counters `which`, k0 and k1 their targets of the first two.
+__device__ __forceinline__ bool wait_children(Table<DsArgs> a, Table<DsFront> F, int which, int k0,
+                                              int k1, Shared& sh) {
+  const int lane = thread_id();
+  int c = F->kcnt[0] + which, target = 0;
+  if (lane == 0) target = k0;
+  if (lane == 1) {
+    c = F->kcnt[1] + which;
+    target = k1;
+  }
+  if (!wait_lanes(a, c, target, sh)) return false;
+  for (int base = 2; base < F->nc; base += 64) {   // rare: more than two children
+    target = 0;
+    if (lane < 64 && base + lane < F->nc) {
+      const DsChild& K = a->kid[F->c0 + base + lane];
+      c = K.cnt + which;
+      target = which == kDsHeadDone ? K.nhead : which == kDsSchurDone ? K.nschur : K.nfwd;
+    }
+    if (!wait_lanes(a, c, target, sh)) return false;
+  }
+  return true;
+}
+
+// Waits for the border rows of the tile groups [g0, g1).
+__device__ __forceinline__ bool wait_rows(Table<DsArgs> a, Table<DsFront> F, int g0, int g1,
+                                          Shared& sh) {
+  constexpr int per = kDsSchurTile / kDsRowTile;
+  const int g = g0 + thread_id();
+  const int all = (F->nb + kDsRowTile - 1) / kDsRowTile;
+  return wait_lanes(a, F->cnt + kDsRowsDone + g,
+                    threadIdx.x < 64 && g < g1 ? min(per, all - per * g) : 0, sh);
+}
+
+// Counts a task as done once every wavefront's stores have completed (put() writes
+// through, so completion is visibility).
+__device__ __forceinline__ void signal(Table<DsArgs> a, int c, int c2 = -1) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  sync();
+  if (threadIdx.x == 0) {
+    __hip_atomic_fetch_add(a->count + c, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (c2 >= 0) __hip_atomic_fetch_add(a->count + c2, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+// The local unknowns of a child's pivot rows, one per thread, into sh.map[slot].
+__device__ __forceinline__ void stage_map(Table<DsArgs> a, Table<DsChild> K, int slot, Shared& sh) {
+  const int c = thread_id();
+  if (c < 3 * K->q) sh.map[slot][c] = 3 * a->tab[K->map + c / 3] + c % 3;
+}
+
+// X = F_pp^-1. F_pp is gathered into LDS (A's entries, then the children's updates in
+// order), then held as 16x16 tiles: the diagonal ones by wavefront 0 in LDS, the others
+// in the registers of the rest. Per tile row k, wavefront 0 brings tile (k, k) up to date
+// and sweeps it while the others apply step k - 1 to their tiles and publish row k; the
+// row is then scaled by the inverse, and old and scaled row are the operands of the
+// rank-16 updates. Wavefront 0 updates its later diagonal tiles while the row is scaled,
+// so a step costs one 16x16 sweep and one scaling.
+// A front whose sweep meets a non-positive pivot stores NaN: its solution fails the
+// residual test.
+__device__ __forceinline__ bool task_pivot(Table<DsArgs> a, Table<DsFront> F, double* fac,
+                                           double* lds, Shared& sh) {
+  const int tid = thread_id(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int np = F->np, T = np / kDsTile, n3 = 3 * F->p;
+  if (tid == 0) sh.bad = 0;
+  for (int e = tid; e < np * kLd; e += kThreads) lds[e] = 0.0;
+  for (int ch = 0; ch < min(F->nc, 2); ++ch) stage_map(a, table(a->kid + F->c0 + ch), ch, sh);
+  sync();
+  if (tid < np && tid >= n3) lds[tid * kLd + tid] = 1.0;
+  for (int e = tid; e < F->nalist; e += kThreads) {
+    const int2 en = reinterpret_cast<const int2*>(a->tab + F->alist)[e];
+    const int l = en.y >> 16, i = en.y & 0xffff;
+    double x[9];
+#pragma unroll
+    for (int q = 0; q < 9; ++q) x[q] = a->A[en.x + (size_t)q * a->nv];
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        if (l == i && c < r) continue;
+        lds[(3 * l + c) * kLd + 3 * i + r] = x[3 * r + c];
+        lds[(3 * i + r) * kLd + 3 * l + c] = x[3 * r + c];
+      }
+  }
+  if (!wait_children(a, F, kDsHeadDone, F->khead[0], F->khead[1], sh)) return false;
+  for (int ch = 0; ch < F->nc; ++ch) {
+    const Table<DsChild> K = table(a->kid + F->c0 + ch);
+    const double* S = a->ws + K->so;
+    const int nq = 3 * K->q;
+    if (ch > 0) sync();
+    if (ch > 1) {
+      stage_map(a, K, ch & 1, sh);
+      sync();
+    }
+    // a lane takes columns lane and lane + 64 of every eighth row (nq <= 96); all loads
+    // are in flight before the first is used
+    const int* map = sh.map[ch & 1];
+    constexpr int NR = 3 * kDsMaxPiv / kWaves, N1 = NR - 64 / kWaves;
+    double s0[NR], s1[N1];
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      const int r = wave + kWaves * q;
+      s0[q] = r < nq && lane <= r ? *(S + (size_t)r * K->nb + lane) : 0.0;
+      if (q >= NR - N1)
+        s1[q - (NR - N1)] = r < nq && lane + 64 <= r ? *(S + (size_t)r * K->nb + lane + 64) : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      const int r = wave + kWaves * q;
+      if (r >= nq) continue;
+      const int pr = map[r];
+      if (lane <= r) {
+        const int p0 = map[lane];
+        const double x = lds[pr * kLd + p0] + s0[q];
+        lds[pr * kLd + p0] = x;
+        lds[p0 * kLd + pr] = x;
+      }
+      if (q >= NR - N1 && lane + 64 <= r) {
+        const int p1 = map[lane + 64];
+        const double x = lds[pr * kLd + p1] + s1[q - (NR - N1)];
+        lds[pr * kLd + p1] = x;
+        lds[p1 * kLd + pr] = x;
+      }
+    }
+  }
+  sync();
+  const int g = lane >> 4, c16 = lane & 15;
+  // wavefront 0: the diagonal tiles, in LDS; the others: the off-diagonal tiles in turn, in
+  // registers
+  constexpr int NS = (kSide * (kSide - 1) + kWaves - 2) / (kWaves - 1);
+  dbl4 d[NS];
+  int ti[NS], tj[NS];
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    const int e = (wave - 1) + (kWaves - 1) * s;
+    const bool own = wave > 0 && e < T * (T - 1);
+    ti[s] = own ? e / (T - 1) : -1;
+    tj[s] = own ? e - ti[s] * (T - 1) : -1;
+    if (own && tj[s] >= ti[s]) ++tj[s];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      d[s][q] = own ? lds[(16 * ti[s] + 4 * q + g) * kLd + 16 * tj[s] + c16] : 0.0;
+  }
+  double dg[kSide][4];
+  if (wave == 0) {
+#pragma unroll
+    for (int s = 0; s < kSide; ++s)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        dg[s][q] = s < T ? lds[(16 * s + 4 * q + g) * kLd + 16 * s + c16] : 0.0;
+  }
+  sync();
+  double* Rl = lds;                        // [2][T] old rows, tiles in C layout
+  double* Vl = Rl + 2 * kSide * 256;       // [2][T] scaled rows
+  double* Dl = Vl + 2 * kSide * 256;       // [T] diagonal tiles
+  double* Pl = Dl + kSide * 256;
+  if (wave == 0) {
+#pragma unroll
+    for (int s = 0; s < kSide; ++s)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (s < T) Dl[s * 256 + 64 * q + lane] = dg[s][q];
+  }
+  // applies step k to a tile
+  auto update = [&](dbl4 v, int i, int j, int k) {
+    const double* R = Rl + ((k & 1) * kSide + i) * 256;
+    const double* V = Vl + ((k & 1) * kSide + j) * 256;
+    if (j == k) v = dbl4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v = mfma4(-R[64 * q + lane], V[64 * q + lane], v);
+    return v;
+  };
+  auto load_diag = [&](int s) {
+    dbl4 v;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = Dl[s * 256 + 64 * q + lane];
+    return v;
+  };
+  auto store_diag = [&](int s, dbl4 v) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) Dl[s * 256 + 64 * q + lane] = v[q];
+  };
+#pragma unroll 1
+  for (int k = 0; k < T; ++k) {
+    double* Rk = Rl + (k & 1) * kSide * 256;
+    double* Vk = Vl + (k & 1) * kSide * 256;
+    if (wave == 0) {
+      __builtin_amdgcn_s_setprio(3);
+      dbl4 v = load_diag(k);
+      if (k > 0) v = update(v, k, k, k - 1);
+      const bool good = sweep16(v, lane);
+      store_diag(k, v);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        Pl[64 * q + lane] = -v[q];
+        Vk[k * 256 + 64 * q + lane] = v[q];   // in V's place for the pivot column
+      }
+      if (!good && lane == 0) sh.bad = 1;
+      __builtin_amdgcn_s_setprio(0);
+    } else {
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        if (ti[s] < 0) continue;
+        if (k > 0 && ti[s] != k - 1) d[s] = update(d[s], ti[s], tj[s], k - 1);
+        if (ti[s] == k) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) Rk[tj[s] * 256 + 64 * q + lane] = d[s][q];
+        }
+      }
+    }
+    sync();
+    if (wave == 0) {
+      if (k > 0) {
+#pragma unroll 1
+        for (int s = 0; s < T; ++s)
+          if (s != k && s != k - 1) store_diag(s, update(load_diag(s), s, s, k - 1));
+      }
+    } else {
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        if (ti[s] != k) continue;
+        dbl4 v = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v = mfma4(Pl[64 * q + lane], d[s][q], v);
+        d[s] = v;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) Vk[tj[s] * 256 + 64 * q + lane] = v[q];
+      }
+    }
+    sync();
+  }
+  const bool bad = sh.bad != 0;
+  double* X = fac + F->xo;
+  auto store = [&](dbl4 v, int i, int j) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      put(X + (size_t)(16 * i + 4 * q + g) * np + 16 * j + c16, bad ? NAN : -v[q]);
+  };
+  if (wave == 0) {
+#pragma unroll 1
+    for (int s = 0; s < T; ++s) {
+      dbl4 v = load_diag(s);
+      if (s != T - 1) v = update(v, s, s, T - 1);
+      store(v, s, s);
+    }
+  } else {
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      if (ti[s] < 0) continue;
+      if (ti[s] != T - 1) d[s] = update(d[s], ti[s], tj[s], T - 1);
+      store(d[s], ti[s], tj[s]);
+    }
+  }
+  signal(a, F->cnt + kDsPivotDone);
+  return true;
+}
+
+// W rows of a border tile: wavefront j forms column tile j of both row tiles. The lanes'
+// part of X (symmetric: read along its rows, lane groups taking contiguous quarters of
+// the inner dimension) is loaded at once.
+template <int T>
+__device__ __forceinline__ void border_product(const double* __restrict__ X, const double* Fl,
+                                               double* W, int rows, int wave, int lane) {
+  constexpr int np = 16 * T, kq = np / 4;
+  if (wave >= T) return;
+  const int g = lane >> 4, c16 = lane & 15;
+  const double2* xr = reinterpret_cast<const double2*>(X + (size_t)(16 * wave + c16) * np + g * kq);
+  double2 x[kq / 2];
+#pragma unroll
+  for (int s = 0; s < kq / 2; ++s) x[s] = get2(reinterpret_cast<const double*>(xr + s));
+  dbl4 acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+  const double2* f0 = reinterpret_cast<const double2*>(Fl + c16 * kLd + g * kq);
+  const double2* f1 = reinterpret_cast<const double2*>(Fl + (16 + c16) * kLd + g * kq);
+#pragma unroll
+  for (int s = 0; s < kq / 2; ++s) {
+    const double2 u = f0[s], v = f1[s];
+    acc[0] = mfma4(u.x, x[s].x, acc[0]);
+    acc[1] = mfma4(v.x, x[s].x, acc[1]);
+    acc[0] = mfma4(u.y, x[s].y, acc[0]);
+    acc[1] = mfma4(v.y, x[s].y, acc[1]);
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+    if (16 * i < rows) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        put(W + (size_t)(16 * i + 4 * q + g) * np + 16 * wave + c16, acc[i][q]);
+    }
+}
+
+// F_bp and W = F_bp X of 32 border rows; F_bp is gathered into LDS like the pivot block.
+__device__ __forceinline__ bool task_border(Table<DsArgs> a, Table<DsFront> F, int tile,
+                                            double* fac, double* lds, Shared& sh) {
+  constexpr int NR = kDsRowTile / kWaves;
+  double* Fl = lds;
+  const int tid = thread_id(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int np = F->np, r0 = tile * kDsRowTile, rows = min(kDsRowTile, F->nb - r0);
+  const int l0 = *table(a->tab + F->blist + tile), l1 = *table(a->tab + F->blist + tile + 1);
+  for (int e = tid; e < kDsRowTile * kLd; e += kThreads) Fl[e] = 0.0;
+  // child ch's border rows of this wavefront's rows
+  auto rows_of = [&](int ch, int (&u)[NR]) {
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      const int br = r0 + wave + kWaves * q;
+      const int v = ch < F->nc && br < 3 * F->b
+                        ? a->tab[table(a->kid + F->c0 + ch)->inv + F->p + br / 3] : -1;
+      u[q] = v < 0 ? -1 : 3 * v + br % 3;
+    }
+  };
+  int u0[NR], u1[NR];
+  rows_of(0, u0);
+  rows_of(1, u1);
+  for (int ch = 0; ch < min(F->nc, 2); ++ch) stage_map(a, table(a->kid + F->c0 + ch), ch, sh);
+  sync();
+  for (int e = (l0 >> 1) + tid; e < (l1 >> 1); e += kThreads) {
+    const int2 en = reinterpret_cast<const int2*>(a->tab)[e];
+    const int l = (en.y >> 16) - F->p, i = en.y & 0xffff;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const int row = 3 * l + c - r0;
+      if (row < 0 || row >= kDsRowTile) continue;
+#pragma unroll
+      for (int r = 0; r < 3; ++r)
+        Fl[row * kLd + 3 * i + r] = a->A[en.x + (size_t)(r * 3 + c) * a->nv];
+    }
+  }
+  if (!wait_children(a, F, kDsSchurDone, F->kschur[0], F->kschur[1], sh)) return false;
+  auto add = [&](int ch, const int (&u)[NR]) {
+    const Table<DsChild> K = table(a->kid + F->c0 + ch);
+    const int nq = 3 * K->q, ld = K->nb;
+    const double* S0 = a->ws + K->so;
+    double s0[NR], s1[NR];
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      const double* S = S0 + (size_t)max(u[q], 0) * ld;
+      s0[q] = u[q] >= 0 && lane < nq ? *(S + lane) : 0.0;
+      s1[q] = u[q] >= 0 && lane + 64 < nq ? *(S + lane + 64) : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      const int r = wave + kWaves * q;
+      if (lane < nq) Fl[r * kLd + sh.map[ch & 1][lane]] += s0[q];
+      if (lane + 64 < nq) Fl[r * kLd + sh.map[ch & 1][lane + 64]] += s1[q];
+    }
+  };
+  if (F->nc > 0) add(0, u0);
+  if (F->nc > 1) {
+    sync();
+    add(1, u1);
+  }
+  for (int ch = 2; ch < F->nc; ++ch) {   // rare
+    sync();
+    stage_map(a, table(a->kid + F->c0 + ch), ch & 1, sh);
+    rows_of(ch, u0);
+    sync();
+    add(ch, u0);
+  }
+  sync();
+  double* Bg = a->ws + F->bo + (size_t)r0 * np;
+  for (int r = wave; r < rows; r += kWaves)
+    for (int c = lane; c < np; c += 64) put(Bg + (size_t)r * np + c, Fl[r * kLd + c]);
+  if (!wait_one(a, F->cnt + kDsPivotDone, 1, sh)) return false;
+  const double* X = fac + F->xo;
+  double* W = fac + F->wo + (size_t)r0 * np;
+  switch (np / kDsTile) {
+    case 1: border_product<1>(X, Fl, W, rows, wave, lane); break;
+    case 2: border_product<2>(X, Fl, W, rows, wave, lane); break;
+    case 3: border_product<3>(X, Fl, W, rows, wave, lane); break;
+    case 4: border_product<4>(X, Fl, W, rows, wave, lane); break;
+    case 5: border_product<5>(X, Fl, W, rows, wave, lane); break;
+    default: border_product<6>(X, Fl, W, rows, wave, lane); break;
+  }
+  signal(a, F->cnt + kDsRowsDone + tile / (kDsSchurTile / kDsRowTile));
+  return true;
+}
+
+// acc += (rows of W) (rows of B)^T over kc (a multiple of 16) staged columns: a 32x16 block
+// per wavefront, lane groups taking quarters of the columns.
+__device__ __forceinline__ void schur_product(const double* w0, const double* b0, int kc, int g,
+                                              dbl4 (&acc)[2]) {
+  const int kq = kc / 4, o = g * kq;
+  for (int s = 0; s < kq; s += 4) {
+    const double2 x0 = *reinterpret_cast<const double2*>(w0 + o + s);
+    const double2 x1 = *reinterpret_cast<const double2*>(w0 + o + s + 2);
+    const double2 y0 = *reinterpret_cast<const double2*>(w0 + 16 * kLdK + o + s);
+    const double2 y1 = *reinterpret_cast<const double2*>(w0 + 16 * kLdK + o + s + 2);
+    const double2 z0 = *reinterpret_cast<const double2*>(b0 + o + s);
+    const double2 z1 = *reinterpret_cast<const double2*>(b0 + o + s + 2);
+    acc[0] = mfma4(x0.x, z0.x, acc[0]);
+    acc[1] = mfma4(y0.x, z0.x, acc[1]);
+    acc[0] = mfma4(x0.y, z0.y, acc[0]);
+    acc[1] = mfma4(y0.y, z0.y, acc[1]);
+    acc[0] = mfma4(x1.x, z1.x, acc[0]);
+    acc[1] = mfma4(y1.x, z1.x, acc[1]);
+    acc[0] = mfma4(x1.y, z1.y, acc[0]);
+    acc[1] = mfma4(y1.y, z1.y, acc[1]);
+  }
+}
+
+// S = (children) - W F_bp^T, one lower 64x64 tile: each wavefront forms a 32x16 block. The
+// children's parts are gathered while the border rows are still being formed; the
+// operands pass through LDS in halves of the inner dimension.
+__device__ __forceinline__ bool task_schur(Table<DsArgs> a, Table<DsFront> F, int ij, double* fac,
+                                           double* lds, Shared& sh) {
+  double* Wl = lds;
+  double* Bl = lds + kDsSchurTile * kLdK;
+  const int tid = thread_id(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 4, c16 = lane & 15;
+  const int np = F->np, nb = F->nb;
+  const int I = ij >> 16, J = ij & 0xffff, I0 = I * kDsSchurTile, J0 = J * kDsSchurTile;
+  const int i0 = I0 + 32 * (wave >> 2), col = J0 + 16 * (wave & 3) + c16;
+  dbl4 acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+  int u[2][8], w[2];   // the first children's rows and column of this lane's entries
+#pragma unroll
+  for (int ch = 0; ch < 2; ++ch) {
+    const bool have = ch < F->nc;
+    const int* inv = a->tab + (have ? table(a->kid + F->c0 + ch)->inv : 0) + F->p;
+    const int v = have && col < 3 * F->b ? inv[col / 3] : -1;
+    w[ch] = v < 0 ? -1 : 3 * v + col % 3;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int row = i0 + 4 * q + g;
+      const int x = have && row < 3 * F->b && col <= row ? inv[row / 3] : -1;
+      u[ch][q] = x < 0 ? -1 : 3 * x + row % 3;
+    }
+  }
+  if (!wait_children(a, F, kDsSchurDone, F->kschur[0], F->kschur[1], sh)) return false;
+#pragma unroll
+  for (int ch = 0; ch < 2; ++ch) {
+    if (ch >= F->nc) continue;
+    const Table<DsChild> K = table(a->kid + F->c0 + ch);
+    const double* S = a->ws + K->so + max(w[ch], 0);
+    double x[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      x[q] = u[ch][q] >= 0 && w[ch] >= 0 ? *(S + (size_t)u[ch][q] * K->nb) : 0.0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) acc[q >> 2][q & 3] -= x[q];
+  }
+  for (int ch = 2; ch < F->nc; ++ch) {   // rare
+    const Table<DsChild> K = table(a->kid + F->c0 + ch);
+    const int* inv = a->tab + K->inv + F->p;
+    const int v = col < 3 * F->b ? inv[col / 3] : -1;
+    if (v < 0) continue;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int row = i0 + 4 * q + g;
+      const int x = row < 3 * F->b && col <= row ? inv[row / 3] : -1;
+      if (x >= 0)
+        acc[q >> 2][q & 3] -= a->ws[K->so + (size_t)(3 * x + row % 3) * K->nb + 3 * v + col % 3];
+    }
+  }
+  if (!wait_lanes(a, F->cnt + kDsRowsDone + (lane == 0 ? I : J),
+                  lane < 2 ? min(kDsSchurTile / kDsRowTile,
+                                 (nb + kDsRowTile - 1) / kDsRowTile -
+                                     kDsSchurTile / kDsRowTile * (lane == 0 ? I : J))
+                           : 0,
+                  sh))
+    return false;
+  const double* W = fac + F->wo;
+  const double* B = a->ws + F->bo;
+  // Halves of at most 48 columns: a half is 64 rows of up to 24 double2 per operand, three
+  // per thread (row e / per, pair e % per); the second half travels during the first's
+  // products.
+  const int k1 = min(np, 48), k2 = np - k1;
+  double2 wv0, wv1, wv2, bv0, bv1, bv2;
+#define PHISFT_DS_LOAD(q, k0, per)                                                             \
+  {                                                                                            \
+    const int e = min(tid + kThreads * q, kDsSchurTile * (per)-1);                             \
+    const int r = e / (per), c = 2 * (e - r * (per));                                          \
+    wv##q = get2(W + (size_t)min(I0 + r, nb - 1) * np + (k0) + c); \
+    bv##q = get2(B + (size_t)min(J0 + r, nb - 1) * np + (k0) + c); \
+  }
+#define PHISFT_DS_STAGE(q, per)                                       \
+  {                                                                   \
+    const int e = min(tid + kThreads * q, kDsSchurTile * (per)-1);    \
+    const int r = e / (per), c = 2 * (e - r * (per));                 \
+    *reinterpret_cast<double2*>(Wl + r * kLdK + c) = wv##q;           \
+    *reinterpret_cast<double2*>(Bl + r * kLdK + c) = bv##q;           \
+  }
+  PHISFT_DS_LOAD(0, 0, k1 / 2)
+  PHISFT_DS_LOAD(1, 0, k1 / 2)
+  PHISFT_DS_LOAD(2, 0, k1 / 2)
+  PHISFT_DS_STAGE(0, k1 / 2)
+  PHISFT_DS_STAGE(1, k1 / 2)
+  PHISFT_DS_STAGE(2, k1 / 2)
+  if (k2 > 0) {
+    PHISFT_DS_LOAD(0, k1, k2 / 2)
+    PHISFT_DS_LOAD(1, k1, k2 / 2)
+    PHISFT_DS_LOAD(2, k1, k2 / 2)
+  }
+  sync();
+  const double* w0 = Wl + (32 * (wave >> 2) + c16) * kLdK;
+  const double* b0 = Bl + (16 * (wave & 3) + c16) * kLdK;
+  schur_product(w0, b0, k1, g, acc);
+  if (k2 > 0) {
+    sync();
+    PHISFT_DS_STAGE(0, k2 / 2)
+    PHISFT_DS_STAGE(1, k2 / 2)
+    PHISFT_DS_STAGE(2, k2 / 2)
+    sync();
+    schur_product(w0, b0, k2, g, acc);
+  }
+#undef PHISFT_DS_LOAD
+#undef PHISFT_DS_STAGE
+  if (col < nb) {
+    double* S = a->ws + F->so;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int row = i0 + 16 * i + 4 * q + g;
+        if (row < nb) put(S + (size_t)row * nb + col, -acc[i][q]);
+      }
+  }
+  signal(a, F->cnt + kDsSchurDone, I < 2 ? F->cnt + kDsHeadDone : -1);
+  return true;
+}
+
+// t = b_p + (children), g = (children) - W t of 64 border rows, 16 lanes a row. Every
+// workgroup of a front gathers t itself; W travels while the children are waited for.
+__device__ __forceinline__ bool task_forward(Table<DsArgs> a, Table<DsFront> F, int chunk,
+                                             bool factor, double* fac, double* lds, Shared& sh) {
+  constexpr int NP = kDsFwdRows * 16 / kThreads;   // rows of a thread
+  static_assert(kDsFwdRows == kDsSchurTile, "a chunk is a group of row tiles");
+  double* t = lds;
+  const int tid = thread_id(), np = F->np, l16 = tid & 15, nl = F->p + F->b;
+  // W belongs to this launch only when it factorises too
+  if (factor && F->nb > 0 && !wait_rows(a, F, chunk, chunk + 1, sh)) return false;
+  double w[NP][kSide];
+  int gs[NP][2], ts[2];
+#pragma unroll
+  for (int q = 0; q < NP; ++q) {
+    const int r = chunk * kDsFwdRows + (kThreads / 16) * q + (tid >> 4);
+#pragma unroll
+    for (int k = 0; k < kSide; ++k)
+      w[q][k] = r < F->nb && 16 * k < np ? *(fac + F->wo + (size_t)r * np + 16 * k + l16) : 0.0;
+#pragma unroll
+    for (int ch = 0; ch < 2; ++ch)
+      gs[q][ch] = ch < F->nc && l16 == 0 && r < 3 * F->b ? a->tab[F->gsrc + ch * nl + F->p + r / 3] : -1;
+  }
+#pragma unroll
+  for (int ch = 0; ch < 2; ++ch)
+    ts[ch] = ch < F->nc && tid < 3 * F->p ? a->tab[F->gsrc + ch * nl + tid / 3] : -1;
+  double v = 0.0;
+  if (tid < 3 * F->p) v = a->rhs[(size_t)(tid % 3) * a->nv + a->tab[F->verts + tid / 3]];
+  if (!wait_children(a, F, kDsForwardDone, F->kfwd[0], F->kfwd[1], sh)) return false;
+  double h[NP], e[2];
+#pragma unroll
+  for (int ch = 0; ch < 2; ++ch) e[ch] = ts[ch] >= 0 ? *(a->ws + ts[ch] + tid % 3) : 0.0;
+#pragma unroll
+  for (int q = 0; q < NP; ++q) {
+    const int r = chunk * kDsFwdRows + (kThreads / 16) * q + (tid >> 4);
+    double x[2];
+#pragma unroll
+    for (int ch = 0; ch < 2; ++ch) x[ch] = gs[q][ch] >= 0 ? *(a->ws + gs[q][ch] + r % 3) : 0.0;
+    h[q] = x[0] + x[1];
+    if (l16 == 0 && r < 3 * F->b)
+      for (int ch = 2; ch < F->nc; ++ch) {
+        const int s = a->tab[F->gsrc + ch * nl + F->p + r / 3];
+        if (s >= 0) h[q] += a->ws[s + r % 3];
+      }
+  }
+  if (tid < np) {
+    v += e[0] + e[1];
+    if (tid < 3 * F->p)
+      for (int ch = 2; ch < F->nc; ++ch) {
+        const int s = a->tab[F->gsrc + ch * nl + tid / 3];
+        if (s >= 0) v += a->ws[s + tid % 3];
+      }
+    t[tid] = v;
+    if (chunk == 0) put(a->ws + F->t + tid, v);
+  }
+  sync();
+#pragma unroll
+  for (int q = 0; q < NP; ++q) {
+    const int r = chunk * kDsFwdRows + (kThreads / 16) * q + (tid >> 4);
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < kSide; ++k)
+      if (16 * k < np) s += w[q][k] * t[16 * k + l16];
+    s = row_sum(s);
+    if (l16 == 0 && r < 3 * F->b) put(a->ws + F->g + r, h[q] - s);
+  }
+  signal(a, F->cnt + kDsForwardDone);
+  return true;
+}
+
+// x_p = X t - W^T x_b of 32 pivot unknowns, the border rows spread over 16 groups of
+// threads; X, the first rows of W and the places of x_b travel while the parent is
+// waited for.
+__device__ __forceinline__ bool task_backward(Table<DsArgs> a, Table<DsFront> F, int chunk,
+                                              bool factor, double* fac, double* lds, Shared& sh) {
+  constexpr int G = kThreads / kDsBwdCols, NW = 20, NX = 3 * kDsMaxPiv / G, NB = 2;
+  double* xb = lds;
+  double* t = xb + kDsMaxBorder;
+  double* part = t + 3 * kDsMaxPiv;          // [G][33]
+  const int tid = thread_id(), np = F->np, n3 = 3 * F->b;
+  const int cl = tid % kDsBwdCols, rg = tid / kDsBwdCols;
+  const int c = chunk * kDsBwdCols + cl;
+  if (factor) {
+    if (!wait_one(a, F->cnt + kDsPivotDone, 1, sh)) return false;
+    if (!wait_rows(a, F, 0, (F->nb + kDsSchurTile - 1) / kDsSchurTile, sh)) return false;
+  }
+  const double* X = fac + F->xo + c;
+  const double* W = fac + F->wo + c;
+  double w[NW], x[NX];
+  int xs[NB];
+#pragma unroll
+  for (int q = 0; q < NB; ++q) {
+    const int r = tid + kThreads * q;
+    xs[q] = r < n3 ? a->tab[F->xsrc + r / 3] + r % 3 : -1;
+  }
+#pragma unroll
+  for (int q = 0; q < NW; ++q) {
+    const int r = rg + G * q;
+    w[q] = c < np && r < n3 ? W[(size_t)r * np] : 0.0;
+  }
+#pragma unroll
+  for (int q = 0; q < NX; ++q) {
+    const int k = rg + G * q;
+    x[q] = c < np && k < np ? *(X + (size_t)k * np) : 0.0;
+  }
+  if (!wait_one(a, F->pcnt < 0 ? F->cnt + kDsForwardDone : F->pcnt + kDsBackwardDone,
+                F->pcnt < 0 ? F->nfwd : F->pbwd, sh))
+    return false;
+#pragma unroll
+  for (int q = 0; q < NB; ++q)
+    if (xs[q] >= 0) xb[tid + kThreads * q] = a->ws[xs[q]];
+  for (int r = tid + kThreads * NB; r < n3; r += kThreads)
+    xb[r] = a->ws[a->tab[F->xsrc + r / 3] + r % 3];
+  if (tid < np) t[tid] = a->ws[F->t + tid];
+  sync();
+  double s = 0.0, u = 0.0;
+#pragma unroll
+  for (int q = 0; q < NX; ++q)
+    if (rg + G * q < np) s += x[q] * t[rg + G * q];
+#pragma unroll
+  for (int q = 0; q < NW; ++q)
+    if (rg + G * q < n3) u += w[q] * xb[rg + G * q];
+  if (c < np) {
+#pragma unroll 8
+    for (int r = rg + G * NW; r < n3; r += G) u += W[(size_t)r * np] * xb[r];
+  }
+  part[rg * 33 + cl] = s - u;
+  sync();
+  if (tid < kDsBwdCols && c < np) {
+    double v = 0.0;
+#pragma unroll
+    for (int q = 0; q < G; ++q) v += part[q * 33 + cl];
+    put(a->ws + F->x + c, v);
+    if (c < 3 * F->p) a->sol[(size_t)(c % 3) * a->nv + a->tab[F->verts + c / 3]] = v;
+  }
+  signal(a, F->cnt + kDsBackwardDone);
+  return true;
+}
+
+// The tables come through a device copy of DsArgs that every task reads anew: as kernel
+// arguments their pointers would stay in scalar registers across the task loop, whose
+// spills then cost vector registers in every task.
+__global__ void __launch_bounds__(kThreads, 4) k_ds_run(const DsArgs* __restrict__ args,
+                                                        double* __restrict__ fac,
+                                                        const DsTask* __restrict__ tasks,
+                                                        int ntasks, int factor,
+                                                        const int* __restrict__ done, int ninst) {
+  if (done) {   // a correction: nothing to do when every sheet is solved
+    int n = 0;
+    for (int b = 0; b < ninst; ++b) n += done[b];
+    if (n == ninst) return;
+  }
+  extern __shared__ __align__(16) double lds[];
+  __shared__ Shared sh;
+  int* queue = args->queue;
+  if (threadIdx.x == 0)
+    sh.next = __hip_atomic_fetch_add(queue, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll 1
+  for (;;) {
+    sync();
+    const int at = __builtin_amdgcn_readfirstlane(sh.next);
+    if (at >= ntasks) return;
+    sync();
+    int next = 0;   // the next task's number travels while this one runs
+    if (threadIdx.x == 0)
+      next = __hip_atomic_fetch_add(queue, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const DsArgs* ap = args;
+    asm volatile("" : "+s"(ap));
+    const Table<DsArgs> a = table(ap);
+    const Table<DsTask> tk = table(tasks + at);
+    const Table<DsFront> F = table(a->fr + tk->front);
+    bool go = true;
+    if (tk->kind == kDsPivot) go = task_pivot(a, F, fac, lds, sh);
+    else if (tk->kind == kDsBorder) go = task_border(a, F, tk->a, fac, lds, sh);
+    else if (tk->kind == kDsSchur) go = task_schur(a, F, tk->a, fac, lds, sh);
+    else if (tk->kind == kDsForward) go = task_forward(a, F, tk->a, factor != 0, fac, lds, sh);
+    else go = task_backward(a, F, tk->a, factor != 0, fac, lds, sh);
+    if (!go) return;
+    if (threadIdx.x == 0) sh.next = next;
+  }
+}
+
+// x += dx of the sheets not accepted yet.
+__global__ void __launch_bounds__(256) k_ds_add(DsArgs a, DsAccept o, const double* __restrict__ dx,
+                                                const int* __restrict__ vert_inst) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= a.nv || o.done[vert_inst[i]]) return;
+#pragma unroll
+  for (int r = 0; r < 3; ++r) a.sol[(size_t)r * a.nv + i] += dx[(size_t)r * a.nv + i];
+}
+
+// True residual of the solution, 64 rows per workgroup (the four wavefronts take every
+// fourth slot of the rows); the last workgroup of a sheet to finish adds the partial
+// sums in order and accepts the solve when |b - A x| <= tol |b|. With o.again only the
+// sheets not accepted before are looked at.
+__global__ void __launch_bounds__(256) k_ds_resid(DsArgs a, DsAccept o,
+                                                  const DsTask* __restrict__ tasks) {
+  __shared__ double part[4][3][kDsResRows];
+  __shared__ int s_last;
+  const DsTask tk = tasks[blockIdx.x];
+  const int inst = tk.front, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // the next solve's counters, queue and abort flag start at zero
+  for (int e = blockIdx.x * 256 + tid; e < o.clear_ints; e += gridDim.x * 256) a.count[e] = 0;
+  if (o.again && o.done[inst]) return;   // every workgroup of the sheet
+  const int end = o.inst_voff[inst] + o.inst_nv[inst];
+  const int i = tk.a + lane, nv = a.nv;
+  double y[3] = {0.0, 0.0, 0.0};
+  if (i < end)
+    for (int k = wave; k < a.maxnz; k += 4) {
+      const int j = o.ell_col[k * nv + i];
+      if (j < 0) continue;
+      const double x0 = a.sol[j], x1 = a.sol[nv + j], x2 = a.sol[2 * nv + j];
+#pragma unroll
+      for (int r = 0; r < 3; ++r) {
+        const double* A = a.A + (size_t)(k * 9 + 3 * r) * nv + i;
+        y[r] += A[0] * x0 + A[nv] * x1 + A[2 * (size_t)nv] * x2;
+      }
+    }
+#pragma unroll
+  for (int r = 0; r < 3; ++r) part[wave][r][lane] = y[r];
+  __syncthreads();
+  const int w0 = o.inst_res0[inst], nw = o.inst_res0[inst + 1] - w0;
+  if (wave == 0) {
+    double rr = 0.0, bb = 0.0;
+    if (i < end) {
+#pragma unroll
+      for (int r = 0; r < 3; ++r) {
+        const double b = a.rhs[(size_t)r * nv + i];
+        const double e = b - (part[0][r][lane] + part[1][r][lane] + part[2][r][lane] +
+                              part[3][r][lane]);
+        if (o.res) o.res[(size_t)r * nv + i] = e;
+        rr += e * e;
+        bb += b * b;
+      }
+    }
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) {
+      rr += __shfl_xor(rr, s);
+      bb += __shfl_xor(bb, s);
+    }
+    if (lane == 0) {
+      __hip_atomic_store(o.part + 2 * blockIdx.x, rr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(o.part + 2 * blockIdx.x + 1, bb, __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+      const int n = __hip_atomic_fetch_add(o.arrived + inst, 1, __ATOMIC_ACQ_REL,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+      s_last = n == nw - 1;
+    }
+  }
+  __syncthreads();
+  if (!s_last || wave != 0) return;
+  double rr = 0.0, bb = 0.0;
+  for (int w = lane; w < nw; w += 64) {
+    rr += __hip_atomic_load(o.part + 2 * (w0 + w), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    bb += __hip_atomic_load(o.part + 2 * (w0 + w) + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+#pragma unroll
+  for (int s = 32; s > 0; s >>= 1) {
+    rr += __shfl_xor(rr, s);
+    bb += __shfl_xor(bb, s);
+  }
+  if (lane != 0) return;
+  __hip_atomic_store(o.arrived + inst, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const bool ok = isfinite(bb) && rr <= o.tol * o.tol * bb;   // NaN: false
+  o.done[inst] = ok ? 1 : 0;
+  if (ok) {
+    if (o.iters) o.iters[inst] = bb > 0.0 ? 1 : 0;
+    if (o.resid) o.resid[inst] = bb > 0.0 ? sqrt(rr / bb) : 0.0;
+  }
+}
+
+}  // namespace
+
+hipError_t ds_prepare(int* blocks_per_cu) {
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_ds_run),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           kLds * (int)sizeof(double));
+  if (e != hipSuccess) return e;
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(
+      blocks_per_cu, reinterpret_cast<const void*>(&k_ds_run), kThreads, kLds * sizeof(double));
+}
+
+void launch_ds_run(const DsArgs* args, double* fac, const DsTask* tasks, int ntasks, bool factor,
+                   int grid, const int* done, int ninst, hipStream_t st) {
+  hipLaunchKernelGGL(k_ds_run, dim3(std::min(grid, ntasks)), dim3(kThreads), kLds * sizeof(double),
+                     st, args, fac, tasks, ntasks, factor ? 1 : 0, done, ninst);
+}
+
+void launch_ds_add(const DsArgs& a, const DsAccept& o, const double* dx, const int* vert_inst,
+                   hipStream_t st) {
+  hipLaunchKernelGGL(k_ds_add, dim3((a.nv + 255) / 256), dim3(256), 0, st, a, o, dx, vert_inst);
+}
+
+void launch_ds_resid(const DsArgs& a, const DsAccept& o, const DsTask* tasks, int ntasks,
+                     hipStream_t st) {
+  hipLaunchKernelGGL(k_ds_resid, dim3(ntasks), dim3(256), 0, st, a, o, tasks);
+}
+
+}  // namespace phisft

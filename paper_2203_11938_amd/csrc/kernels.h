@@ -35,6 +35,7 @@ struct PcgArgs {
   int* iters;          // [ninst] or nullptr
   double* resid;       // [ninst] or nullptr
   int* status;
+  const int* done;     // [ninst] 1: the sheet is solved already and left alone; or nullptr
 };
 
 template <typename T>

@@ -804,6 +804,7 @@ __global__ void __launch_bounds__(256) k_assemble(Mesh m, Elem el, AssembleArgs<
 // x_i - c of its members (zero on pinned members and where rotations are unused).
 __global__ void __launch_bounds__(64) k_coarse_frame(Mesh m, Coarse c, const double* __restrict__ x) {
   const int a = blockIdx.x, lane = threadIdx.x, nv = m.nv;
+  if (c.done && c.done[c.agg_inst[a]]) return;
   const int v0 = c.agg_v0[a], v1 = c.agg_v0[a + 1];
   double s[3] = {0.0, 0.0, 0.0}, cnt = 0.0;
   for (int i = v0 + lane; i < v1; i += 64) {
@@ -850,6 +851,7 @@ __global__ void __launch_bounds__(256) k_coarse_assemble(Mesh m, Coarse c, const
   __shared__ double s_part[4][36];
   const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nv = m.nv;
   const int a = c.pair_a[p], b = c.pair_b[p];
+  if (c.done && c.done[c.agg_inst[a]]) return;
   double acc[36];
 #pragma unroll
   for (int e = 0; e < 36; ++e) acc[e] = 0.0;
@@ -906,6 +908,7 @@ __global__ void __launch_bounds__(64) k_mid_setup(Mesh m, Coarse c, const double
   __shared__ double sr[3][kMid];
   const int a = blockIdx.x, lane = threadIdx.x, nv = m.nv;
   const int v0 = c.mid_v0[a], v1 = c.mid_v0[a + 1], modes = c.mid_modes[a];
+  if (c.done && c.done[m.vert_inst[v0]]) return;
   const int i = v0 + lane;
   const bool mem = lane < kMid && i < v1;
   const bool fr = mem && !m.pinned[i];
@@ -1185,6 +1188,7 @@ __global__ void __launch_bounds__(256) k_gj_sweep(Coarse c, int ninst, int wg0) 
   __shared__ double s_col[T];
   const int w = wg0 + blockIdx.x, tid = threadIdx.x, tpw = c.sw_tpw;
   const int inst = c.sw_inst[w];
+  if (c.done && c.done[inst]) return;   // every workgroup of the sheet
   const int np = c.inst_np[inst], nb = np / T;
   // flags, kSwFlag ints apart: pivot, then one per panel t
   int* sync = c.sw_sync + (size_t)inst * c.sw_stride;
@@ -2314,6 +2318,7 @@ __global__ void __launch_bounds__(256, OCC) k_pcg(Mesh m, SolverPlan plan, Solve
   __shared__ double s_wd[3 * 4];   // tagged dot partials per wavefront (unsplit blocks)
   const int wg = plan.wg_base + blockIdx.x;
   const int inst = plan.wg_inst[wg];
+  if (a.done && a.done[inst]) return;   // every workgroup of the sheet: solved directly
   const int row0 = plan.wg_row0[wg];
   const int nrows = plan.wg_nrows[wg];
   const int iw0 = plan.inst_wg0[inst], nwg = plan.inst_nwg[inst];
@@ -3272,13 +3277,31 @@ __global__ void k_fill_int(int* p, int n, int v) {
 struct ZeroRanges {
   int* p[4];
   int n[4];
+  const int* done;   // with it: nothing to do when every sheet is solved
+  int ninst;
 };
 
+// Whether every sheet is marked (done may be nullptr: none is).
+__device__ __forceinline__ bool all_done(const int* done, int ninst) {
+  if (!done) return false;
+  int n = 0;
+  for (int b = 0; b < ninst; ++b) n += done[b];
+  return n == ninst;
+}
+
 __global__ void __launch_bounds__(256) k_zero_ranges(ZeroRanges z) {
+  if (all_done(z.done, z.ninst)) return;
   const int stride = gridDim.x * blockDim.x;
 #pragma unroll
   for (int r = 0; r < 4; ++r)
     for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < z.n[r]; k += stride) z.p[r][k] = 0;
+}
+
+// Clears the coarse matrices before their assembly.
+__global__ void __launch_bounds__(256) k_coarse_clear(Coarse c, int ninst, long n) {
+  if (all_done(c.done, ninst)) return;
+  const long stride = (long)gridDim.x * blockDim.x;
+  for (long k = (long)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += stride) c.mat[k] = 0.0;
 }
 
 __global__ void k_fill_double(double* p, long n, double v) {
@@ -3418,6 +3441,8 @@ void launch_pcg(const Mesh& m, const SolverPlan& plan, const SolverWork& w, cons
   size_t lds = pcg_lds_bytes<TM>(m.maxnz, plan.rows, plan.mat_home, coarse ? cs.max_nc : 0,
                                  plan.max_halo, coarse ? plan.xl_floats : 0);
   ZeroRanges z{};
+  z.done = a.done;
+  z.ninst = m.ninst;
   z.p[0] = w.barrier;
   z.n[0] = w.barrier_ints;
   z.p[1] = w.abort_flag;
@@ -3468,7 +3493,8 @@ void launch_coarse_setup(const Mesh& m, const Coarse& c, const double* x, const 
                          hipStream_t st) {
   if (c.nagg == 0) return;
   hipLaunchKernelGGL(k_coarse_frame, dim3(c.nagg), dim3(64), 0, st, m, c, x);
-  launch_fill_double(c.mat, coarse_doubles, 0.0, st);
+  hipLaunchKernelGGL(k_coarse_clear, dim3(std::min(blocks_for(coarse_doubles, 256), 2048)), dim3(256),
+                     0, st, c, m.ninst, (long)coarse_doubles);
   if (c.npair > 0)
     hipLaunchKernelGGL((k_coarse_assemble<TM>), dim3(c.npair), dim3(256), 0, st, m, c, A);
   if (c.nmid > 0) hipLaunchKernelGGL((k_mid_setup<TM>), dim3(c.nmid), dim3(64), 0, st, m, c, x, A);

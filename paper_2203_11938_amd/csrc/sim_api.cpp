@@ -19,6 +19,8 @@
 #include <vector>
 
 #include "../../include/phisft_sim.h"
+#include "direct.h"
+#include "direct_kernels.h"
 #include "kernels.h"
 #include "mesh_prep.h"
 #include "sim_internal.h"
@@ -64,6 +66,22 @@ struct sim_s {
   double* minv_store = nullptr;
   std::vector<int> slot_step;             // step held by each slot, 0 = none
   std::vector<int> sweep_groups;          // first sweep workgroup of each launch, then total
+  // direct solver (use_direct): plan, device tables and the factors of kept steps; slot of
+  // step s: (s - 1) % slots
+  bool use_direct = false;
+  DsPlan dp;
+  DsArgs da{};
+  const DsTask *ds_factor = nullptr, *ds_solve = nullptr, *ds_res = nullptr;
+  const DsArgs* ds_args = nullptr;        // device copy of da
+  const DsArgs* ds_corr = nullptr;        // the same for a correction: A dx = r
+  double *ds_r = nullptr, *ds_dx = nullptr;
+  int ds_grid = 0;                        // workgroups of a launch
+  DsAccept dacc{};
+  std::vector<double*> ds_fac;            // factors of ds_fac.size() steps, kept between
+                                          // forward pass and adjoint; never moved (a graph
+                                          // captured by the caller holds their addresses)
+  bool ds_grad = false;                   // an adjoint has run: the factors are worth keeping
+  std::vector<int> ds_step;               // step held by each slot, 0 = none
   void* A = nullptr;
   void* Jinv = nullptr;
   double* rhs = nullptr;
@@ -102,6 +120,7 @@ struct sim_s {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     std::vector<int> slot_after;   // host slot bookkeeping after the captured call
+    std::vector<int> ds_after;
   };
   bool use_graph = false;
   hipStream_t cap_stream = nullptr;
@@ -124,6 +143,22 @@ namespace {
 constexpr int kCoarseMaxAggs = 320;
 // device memory for coarse operators kept between the forward pass and the adjoint
 constexpr double kCoarseStoreCap = 16.0 * (1 << 30);
+// the same for the direct solver's factors, which are taken from free memory when the
+// first adjoint shows that they are used: at most this, and a fifth of what is free
+constexpr double kFactorStoreCap = 32.0 * (1 << 30);
+// memory of the direct solver's workspace and one factor: sheets beyond it are solved
+// iteratively
+constexpr double kDirectWorkCap = 16.0 * (1 << 30);
+// tightest tolerance given to the direct solver
+constexpr double kDirectMinTol = 1e-12;
+// below this tolerance a solve whose residual misses it is corrected once by the solution
+// for that residual (measured residuals of one solve: up to 5e-11 on a 200x200 sheet, so
+// looser handles have no use for the three launches)
+constexpr double kDirectCorrectTol = 1e-9;
+// and below this one every solve is corrected: its residual, though it may meet the
+// tolerance, has no smooth part taken out as the iterative solver's has (momentum of an
+// unpinned 200x200 sheet at 1e-12: 1.7e-9 off after 8 steps without)
+constexpr double kDirectAlwaysTol = 1e-11;
 
 sim_status bits_to_status(int bits) {
   if (bits & ST_TIMEOUT) return SIM_E_HIP;
@@ -319,6 +354,123 @@ sim_status autotune(sim_t* s, const std::vector<HostPlan>& cands, const std::vec
   (void)hipEventDestroy(e1);
   s->stats.autotune_ms_per_iter = best_ms / (3.0 * kTuneIters);
   return SIM_OK;
+}
+
+// Positions of the sheets' rest shapes in the internal vertex order, [nv][3].
+std::vector<double> rest_internal(const sim_t* s, const std::vector<HostSheet>& sheets) {
+  const HostLayout& L = s->L;
+  std::vector<double> xr(3 * (size_t)L.nv);
+  for (int b = 0; b < L.ninst; ++b)
+    for (int q = 0; q < L.inst_nv[b]; ++q) {
+      const int i = L.inst_voff[b] + q, src = L.vold[i] - L.inst_voff[b];
+      for (int c = 0; c < 3; ++c) xr[3 * (size_t)i + c] = sheets[b].rest[3 * (size_t)src + c];
+    }
+  return xr;
+}
+
+// The direct solver serves handles that leave the solver to the library. An explicit
+// launch shape, matrix home, matrix precision or coarse space asks for the iterative
+// solver, and so does an iteration cap below the dimension (CG's own bound), which may
+// be meant to truncate the solve.
+bool want_direct(const sim_t* s, const sim_options& o) {
+  int most = 0;
+  for (int n : s->L.inst_nv) most = std::max(most, n);
+  sim_options d;
+  sim_default_options(&d);
+  return o.rows_per_block == 0 && o.matrix_home == SIM_MATRIX_AUTO && s->mprec == SIM_FP64 &&
+         o.coarse_size == d.coarse_size && o.cg_max_iter >= std::min(d.cg_max_iter, 3 * most) &&
+         o.cg_tol >= kDirectMinTol;
+}
+
+sim_status setup_direct(sim_t* s, const std::vector<HostSheet>& sheets) {
+  const HostLayout& L = s->L;
+  DsPlan& P = s->dp;
+  build_direct_plan(L.nv, L.maxnz, L.ell_col, L.inst_voff, L.inst_nv, rest_internal(s, sheets), P);
+  const double bytes = 8.0 * ((double)P.factor_doubles + (double)P.work_doubles);
+  if (!P.ok || bytes > kDirectWorkCap) return SIM_OK;
+  int dev = 0, ncu = 0, per_cu = 0;
+  HIPCHECK(s, hipGetDevice(&dev));
+  HIPCHECK(s, hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
+  HIPCHECK(s, ds_prepare(&per_cu));
+  s->ds_grid = std::max(1, per_cu * ncu);
+  DsArgs& a = s->da;
+  TRY(upload(s, P.fronts, &a.fr));
+  TRY(upload(s, P.kids, &a.kid));
+  TRY(upload(s, P.tab, &a.tab));
+  TRY(upload(s, P.factor_tasks, &s->ds_factor));
+  TRY(upload(s, P.solve_tasks, &s->ds_solve));
+  TRY(upload(s, P.res_tasks, &s->ds_res));
+  void* q = nullptr;
+  TRY(alloc(s, (size_t)P.factor_doubles * 8, &q)); s->ds_fac.assign(1, (double*)q);
+  TRY(alloc(s, (size_t)P.work_doubles * 8, &q)); a.ws = (double*)q;
+  const int counters = (P.counters + 31) / 32 * 32 + 64;   // + queue and abort flag
+  TRY(alloc(s, 4 * (size_t)counters, &q)); a.count = (int*)q;
+  HIPCHECK(s, hipMemset(a.count, 0, 4 * (size_t)counters));
+  a.queue = a.count + counters - 64;
+  a.abort_flag = a.count + counters - 32;
+  s->dacc.clear_ints = counters;
+  a.nv = L.nv;
+  a.maxnz = L.maxnz;
+  a.A = static_cast<const double*>(s->A);
+  a.sol = s->sol;
+  a.rhs = s->rhs;
+  TRY(upload(s, std::vector<DsArgs>(1, a), &s->ds_args));
+  if (s->cg_tol < kDirectCorrectTol) {
+    TRY(alloc(s, 3 * (size_t)L.nv * 8, &q)); s->ds_r = (double*)q;
+    TRY(alloc(s, 3 * (size_t)L.nv * 8, &q)); s->ds_dx = (double*)q;
+    DsArgs c = a;
+    c.rhs = s->ds_r;
+    c.sol = s->ds_dx;
+    TRY(upload(s, std::vector<DsArgs>(1, c), &s->ds_corr));
+  }
+  DsAccept& o = s->dacc;
+  o.ell_col = s->mesh.ell_col;
+  o.inst_voff = s->mesh.inst_voff;
+  o.inst_nv = s->mesh.inst_nv;
+  TRY(upload(s, P.res0, &o.inst_res0));
+  o.tol = s->cg_tol;
+  TRY(alloc(s, 2 * P.res_tasks.size() * 8, &q)); o.part = (double*)q;
+  TRY(alloc(s, 4 * (size_t)L.ninst, &q)); o.arrived = (int*)q;
+  HIPCHECK(s, hipMemset(o.arrived, 0, 4 * (size_t)L.ninst));
+  TRY(alloc(s, 4 * (size_t)L.ninst, &q)); o.done = (int*)q;
+  s->ds_step.assign(1, 0);
+  s->use_direct = true;
+  return SIM_OK;
+}
+
+// Room for the factors of up to `steps` steps once the handle is used for gradients. The
+// slots held stay where they are; nothing is allocated while the caller's stream is being
+// captured; without room the adjoint factorises again.
+void keep_factors(sim_t* s, int steps, hipStream_t stream) {
+  if (!s->use_direct || !s->ds_grad) return;
+  const int have = (int)s->ds_fac.size();
+  const int want = std::min(s->ckpt > 0 ? s->ckpt : steps, s->max_steps);
+  if (want <= have) return;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return;
+  size_t fre = 0, total = 0;
+  if (hipMemGetInfo(&fre, &total) != hipSuccess) return;
+  const double bytes = 8.0 * (double)s->dp.factor_doubles;
+  const double room = std::min(kFactorStoreCap - have * bytes, 0.2 * (double)fre);
+  // growing windows ask again and again: at least double what is held
+  int n = std::min(std::max(want, 2 * have), s->ckpt > 0 ? want : s->max_steps) - have;
+  n = (int)std::min((double)n, room / bytes);
+  if (n <= 0) return;
+  // relaxed: a capture that another thread or stream runs is not disturbed
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  void* q = nullptr;
+  const hipError_t e = hipMalloc(&q, (size_t)n * (size_t)bytes);
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    return;
+  }
+  s->allocs.push_back(q);
+  s->dev_bytes += (size_t)n * (size_t)bytes;
+  for (int k = 0; k < n; ++k)
+    s->ds_fac.push_back(static_cast<double*>(q) + (size_t)k * s->dp.factor_doubles);
+  s->ds_step.assign(s->ds_fac.size(), 0);
 }
 
 sim_status setup(sim_t* s, const std::vector<HostSheet>& sheets, double dt, const sim_options* opt) {
@@ -660,6 +812,7 @@ sim_status setup(sim_t* s, const std::vector<HostSheet>& sheets, double dt, cons
     TRY(alloc(s, 3 * state_bytes(s), &s->tmp));
     TRY(alloc(s, (size_t)s->ckpt * state_bytes(s), &s->seg));
   }
+  if (want_direct(s, o)) TRY(setup_direct(s, sheets));
   HIPCHECK(s, hipMemset(s->status, 0, 4 * (ni + 1)));
   HIPCHECK(s, hipMemset(s->it_fwd, 0, st * 4));
   HIPCHECK(s, hipMemset(s->it_rec, 0, st * 4));
@@ -673,12 +826,10 @@ sim_status setup(sim_t* s, const std::vector<HostSheet>& sheets, double dt, cons
   // the step system of the rest state
   s->stats.autotune_candidates = (int)feasible.size();
   if (o.autotune && feasible.size() > 1) {
+    const std::vector<double> xi = rest_internal(s, sheets);
     std::vector<double> xr(3 * nv);
-    for (int b = 0; b < L.ninst; ++b)
-      for (int q2 = 0; q2 < L.inst_nv[b]; ++q2) {
-        const int i = L.inst_voff[b] + q2, src = L.vold[i] - L.inst_voff[b];
-        for (int c = 0; c < 3; ++c) xr[(size_t)c * nv + i] = sheets[b].rest[3 * (size_t)src + c];
-      }
+    for (size_t i = 0; i < nv; ++i)
+      for (int c = 0; c < 3; ++c) xr[(size_t)c * nv + i] = xi[3 * i + c];
     int pick = best;
     TRY(s->mprec == SIM_FP64 ? autotune<double>(s, feasible, xr, &pick)
                              : autotune<float>(s, feasible, xr, &pick));
@@ -714,9 +865,9 @@ Coarse coarse_for_step(sim_t* s, int step, bool* have) {
   return c;
 }
 
-// Solver launch bracketed by timing events when timing is enabled.
-template <typename TM>
-void timed_pcg(sim_t* s, const Coarse& cs, const PcgArgs<TM>& c, hipStream_t st) {
+// Runs the solver launches `body`, bracketed by timing events when timing is enabled.
+template <class Body>
+void timed(sim_t* s, hipStream_t st, Body&& body) {
   if (s->timing) {
     if (s->ev_used + 2 > s->ev.size()) {
       for (int k = 0; k < 64; ++k) {
@@ -727,13 +878,58 @@ void timed_pcg(sim_t* s, const Coarse& cs, const PcgArgs<TM>& c, hipStream_t st)
     }
     if (s->ev_used + 2 <= s->ev.size()) {
       (void)hipEventRecord(s->ev[s->ev_used], st);
-      launch_pcg<TM>(s->mesh, s->plan, s->sw, cs, c, st);
+      body();
       (void)hipEventRecord(s->ev[s->ev_used + 1], st);
       s->ev_used += 2;
       return;
     }
   }
-  launch_pcg<TM>(s->mesh, s->plan, s->sw, cs, c, st);
+  body();
+}
+
+// Solves the assembled step matrix of step `step` at positions xp for c.rhs. Direct
+// handles factorise (or reuse the step's kept factor when `reuse`), solve and check the
+// true residual; the launches of the iterative solver that follow leave a sheet alone
+// whose solve was accepted. (Its coarse operators are then rebuilt when needed: the
+// kept slots belong to iterative handles.)
+template <typename TM>
+void solve_step(sim_t* s, int step, const double* xp, PcgArgs<TM> c, bool reuse, hipStream_t st) {
+  if (s->use_direct) {
+    timed(s, st, [&] {
+      const int slot = (step - 1) % (int)s->ds_fac.size();
+      double* fac = s->ds_fac[slot];
+      const bool factor = !(reuse && s->ds_step[slot] == step);
+      launch_ds_run(s->ds_args, fac, factor ? s->ds_factor : s->ds_solve,
+                    (int)(factor ? s->dp.factor_tasks : s->dp.solve_tasks).size(), factor,
+                    s->ds_grid, nullptr, 0, st);
+      s->ds_step[slot] = step;
+      DsAccept o = s->dacc;
+      o.iters = c.iters;
+      o.resid = c.resid;
+      o.res = s->ds_r;
+      if (s->ds_corr && s->cg_tol < kDirectAlwaysTol) o.tol = 0.0;
+      launch_ds_resid(s->da, o, s->ds_res, (int)s->dp.res_tasks.size(), st);
+      if (s->ds_corr) {
+        launch_ds_run(s->ds_corr, fac, s->ds_solve, (int)s->dp.solve_tasks.size(), false, s->ds_grid,
+                      o.done, s->L.ninst, st);
+        launch_ds_add(s->da, o, s->ds_dx, s->mesh.vert_inst, st);
+        o.res = nullptr;
+        o.again = 1;
+        o.tol = s->cg_tol;
+        launch_ds_resid(s->da, o, s->ds_res, (int)s->dp.res_tasks.size(), st);
+      }
+      Coarse cs = s->coarse;
+      cs.done = c.done = o.done;
+      launch_coarse_setup<TM>(s->mesh, cs, xp, c.A, s->L.coarse_doubles, s->sweep_groups, st);
+      launch_pcg<TM>(s->mesh, s->plan, s->sw, cs, c, st);
+    });
+    return;
+  }
+  bool have = false;
+  const Coarse cs = coarse_for_step(s, step, &have);
+  if (!(reuse && have))
+    launch_coarse_setup<TM>(s->mesh, cs, xp, c.A, s->L.coarse_doubles, s->sweep_groups, st);
+  timed(s, st, [&] { launch_pcg<TM>(s->mesh, s->plan, s->sw, cs, c, st); });
 }
 
 // ---------------------------------------------------------- step sequences
@@ -761,10 +957,6 @@ void forward_step(sim_t* s, int step, const char* sp, char* sn, const T* F, cons
   a.b = s->rhs;
   a.status = s->status;
   launch_assemble<T, TM>(s->mesh, s->el, a, st);
-  bool have = false;
-  const Coarse cs = coarse_for_step(s, step, &have);
-  if (!(reuse && have))
-    launch_coarse_setup<TM>(s->mesh, cs, xp, a.A, s->L.coarse_doubles, s->sweep_groups, st);
   PcgArgs<TM> c{};
   c.A = a.A;
   c.Jinv = a.Jinv;
@@ -775,7 +967,7 @@ void forward_step(sim_t* s, int step, const char* sp, char* sn, const T* F, cons
   c.iters = iters;
   c.resid = resid;
   c.status = s->status;
-  timed_pcg<TM>(s, cs, c, st);
+  solve_step<TM>(s, step, xp, c, reuse, st);
   launch_update<T>(s->mesh, xp, vp, s->sol, s->h, xn, vn, xout, s->status, st);
 }
 
@@ -832,12 +1024,6 @@ void adjoint_step(sim_t* s, int k, const char* sp, const char* sn, const T* dl, 
   a.b = nullptr;
   a.status = s->status;
   launch_assemble<T, TM>(s->mesh, s->el, a, st);
-  // the step's coarse operator: kept from the forward pass or the recompute when the
-  // handle stores them, else rebuilt (the same kernels on the same inputs)
-  bool have = false;
-  const Coarse cs = coarse_for_step(s, k, &have);
-  if (!have)
-    launch_coarse_setup<TM>(s->mesh, cs, xp, a.A, s->L.coarse_doubles, s->sweep_groups, st);
   PcgArgs<TM> c{};
   c.A = a.A;
   c.Jinv = a.Jinv;
@@ -848,7 +1034,9 @@ void adjoint_step(sim_t* s, int k, const char* sp, const char* sn, const T* dl, 
   c.iters = s->it_adj + (size_t)(k - 1) * ni;
   c.resid = s->res_adj + (size_t)(k - 1) * ni;
   c.status = s->status;
-  timed_pcg<TM>(s, cs, c, st);
+  // the step's factor or coarse operator: kept from the forward pass or the recompute when
+  // the handle stores them, else rebuilt (the same kernels on the same inputs)
+  solve_step<TM>(s, k, xp, c, true, st);
   AdjArgs<T> j{};
   j.x = xp;
   j.vp = vp;
@@ -928,6 +1116,7 @@ sim_status graphed(sim_t* s, sim_t::GraphCache& gc, const std::vector<uintptr_t>
   if (!s->use_graph || s->timing) return body(user);
   if (gc.valid && gc.key == key) {
     s->slot_step = gc.slot_after;
+    s->ds_step = gc.ds_after;
     HIPCHECK(s, hipGraphLaunch(gc.exec, user));
     ++s->graph_replays;
     return SIM_OK;
@@ -947,6 +1136,7 @@ sim_status graphed(sim_t* s, sim_t::GraphCache& gc, const std::vector<uintptr_t>
   HIPCHECK(s, hipGraphInstantiate(&gc.exec, g, nullptr, nullptr, 0));
   gc.key = key;
   gc.slot_after = s->slot_step;
+  gc.ds_after = s->ds_step;
   gc.valid = true;
   ++s->graph_captures;
   HIPCHECK(s, hipGraphLaunch(gc.exec, user));
@@ -1101,9 +1291,10 @@ sim_status sim_rollout(sim_t* s, int32_t n_steps, const void* x0, const void* v0
                        const void* forces, const void* material, const void* wind,
                        const int32_t* loss_frames, int32_t n_loss, void* x_out, void* stream) {
   TRY(begin_rollout(s, n_steps, x0, forces, material, wind, loss_frames, n_loss, x_out, stream));
+  keep_factors(s, n_steps, s->stream);
   std::vector<uintptr_t> key = {(uintptr_t)n_steps, (uintptr_t)x0, (uintptr_t)v0,
                                 (uintptr_t)forces, (uintptr_t)s->material, (uintptr_t)wind,
-                                (uintptr_t)x_out};
+                                (uintptr_t)x_out, s->ds_fac.size()};
   key.insert(key.end(), s->frames.begin(), s->frames.end());
   const sim_status st = graphed(s, s->gfwd, key, s->stream, [&](hipStream_t q) {
     return run_rollout(s, n_steps, x0, v0, x_out, q);
@@ -1159,9 +1350,14 @@ sim_status sim_adjoint(sim_t* s, const void* dl_dx, void* dl_dmaterial, void* dl
     return SIM_E_INVALID;
   }
   s->stream = static_cast<hipStream_t>(stream);
+  if (!s->ds_grad) {
+    s->ds_grad = true;
+    keep_factors(s, s->n_steps, s->stream);
+  }
   // the adjoint reads the rollout's states, forces and material: its key includes them
   std::vector<uintptr_t> key = {(uintptr_t)dl_dx, (uintptr_t)dl_dmaterial, (uintptr_t)dl_dwind,
-                                (uintptr_t)dl_dforces, (uintptr_t)dl_dx0, (uintptr_t)dl_dv0};
+                                (uintptr_t)dl_dforces, (uintptr_t)dl_dx0, (uintptr_t)dl_dv0,
+                                s->ds_fac.size()};
   key.insert(key.end(), s->gfwd.key.begin(), s->gfwd.key.end());
   s->have_adjoint = true;
   return graphed(s, s->gadj, key, s->stream, [&](hipStream_t q) {
