@@ -18,8 +18,8 @@
 // What bounds it: the chain of fronts from a leaf to the root (15 of a 64x64 sheet), each
 // a pivot sweep and three hand-offs between workgroups, not the arithmetic (1.3 GFLOP).
 // A forward and adjoint of 60 steps on that sheet took 140 ms with the iterative solver
-// (100 to 300 iterations of 5 to 12 us a solve) and take 54 ms with this one; 40 solves of a
-// 17x17 sheet 67 and 12 ms, 30 forward and adjoint steps of a 200x200 sheet 427 and 233 ms.
+// (100 to 300 iterations of 5 to 12 us a solve) and take 51 ms with this one; 40 solves of a
+// 17x17 sheet 67 and 11 ms, 30 forward and adjoint steps of a 200x200 sheet 427 and 225 ms.
 // Workgroups take the tasks in a topological order from one queue and wait on per-front
 // counters, so the only tasks ever waited for have been taken by workgroups that run:
 // no co-residency is needed, and a launch per level and kind (75 launches of at least
@@ -47,12 +47,13 @@ constexpr int kThreads = 512;
 constexpr int kWaves = kThreads / 64;
 constexpr int kSide = 3 * kDsMaxPiv / kDsTile;   // tiles of the largest pivot block
 constexpr int kLd = 3 * kDsMaxPiv + 2;           // LDS row stride of the blocks
+constexpr int kLdT = 18;                         // LDS row stride of a 16x16 tile
 constexpr int kLdK = 50;                         // LDS row stride of a Schur operand's half
 constexpr int kLds = 3 * kDsMaxPiv * kLd;        // doubles of dynamic LDS
 constexpr int kSpinLimit = 1 << 22;              // polls of a wait (seconds)
 static_assert(kDsMaxBorder + 3 * kDsMaxPiv + 16 * 33 <= kLds, "backward task's vectors");
 static_assert(2 * kDsSchurTile * kLdK <= kLds, "Schur operands");
-static_assert((5 * kSide + 1) * 256 <= kLds, "pivot sweep panels and diagonal");
+static_assert((3 * kSide + 3) * 16 * kLdT <= kLds, "pivot sweep panels and diagonal");
 
 __device__ __forceinline__ dbl4 mfma4(double a, double b, dbl4 c) {
   // A operand: lane l holds row l % 16, column l / 16; B: row l / 16, column l % 16;
@@ -68,12 +69,12 @@ __device__ __forceinline__ double lane_value(double v, int lane) {
   return *reinterpret_cast<double*>(&r);
 }
 
-// Reciprocal by Newton-Raphson refinement of the hardware estimate (two steps of
-// x <- x + x (1 - a x), each squaring the relative error).
+// Reciprocal from the hardware estimate x and its error e = 1 - a x: x (1 + e + e^2),
+// which leaves e^3 (1 / a = x / (1 - e)).
 __device__ __forceinline__ double recip(double a) {
-  double x = __builtin_amdgcn_rcp(a);
-  x = fma(x, fma(-a, x, 1.0), x);
-  return fma(x, fma(-a, x, 1.0), x);
+  const double x = __builtin_amdgcn_rcp(a);
+  const double e = fma(-a, x, 1.0);
+  return fma(x, fma(e, e, e), x);
 }
 
 // Symmetric sweep of a symmetric 16x16 tile in the matrix cores' C layout on one
@@ -83,54 +84,57 @@ __device__ __forceinline__ double recip(double a) {
 // which after all pivots leaves -M^-1. By symmetry the pivot rows in C layout are at once
 // the A operand (R^T) and the B operand of a rank-4 update, so each step is two matrix
 // instructions; the pivot columns come out of the same update with -Q in their place of
-// the B operand and zero in the accumulator (nothing cancels). The 4x4 blocks are
-// inverted by LDL^T from lane broadcasts, every lane solving for one column. False if a
-// pivot is not positive.
+// the B operand and zero in the accumulator (nothing cancels). The 4x4 block is inverted
+// in 2x2 blocks from lane broadcasts (two reciprocals in a row instead of four: 860
+// cycles a step where elimination column by column took 970), the determinants with the
+// products' rounding errors included. False if a pivot is not positive.
+__device__ __forceinline__ double det2(double a, double b, double c) {
+  const double bb = b * b;
+  return fma(a, c, -bb) - fma(b, b, -bb);
+}
 __device__ __forceinline__ bool sweep16(dbl4& d, int lane) {
-  const int g = lane >> 4, c = lane & 15;
+  const int g = lane >> 4, c = lane & 15, c4 = c & 3;
   bool good = true;
 #pragma unroll
   for (int kb = 0; kb < 4; ++kb) {
     const double R = d[kb];
-    const double p00 = lane_value(R, 4 * kb);
-    const double p10 = lane_value(R, 16 + 4 * kb), p11 = lane_value(R, 16 + 4 * kb + 1);
-    const double p20 = lane_value(R, 32 + 4 * kb), p21 = lane_value(R, 32 + 4 * kb + 1),
-                 p22 = lane_value(R, 32 + 4 * kb + 2);
-    const double p30 = lane_value(R, 48 + 4 * kb), p31 = lane_value(R, 48 + 4 * kb + 1),
-                 p32 = lane_value(R, 48 + 4 * kb + 2), p33 = lane_value(R, 48 + 4 * kb + 3);
-    const double r0 = recip(p00);
-    const double l10 = p10 * r0, l20 = p20 * r0, l30 = p30 * r0;
-    const double d1 = fma(-l10, p10, p11);
-    const double u21 = fma(-l20, p10, p21), u31 = fma(-l30, p10, p31);
-    const double r1 = recip(d1);
-    const double l21 = u21 * r1, l31 = u31 * r1;
-    const double d2 = fma(-l21, u21, fma(-l20, p20, p22));
-    const double u32 = fma(-l31, u21, fma(-l30, p20, p32));
-    const double r2 = recip(d2);
-    const double l32 = u32 * r2;
-    const double d3 = fma(-l32, u32, fma(-l31, u31, fma(-l30, p30, p33)));
-    const double r3 = recip(d3);
-    good = good && p00 > 0.0 && d1 > 0.0 && d2 > 0.0 && d3 > 0.0 && isfinite(p00) &&
-           isfinite(d1) && isfinite(d2) && isfinite(d3);
-    // column g of Q
-    const double y0 = g == 0 ? 1.0 : 0.0;
-    const double y1 = fma(-l10, y0, g == 1 ? 1.0 : 0.0);
-    const double y2 = fma(-l21, y1, fma(-l20, y0, g == 2 ? 1.0 : 0.0));
-    const double y3 = fma(-l32, y2, fma(-l31, y1, fma(-l30, y0, g == 3 ? 1.0 : 0.0)));
-    const double q3 = y3 * r3;
-    const double q2 = fma(-l32, q3, y2 * r2);
-    const double q1 = fma(-l31, q3, fma(-l21, q2, y1 * r1));
-    const double q0 = fma(-l30, q3, fma(-l20, q2, fma(-l10, q1, y0 * r0)));
-    const double lo = (c & 1) ? q1 : q0, hi = (c & 1) ? q3 : q2;
-    const double sel = (c & 2) ? hi : lo;             // Q[c % 4][g]
+    const double a = lane_value(R, 4 * kb), b = lane_value(R, 16 + 4 * kb),
+                 e = lane_value(R, 16 + 4 * kb + 1);
+    const double m00 = lane_value(R, 32 + 4 * kb), m01 = lane_value(R, 32 + 4 * kb + 1),
+                 m10 = lane_value(R, 48 + 4 * kb), m11 = lane_value(R, 48 + 4 * kb + 1);
+    const double s00 = lane_value(R, 32 + 4 * kb + 2), s10 = lane_value(R, 48 + 4 * kb + 2),
+                 s11 = lane_value(R, 48 + 4 * kb + 3);
+    // I = [a b; b e]^-1, L = [m] I, J = ([s] - L [m]^T)^-1
+    const double da = det2(a, b, e), ra = recip(da);
+    const double i00 = e * ra, i01 = -b * ra, i11 = a * ra;
+    const double l00 = fma(m00, i00, m01 * i01), l01 = fma(m00, i01, m01 * i11);
+    const double l10 = fma(m10, i00, m11 * i01), l11 = fma(m10, i01, m11 * i11);
+    const double t00 = s00 - fma(l00, m00, l01 * m01);
+    const double t10 = s10 - fma(l10, m00, l11 * m01);
+    const double t11 = s11 - fma(l10, m10, l11 * m11);
+    const double dt = det2(t00, t10, t11), rt = recip(dt);
+    const double j00 = t11 * rt, j01 = -t10 * rt, j11 = t00 * rt;
+    good = good && a > 0.0 && da > 0.0 && t00 > 0.0 && dt > 0.0;
+    // Q = [I + L^T K, -K^T; -K, J], K = J L
+    const double k00 = fma(j00, l00, j01 * l10), k01 = fma(j00, l01, j01 * l11);
+    const double k10 = fma(j01, l00, j11 * l10), k11 = fma(j01, l01, j11 * l11);
+    const double q00 = fma(l00, k00, fma(l10, k10, i00)), q01 = fma(l00, k01, fma(l10, k11, i01)),
+                 q11 = fma(l01, k01, fma(l11, k11, i11));
+    // this lane's entry Q[c % 4][g]
+    const bool g1 = g & 1, c1 = c & 1;
+    const double qi = c1 ? (g1 ? q11 : q01) : (g1 ? q01 : q00);
+    const double qj = c1 ? (g1 ? j11 : j01) : (g1 ? j01 : j00);
+    const int row = g < 2 ? c4 : g, col = g < 2 ? g : c4;   // below the diagonal blocks
+    const double qk = (row & 1) ? ((col & 1) ? k11 : k10) : ((col & 1) ? k01 : k00);
+    const double sel = (g < 2) == (c4 < 2) ? (g < 2 ? qi : qj) : -qk;
     const dbl4 zero = {0.0, 0.0, 0.0, 0.0};
     const dbl4 v = mfma4(c < 4 ? sel : 0.0, R, zero);  // rows 0..3: Q R
     const bool piv = (c >> 2) == kb;
     const double V = piv ? -sel : v[0];
-    dbl4 a;
+    dbl4 acc;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) a[q] = piv ? 0.0 : d[q];
-    d = mfma4(-R, V, a);
+    for (int q = 0; q < 4; ++q) acc[q] = piv ? 0.0 : d[q];
+    d = mfma4(-R, V, acc);
     d[kb] = V;
   }
   return good;
@@ -156,6 +160,14 @@ __device__ __forceinline__ double row_sum(double v) {
 // Stores that reach memory, for data other workgroups of the launch read.
 __device__ __forceinline__ void put(double* p, double v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The same for 16 bytes at p + 8 e, p uniform: a buffer store past the caches.
+__device__ __forceinline__ void put2(double* p, int e, double2 v) {
+  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+  constexpr int kRaw = 0x00027000, kSc1 = 16;
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(p, 0, -1, kRaw);
+  __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4*>(&v), r, 8 * e, 0, kSc1);
 }
 
 __device__ __forceinline__ double2 get2(const double* p) {
@@ -272,13 +284,16 @@ __device__ __forceinline__ void stage_map(Table<DsArgs> a, Table<DsChild> K, int
   if (c < 3 * K->q) sh.map[slot][c] = 3 * a->tab[K->map + c / 3] + c % 3;
 }
 
-// X = F_pp^-1. F_pp is gathered into LDS (A's entries, then the children's updates in
-// order), then held as 16x16 tiles: the diagonal ones by wavefront 0 in LDS, the others
-// in the registers of the rest. Per tile row k, wavefront 0 brings tile (k, k) up to date
-// and sweeps it while the others apply step k - 1 to their tiles and publish row k; the
-// row is then scaled by the inverse, and old and scaled row are the operands of the
-// rank-16 updates. Wavefront 0 updates its later diagonal tiles while the row is scaled,
-// so a step costs one 16x16 sweep and one scaling.
+// X = F_pp^-1. The lower triangle of F_pp is gathered into LDS (A's entries, then the
+// children's updates in order), then held as 16x16 tiles by wavefronts 1 to 7, three
+// each at most; wavefront 0 carries the chain. Per tile row k, phase A: wavefront 0
+// applies step k - 1 to tile (k, k) and sweeps it, publishing -Q (Q its inverse); the
+// others apply step k - 1 to their tiles and publish the old row k, R (the part right of
+// the diagonal transposed), and tile (k + 1, k + 1). Phase B: V = Q R is formed, a column
+// tile per wavefront; wavefront 0 takes column k + 1, the one it goes on with, from and
+// into registers. So the chain per step is one 16x16 sweep, eight matrix instructions and
+// two barriers, and everything else runs beside the sweep: a 96x96 block takes 13.6 us
+// where updating the diagonal tiles on wavefront 0 as well took 19.0 us.
 // A front whose sweep meets a non-positive pivot stores NaN: its solution fails the
 // residual test.
 __device__ __forceinline__ bool task_pivot(Table<DsArgs> a, Table<DsFront> F, double* fac,
@@ -302,7 +317,6 @@ __device__ __forceinline__ bool task_pivot(Table<DsArgs> a, Table<DsFront> F, do
       for (int c = 0; c < 3; ++c) {
         if (l == i && c < r) continue;
         lds[(3 * l + c) * kLd + 3 * i + r] = x[3 * r + c];
-        lds[(3 * i + r) * kLd + 3 * l + c] = x[3 * r + c];
       }
   }
   if (!wait_children(a, F, kDsHeadDone, F->khead[0], F->khead[1], sh)) return false;
@@ -333,146 +347,138 @@ __device__ __forceinline__ bool task_pivot(Table<DsArgs> a, Table<DsFront> F, do
       if (r >= nq) continue;
       const int pr = map[r];
       if (lane <= r) {
-        const int p0 = map[lane];
-        const double x = lds[pr * kLd + p0] + s0[q];
-        lds[pr * kLd + p0] = x;
-        lds[p0 * kLd + pr] = x;
+        lds[pr * kLd + map[lane]] += s0[q];
       }
-      if (q >= NR - N1 && lane + 64 <= r) {
-        const int p1 = map[lane + 64];
-        const double x = lds[pr * kLd + p1] + s1[q - (NR - N1)];
-        lds[pr * kLd + p1] = x;
-        lds[p1 * kLd + pr] = x;
-      }
+      if (q >= NR - N1 && lane + 64 <= r) lds[pr * kLd + map[lane + 64]] += s1[q - (NR - N1)];
     }
   }
   sync();
   const int g = lane >> 4, c16 = lane & 15;
-  // wavefront 0: the diagonal tiles, in LDS; the others: the off-diagonal tiles in turn, in
-  // registers
-  constexpr int NS = (kSide * (kSide - 1) + kWaves - 2) / (kWaves - 1);
+  constexpr int NS = (kSide * (kSide + 1) / 2 + kWaves - 2) / (kWaves - 1);
+  constexpr int TL = 16 * kLdT;            // a tile in LDS
   dbl4 d[NS];
   int ti[NS], tj[NS];
 #pragma unroll
   for (int s = 0; s < NS; ++s) {
     const int e = (wave - 1) + (kWaves - 1) * s;
-    const bool own = wave > 0 && e < T * (T - 1);
-    ti[s] = own ? e / (T - 1) : -1;
-    tj[s] = own ? e - ti[s] * (T - 1) : -1;
-    if (own && tj[s] >= ti[s]) ++tj[s];
+    const bool own = wave > 0 && e < T * (T + 1) / 2;
+    int i = 0;
+    while ((i + 1) * (i + 2) / 2 <= e) ++i;
+    ti[s] = own ? i : -1;
+    tj[s] = own ? e - i * (i + 1) / 2 : -1;
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-      d[s][q] = own ? lds[(16 * ti[s] + 4 * q + g) * kLd + 16 * tj[s] + c16] : 0.0;
+    for (int q = 0; q < 4; ++q) {
+      const int r = 16 * ti[s] + 4 * q + g, c = 16 * tj[s] + c16;
+      d[s][q] = own ? lds[max(r, c) * kLd + min(r, c)] : 0.0;
+    }
   }
-  double dg[kSide][4];
+  dbl4 v = {0.0, 0.0, 0.0, 0.0}, vr = v, vv = v;   // wavefront 0: tile (k, k), R and V of column k
   if (wave == 0) {
 #pragma unroll
-    for (int s = 0; s < kSide; ++s)
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        dg[s][q] = s < T ? lds[(16 * s + 4 * q + g) * kLd + 16 * s + c16] : 0.0;
+    for (int q = 0; q < 4; ++q) {
+      const int r = 4 * q + g;
+      v[q] = lds[max(r, c16) * kLd + min(r, c16)];
+    }
   }
   sync();
-  double* Rl = lds;                        // [2][T] old rows, tiles in C layout
-  double* Vl = Rl + 2 * kSide * 256;       // [2][T] scaled rows
-  double* Dl = Vl + 2 * kSide * 256;       // [T] diagonal tiles
-  double* Pl = Dl + kSide * 256;
-  if (wave == 0) {
+  double* Rl = lds;                        // [2][T] old rows
+  double* Vl = Rl + 2 * kSide * TL;        // [T] scaled rows
+  double* Pl = Vl + kSide * TL;            // [2] -Q
+  double* Dl = Pl + 2 * TL;                // the next diagonal tile
+  const int at = g * kLdT + c16;
+  auto load = [&](const double* t) {
+    dbl4 x;
 #pragma unroll
-    for (int s = 0; s < kSide; ++s)
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if (s < T) Dl[s * 256 + 64 * q + lane] = dg[s][q];
-  }
-  // applies step k to a tile
-  auto update = [&](dbl4 v, int i, int j, int k) {
-    const double* R = Rl + ((k & 1) * kSide + i) * 256;
-    const double* V = Vl + ((k & 1) * kSide + j) * 256;
-    if (j == k) v = dbl4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int q = 0; q < 4; ++q) v = mfma4(-R[64 * q + lane], V[64 * q + lane], v);
-    return v;
+    for (int q = 0; q < 4; ++q) x[q] = t[4 * q * kLdT + at];
+    return x;
   };
-  auto load_diag = [&](int s) {
-    dbl4 v;
+  auto store = [&](double* t, const dbl4& x) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = Dl[s * 256 + 64 * q + lane];
-    return v;
+    for (int q = 0; q < 4; ++q) t[4 * q * kLdT + at] = x[q];
   };
-  auto store_diag = [&](int s, dbl4 v) {
+  // this wavefront's tile s after step k
+  auto step = [&](int s, int k) {
+    if (ti[s] == k) {
+      d[s] = load(tj[s] == k ? Pl + (k & 1) * TL : Vl + tj[s] * TL);
+      return;
+    }
+    const dbl4 r = load(Rl + ((k & 1) * kSide + ti[s]) * TL);
+    const dbl4 x = load(tj[s] == k ? Pl + (k & 1) * TL : Vl + tj[s] * TL);
+    if (tj[s] == k) d[s] = dbl4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int q = 0; q < 4; ++q) Dl[s * 256 + 64 * q + lane] = v[q];
+    for (int q = 0; q < 4; ++q) d[s] = mfma4(-r[q], x[q], d[s]);
   };
 #pragma unroll 1
   for (int k = 0; k < T; ++k) {
-    double* Rk = Rl + (k & 1) * kSide * 256;
-    double* Vk = Vl + (k & 1) * kSide * 256;
+    double* Rk = Rl + (k & 1) * kSide * TL;
+    double* Pk = Pl + (k & 1) * TL;
     if (wave == 0) {
       __builtin_amdgcn_s_setprio(3);
-      dbl4 v = load_diag(k);
-      if (k > 0) v = update(v, k, k, k - 1);
-      const bool good = sweep16(v, lane);
-      store_diag(k, v);
+      if (k > 0) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        Pl[64 * q + lane] = -v[q];
-        Vk[k * 256 + 64 * q + lane] = v[q];   // in V's place for the pivot column
+        for (int q = 0; q < 4; ++q) v = mfma4(-vr[q], vv[q], v);
       }
-      if (!good && lane == 0) sh.bad = 1;
-      __builtin_amdgcn_s_setprio(0);
+      if (!sweep16(v, lane) && lane == 0) sh.bad = 1;
+      store(Pk, v);
     } else {
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
         if (ti[s] < 0) continue;
-        if (k > 0 && ti[s] != k - 1) d[s] = update(d[s], ti[s], tj[s], k - 1);
-        if (ti[s] == k) {
+        if (k > 0) step(s, k - 1);
+        if (ti[s] == k && tj[s] < k) store(Rk + tj[s] * TL, d[s]);
+        if (tj[s] == k && ti[s] > k) {
 #pragma unroll
-          for (int q = 0; q < 4; ++q) Rk[tj[s] * 256 + 64 * q + lane] = d[s][q];
+          for (int q = 0; q < 4; ++q) Rk[ti[s] * TL + c16 * kLdT + 4 * q + g] = d[s][q];
         }
+        if (ti[s] == k + 1 && tj[s] == k + 1) store(Dl, d[s]);
       }
     }
     sync();
     if (wave == 0) {
-      if (k > 0) {
-#pragma unroll 1
-        for (int s = 0; s < T; ++s)
-          if (s != k && s != k - 1) store_diag(s, update(load_diag(s), s, s, k - 1));
+      if (k + 1 < T) {
+        vr = load(Rk + (k + 1) * TL);
+        vv = dbl4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) vv = mfma4(-v[q], vr[q], vv);
+        v = load(Dl);
+        store(Vl + (k + 1) * TL, vv);
       }
-    } else {
+      __builtin_amdgcn_s_setprio(0);
+    } else if (wave <= T && wave - 1 != k && wave - 1 != k + 1) {
+      const dbl4 p = load(Pk), r = load(Rk + (wave - 1) * TL);
+      dbl4 x = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        if (ti[s] != k) continue;
-        dbl4 v = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) v = mfma4(Pl[64 * q + lane], d[s][q], v);
-        d[s] = v;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) Vk[tj[s] * 256 + 64 * q + lane] = v[q];
-      }
+      for (int q = 0; q < 4; ++q) x = mfma4(-p[q], r[q], x);
+      store(Vl + (wave - 1) * TL, x);
     }
     sync();
   }
   const bool bad = sh.bad != 0;
-  double* X = fac + F->xo;
-  auto store = [&](dbl4 v, int i, int j) {
+  if (wave > 0) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-      put(X + (size_t)(16 * i + 4 * q + g) * np + 16 * j + c16, bad ? NAN : -v[q]);
-  };
-  if (wave == 0) {
-#pragma unroll 1
-    for (int s = 0; s < T; ++s) {
-      dbl4 v = load_diag(s);
-      if (s != T - 1) v = update(v, s, s, T - 1);
-      store(v, s, s);
-    }
-  } else {
+    for (int s = 0; s < NS; ++s)
+      if (ti[s] >= 0) step(s, T - 1);
+  }
+  sync();
+  // X = -M by way of LDS, both triangles, then rows of it with 16-byte stores
+  if (wave > 0) {
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       if (ti[s] < 0) continue;
-      if (ti[s] != T - 1) d[s] = update(d[s], ti[s], tj[s], T - 1);
-      store(d[s], ti[s], tj[s]);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int r = 16 * ti[s] + 4 * q + g, c = 16 * tj[s] + c16;
+        const double x = bad ? NAN : -d[s][q];
+        lds[r * kLd + c] = x;
+        if (ti[s] != tj[s]) lds[c * kLd + r] = x;
+      }
     }
+  }
+  sync();
+  double* X = fac + F->xo;
+  for (int e = tid; e < np * np / 2; e += kThreads) {
+    const int r = 2 * e / np, c = 2 * e - r * np;
+    put2(X, 2 * e, *reinterpret_cast<const double2*>(lds + r * kLd + c));
   }
   signal(a, F->cnt + kDsPivotDone);
   return true;
