@@ -49,13 +49,34 @@ struct DsChild {
   int cnt, nhead, nschur, nfwd;   // the child's counters and numbers of tasks
   int q, inv, map;
   int nb;
+  int g;                          // the child's border vector
   long long so;
 };
 
-// One unit of work of a front. a: row tile, chunk, or I << 16 | J.
+// One unit of work of a front. a: row tile, chunk, or I << 16 | J. The record holds
+// all that a task looks up before its first data (the front, its first two children and
+// the index lists of its rows), so that a workgroup can fetch it during the task before:
+// the chain of lookups task, front, child, list took 4 us of a Schur task's 12 us.
 enum DsKind { kDsPivot = 0, kDsBorder, kDsSchur, kDsForward, kDsBackward };
-struct DsTask {
+struct alignas(16) DsTask {
   int kind, front, a;
+  int lo, hi;            // border: entries of A, pairs tab[2 lo .. 2 hi)
+  int pad[3];
+  DsFront f;
+  DsChild kid[2];
+  // border indices in children 0 and 1 of the vertices of the task's rows (from vertex
+  // row0 / 3 on; border, Schur, forward) and ...
+  short row[2][24];
+  // ... of its columns (Schur) or the pivots (forward), -1: none; pivot and border: the
+  // local indices of the child's first border vertices (its q pivots of the front)
+  short col[2][32];
+  int pad2[4];
+};
+static_assert(sizeof(DsTask) == 512, "fetched by one wavefront, 8 bytes a lane");
+
+// Residual rows of a sheet: from row0 on.
+struct DsRows {
+  int sheet, row0;
 };
 
 // Completion counters of a front: Schur tiles that hold a parent's pivots (tile rows 0 and
@@ -76,7 +97,7 @@ struct DsPlan {
   // tasks in an order in which every task comes after those it waits for: factorisation
   // with both passes of one right-hand side, and the two passes alone
   std::vector<DsTask> factor_tasks, solve_tasks;
-  std::vector<DsTask> res_tasks;   // (0, sheet, first row) of the residual
+  std::vector<DsRows> res_tasks;   // of the residual
   std::vector<int> res0;           // [sheets + 1]
   long long factor_doubles = 0, work_doubles = 0;
   int counters = 0;

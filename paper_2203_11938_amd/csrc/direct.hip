@@ -162,24 +162,55 @@ __device__ __forceinline__ void put(double* p, double v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The same for 16 bytes at p + 8 e, p uniform: a buffer store past the caches.
-__device__ __forceinline__ void put2(double* p, int e, double2 v) {
-  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-  constexpr int kRaw = 0x00027000, kSc1 = 16;
-  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(p, 0, -1, kRaw);
-  __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4*>(&v), r, 8 * e, 0, kSc1);
-}
-
-__device__ __forceinline__ double2 get2(const double* p) {
-  return *reinterpret_cast<const double2*>(p);
-}
-
 // The workgroup's barrier. The wait for this wavefront's own LDS accesses is written out:
 // hipcc leaves it away at the head of the task loop, where the access in flight is on the
 // loop's back edge (a wavefront then reads the last task's number and does that again).
 __device__ __forceinline__ void sync() {
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   __syncthreads();
+}
+
+// Buffer accesses: a uniform base and size in scalar registers, one 32-bit byte offset per
+// lane, and no test of bounds in the code: a load past the size gives zero, a store past
+// it does nothing. Tasks are short and bound by their instructions, so this counts.
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+constexpr int kNowhere = 0x40000000;   // an offset past every size, also added to another
+constexpr int kSc1 = 16;               // write through the caches
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(const double* p, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(p), 0, bytes, 0x00027000);
+}
+__device__ __forceinline__ double load1(__amdgpu_buffer_rsrc_t b, int at) {
+  const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(b, at, 0, 0);
+  return *reinterpret_cast<const double*>(&v);
+}
+__device__ __forceinline__ double2 load2(__amdgpu_buffer_rsrc_t b, int at) {
+  const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(b, at, 0, 0);
+  return *reinterpret_cast<const double2*>(&v);
+}
+__device__ __forceinline__ void put1(__amdgpu_buffer_rsrc_t b, int at, double v) {
+  __builtin_amdgcn_raw_buffer_store_b64(*reinterpret_cast<const u32x2*>(&v), b, at, 0, kSc1);
+}
+__device__ __forceinline__ void put2(__amdgpu_buffer_rsrc_t b, int at, double2 v) {
+  __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4*>(&v), b, at, 0, kSc1);
+}
+
+// Rows of an LDS block (stride kLd, np columns) to memory, 16 threads a row.
+__device__ __forceinline__ void put_rows(double* p, const double* l, int rows, int np, int tid) {
+  const __amdgpu_buffer_rsrc_t b = buffer(p, rows * np * 8);
+#pragma unroll
+  for (int i = 0; i < 3 * kDsMaxPiv; i += kThreads / 16) {
+    if (i >= rows) break;
+    const int r = i + (tid >> 4), c = 2 * (tid & 15);
+#pragma unroll
+    for (int k = 0; k < 3 * kDsMaxPiv; k += 32)
+      if (k + c < np)
+        put2(b, (r * np + k + c) * 8, *reinterpret_cast<const double2*>(l + r * kLd + k + c));
+  }
+}
+
+__device__ __forceinline__ double2 get2(const double* p) {
+  return *reinterpret_cast<const double2*>(p);
 }
 
 // Tables that no task writes, read at uniform addresses through the scalar cache.
@@ -192,8 +223,18 @@ __device__ __forceinline__ Table<T> table(const T* p) {
 }
 
 struct Shared {
-  int next, go, bad;
-  int map[2][3 * kDsMaxPiv];   // local unknowns of the first children's pivot rows
+  int go, bad;
+  int next[2];     // the number of the task whose record is in rec
+  DsTask rec[2];   // this task's and the next one's record, in turn
+};
+
+// What wavefront 0 holds of the next task while this one runs.
+struct Next {
+  const DsTask* tasks;
+  int ntasks;
+  int slot;        // of Shared::rec for the next task
+  int number;
+  unsigned long long rec;   // 8 bytes of its record per lane
 };
 
 // The thread's number, opaque to the optimiser: what each task derives from it would
@@ -204,16 +245,27 @@ __device__ __forceinline__ int thread_id() {
   return t;
 }
 
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ long long uni(long long v) {
+  const int lo = uni((int)v), hi = uni((int)(v >> 32));
+  return (long long)hi << 32 | (unsigned)lo;
+}
+
 // Waits (bounded) until every lane's counter of wavefront 0 reaches the lane's target (0:
-// nothing to wait for). Every thread calls; false when the launch is to end. Also a
-// barrier of the workgroup.
-__device__ __forceinline__ bool wait_lanes(Table<DsArgs> a, int c, int target, Shared& sh) {
+// nothing to wait for). Every thread calls. 0 when the launch is to end, else 1, or 3 when
+// the counters have also reached `want`. Also a barrier of the workgroup.
+__device__ __forceinline__ int wait_lanes(Table<DsArgs> a, int c, int target, int want,
+                                          Shared& sh) {
   if (threadIdx.x < 64) {
     int go = 1;
     for (int spins = 0;;) {
-      const bool ok = target <= 0 || __hip_atomic_load(a->count + c, __ATOMIC_RELAXED,
-                                                       __HIP_MEMORY_SCOPE_AGENT) >= target;
-      if (__all(ok)) break;
+      int v = 0;
+      if (target > 0 || want > 0)
+        v = __hip_atomic_load(a->count + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (__all(v >= target)) {
+        if (__all(v >= want)) go = 3;
+        break;
+      }
       __builtin_amdgcn_s_sleep(1);
       if ((++spins & 255) == 0) {
         if (spins > kSpinLimit)
@@ -227,49 +279,52 @@ __device__ __forceinline__ bool wait_lanes(Table<DsArgs> a, int c, int target, S
     if (threadIdx.x == 0) sh.go = go;
   }
   sync();
-  return __builtin_amdgcn_readfirstlane(sh.go) != 0;
+  return uni(sh.go);
 }
 
 __device__ __forceinline__ bool wait_one(Table<DsArgs> a, int c, int target, Shared& sh) {
-  return wait_lanes(a, c, threadIdx.x == 0 ? target : 0, sh);
+  return wait_lanes(a, c, threadIdx.x == 0 ? target : 0, 0, sh) != 0;
 }
 
-// Waits for the children's counters `which`, k0 and k1 their targets of the first two.
-__device__ __forceinline__ bool wait_children(Table<DsArgs> a, Table<DsFront> F, int which, int k0,
-                                              int k1, Shared& sh) {
+// Waits for the children's counters `which` (and looks whether the counters c2 of lanes 2
+// and up have reached their `want`): as wait_lanes.
+__device__ __forceinline__ int wait_children(Table<DsArgs> a, const DsTask& tk, int which, int c2,
+                                             int want, Shared& sh) {
   const int lane = thread_id();
-  int c = F->kcnt[0] + which, target = 0;
-  if (lane == 0) target = k0;
-  if (lane == 1) {
-    c = F->kcnt[1] + which;
-    target = k1;
+  int c = c2, target = 0;
+  if (lane < 2) {
+    c = tk.f.kcnt[lane] + which;
+    target = which == kDsHeadDone ? tk.f.khead[lane] : which == kDsSchurDone ? tk.f.kschur[lane]
+                                                                             : tk.f.kfwd[lane];
   }
-  if (!wait_lanes(a, c, target, sh)) return false;
-  for (int base = 2; base < F->nc; base += 64) {   // rare: more than two children
+  const int nc = uni(tk.f.nc);
+  int go = wait_lanes(a, c, target, lane < 2 ? target : want, sh);
+  for (int base = 2; go && base < nc; base += 64) {   // rare: more than two children
     target = 0;
-    if (lane < 64 && base + lane < F->nc) {
-      const DsChild& K = a->kid[F->c0 + base + lane];
+    if (lane < 64 && base + lane < nc) {
+      const DsChild& K = a->kid[tk.f.c0 + base + lane];
       c = K.cnt + which;
       target = which == kDsHeadDone ? K.nhead : which == kDsSchurDone ? K.nschur : K.nfwd;
     }
-    if (!wait_lanes(a, c, target, sh)) return false;
+    go = wait_lanes(a, c, target, 0, sh) ? 1 : 0;
   }
-  return true;
+  return go;
 }
 
-// Waits for the border rows of the tile groups [g0, g1).
-__device__ __forceinline__ bool wait_rows(Table<DsArgs> a, Table<DsFront> F, int g0, int g1,
-                                          Shared& sh) {
-  constexpr int per = kDsSchurTile / kDsRowTile;
-  const int g = g0 + thread_id();
-  const int all = (F->nb + kDsRowTile - 1) / kDsRowTile;
-  return wait_lanes(a, F->cnt + kDsRowsDone + g,
-                    threadIdx.x < 64 && g < g1 ? min(per, all - per * g) : 0, sh);
+// Starts the load of the next task's record; after the task's first wait, when the task's
+// number has come back from the queue.
+__device__ __forceinline__ void fetch_next(Next& nx) {
+  if (threadIdx.x >= 64) return;
+  nx.number = uni(nx.number);
+  if (nx.number < nx.ntasks)
+    nx.rec = reinterpret_cast<const unsigned long long*>(nx.tasks + nx.number)[threadIdx.x];
 }
 
 // Counts a task as done once every wavefront's stores have completed (put() writes
-// through, so completion is visibility).
-__device__ __forceinline__ void signal(Table<DsArgs> a, int c, int c2 = -1) {
+// through, so completion is visibility), and hands over to the next task.
+__device__ __forceinline__ void signal(Table<DsArgs> a, int c, int c2, const Next& nx, Shared& sh) {
+  if (threadIdx.x < 64) reinterpret_cast<unsigned long long*>(&sh.rec[nx.slot])[threadIdx.x] = nx.rec;
+  if (threadIdx.x == 0) sh.next[nx.slot] = nx.number;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   sync();
   if (threadIdx.x == 0) {
@@ -278,10 +333,10 @@ __device__ __forceinline__ void signal(Table<DsArgs> a, int c, int c2 = -1) {
   }
 }
 
-// The local unknowns of a child's pivot rows, one per thread, into sh.map[slot].
-__device__ __forceinline__ void stage_map(Table<DsArgs> a, Table<DsChild> K, int slot, Shared& sh) {
-  const int c = thread_id();
-  if (c < 3 * K->q) sh.map[slot][c] = 3 * a->tab[K->map + c / 3] + c % 3;
+// Local unknown of unknown u of child ch's border (u < 3 q).
+__device__ __forceinline__ int local_of(Table<DsArgs> a, const DsTask& tk, int ch, int u) {
+  const int v = ch < 2 ? tk.col[ch][u / 3] : a->tab[a->kid[tk.f.c0 + ch].map + u / 3];
+  return 3 * v + u % 3;
 }
 
 // X = F_pp^-1. The lower triangle of F_pp is gathered into LDS (A's entries, then the
@@ -296,17 +351,19 @@ __device__ __forceinline__ void stage_map(Table<DsArgs> a, Table<DsChild> K, int
 // where updating the diagonal tiles on wavefront 0 as well took 19.0 us.
 // A front whose sweep meets a non-positive pivot stores NaN: its solution fails the
 // residual test.
-__device__ __forceinline__ bool task_pivot(Table<DsArgs> a, Table<DsFront> F, double* fac,
+__device__ __forceinline__ bool task_pivot(Table<DsArgs> a, const DsTask& tk, Next& nx, double* fac,
                                            double* lds, Shared& sh) {
-  const int tid = thread_id(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int np = F->np, T = np / kDsTile, n3 = 3 * F->p;
+  const int tid = thread_id(), lane = tid & 63, wave = uni(tid >> 6);
+  const int np = uni(tk.f.np), T = np / kDsTile, n3 = 3 * uni(tk.f.p), nc = uni(tk.f.nc);
+  const int cnt = uni(tk.f.cnt);
   if (tid == 0) sh.bad = 0;
   for (int e = tid; e < np * kLd; e += kThreads) lds[e] = 0.0;
-  for (int ch = 0; ch < min(F->nc, 2); ++ch) stage_map(a, table(a->kid + F->c0 + ch), ch, sh);
   sync();
   if (tid < np && tid >= n3) lds[tid * kLd + tid] = 1.0;
-  for (int e = tid; e < F->nalist; e += kThreads) {
-    const int2 en = reinterpret_cast<const int2*>(a->tab + F->alist)[e];
+  const int nalist = uni(tk.f.nalist);
+  const int2* alist = reinterpret_cast<const int2*>(a->tab + uni(tk.f.alist));
+  for (int e = tid; e < nalist; e += kThreads) {
+    const int2 en = alist[e];
     const int l = en.y >> 16, i = en.y & 0xffff;
     double x[9];
 #pragma unroll
@@ -319,38 +376,51 @@ __device__ __forceinline__ bool task_pivot(Table<DsArgs> a, Table<DsFront> F, do
         lds[(3 * l + c) * kLd + 3 * i + r] = x[3 * r + c];
       }
   }
-  if (!wait_children(a, F, kDsHeadDone, F->khead[0], F->khead[1], sh)) return false;
-  for (int ch = 0; ch < F->nc; ++ch) {
-    const Table<DsChild> K = table(a->kid + F->c0 + ch);
-    const double* S = a->ws + K->so;
-    const int nq = 3 * K->q;
-    if (ch > 0) sync();
-    if (ch > 1) {
-      stage_map(a, K, ch & 1, sh);
-      sync();
-    }
-    // a lane takes columns lane and lane + 64 of every eighth row (nq <= 96); all loads
-    // are in flight before the first is used
-    const int* map = sh.map[ch & 1];
-    constexpr int NR = 3 * kDsMaxPiv / kWaves, N1 = NR - 64 / kWaves;
-    double s0[NR], s1[N1];
+  if (!wait_children(a, tk, kDsHeadDone, 0, 0, sh)) return false;
+  fetch_next(nx);
+  // A lane takes columns lane and lane + 64 of every eighth row (at most 96); the loads of
+  // the first two children are all in flight before the first is used.
+  constexpr int NR = 3 * kDsMaxPiv / kWaves, N0 = 64 / kWaves, N1 = NR - N0;
+  auto gather = [&](const double* S, int nq, int nb, double (&s0)[NR], double (&s1)[N1]) {
 #pragma unroll
     for (int q = 0; q < NR; ++q) {
       const int r = wave + kWaves * q;
-      s0[q] = r < nq && lane <= r ? *(S + (size_t)r * K->nb + lane) : 0.0;
-      if (q >= NR - N1)
-        s1[q - (NR - N1)] = r < nq && lane + 64 <= r ? *(S + (size_t)r * K->nb + lane + 64) : 0.0;
+      s0[q] = r < nq && lane <= r ? S[(size_t)r * nb + lane] : 0.0;
+      if (q >= N0) s1[q - N0] = r < nq && lane + 64 <= r ? S[(size_t)r * nb + lane + 64] : 0.0;
     }
+  };
+  auto add = [&](int ch, int nq, const double (&s0)[NR], const double (&s1)[N1]) {
+    const int m0 = lane < nq ? local_of(a, tk, ch, lane) : 0;
+    const int m1 = lane + 64 < nq ? local_of(a, tk, ch, lane + 64) : 0;
 #pragma unroll
     for (int q = 0; q < NR; ++q) {
       const int r = wave + kWaves * q;
       if (r >= nq) continue;
-      const int pr = map[r];
-      if (lane <= r) {
-        lds[pr * kLd + map[lane]] += s0[q];
-      }
-      if (q >= NR - N1 && lane + 64 <= r) lds[pr * kLd + map[lane + 64]] += s1[q - (NR - N1)];
+      double* row = lds + __builtin_amdgcn_readlane(q < N0 ? m0 : m1, r & 63) * kLd;
+      if (lane <= r) row[m0] += s0[q];
+      if (q >= N0 && lane + 64 <= r) row[m1] += s1[q - N0];
     }
+  };
+  {
+    double s0[2][NR], s1[2][N1];
+    int nq[2];
+#pragma unroll
+    for (int ch = 0; ch < 2; ++ch) {
+      nq[ch] = ch < nc ? 3 * uni(tk.kid[ch].q) : 0;
+      gather(a->ws + (ch < nc ? uni(tk.kid[ch].so) : 0), nq[ch], uni(tk.kid[ch].nb), s0[ch], s1[ch]);
+    }
+    add(0, nq[0], s0[0], s1[0]);
+    if (nc > 1) {
+      sync();
+      add(1, nq[1], s0[1], s1[1]);
+    }
+  }
+  for (int ch = 2; ch < nc; ++ch) {   // rare
+    const DsChild& K = a->kid[uni(tk.f.c0) + ch];
+    double s0[NR], s1[N1];
+    gather(a->ws + K.so, 3 * K.q, K.nb, s0, s1);
+    sync();
+    add(ch, 3 * K.q, s0, s1);
   }
   sync();
   const int g = lane >> 4, c16 = lane & 15;
@@ -475,12 +545,8 @@ __device__ __forceinline__ bool task_pivot(Table<DsArgs> a, Table<DsFront> F, do
     }
   }
   sync();
-  double* X = fac + F->xo;
-  for (int e = tid; e < np * np / 2; e += kThreads) {
-    const int r = 2 * e / np, c = 2 * e - r * np;
-    put2(X, 2 * e, *reinterpret_cast<const double2*>(lds + r * kLd + c));
-  }
-  signal(a, F->cnt + kDsPivotDone);
+  put_rows(fac + uni(tk.f.xo), lds, np, np, tid);
+  signal(a, cnt + kDsPivotDone, -1, nx, sh);
   return true;
 }
 
@@ -518,79 +584,85 @@ __device__ __forceinline__ void border_product(const double* __restrict__ X, con
 }
 
 // F_bp and W = F_bp X of 32 border rows; F_bp is gathered into LDS like the pivot block.
-__device__ __forceinline__ bool task_border(Table<DsArgs> a, Table<DsFront> F, int tile,
+__device__ __forceinline__ bool task_border(Table<DsArgs> a, const DsTask& tk, Next& nx,
                                             double* fac, double* lds, Shared& sh) {
   constexpr int NR = kDsRowTile / kWaves;
   double* Fl = lds;
-  const int tid = thread_id(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int np = F->np, r0 = tile * kDsRowTile, rows = min(kDsRowTile, F->nb - r0);
-  const int l0 = *table(a->tab + F->blist + tile), l1 = *table(a->tab + F->blist + tile + 1);
+  const int tid = thread_id(), lane = tid & 63, wave = uni(tid >> 6);
+  const int tile = uni(tk.a), np = uni(tk.f.np), nc = uni(tk.f.nc), p = uni(tk.f.p);
+  const int cnt = uni(tk.f.cnt), r0 = tile * kDsRowTile, rows = min(kDsRowTile, uni(tk.f.nb) - r0);
+  const int lo = uni(tk.lo), hi = uni(tk.hi);
   for (int e = tid; e < kDsRowTile * kLd; e += kThreads) Fl[e] = 0.0;
-  // child ch's border rows of this wavefront's rows
-  auto rows_of = [&](int ch, int (&u)[NR]) {
-#pragma unroll
-    for (int q = 0; q < NR; ++q) {
-      const int br = r0 + wave + kWaves * q;
-      const int v = ch < F->nc && br < 3 * F->b
-                        ? a->tab[table(a->kid + F->c0 + ch)->inv + F->p + br / 3] : -1;
-      u[q] = v < 0 ? -1 : 3 * v + br % 3;
-    }
-  };
-  int u0[NR], u1[NR];
-  rows_of(0, u0);
-  rows_of(1, u1);
-  for (int ch = 0; ch < min(F->nc, 2); ++ch) stage_map(a, table(a->kid + F->c0 + ch), ch, sh);
   sync();
-  for (int e = (l0 >> 1) + tid; e < (l1 >> 1); e += kThreads) {
+  for (int e = lo + tid; e < hi; e += kThreads) {
     const int2 en = reinterpret_cast<const int2*>(a->tab)[e];
-    const int l = (en.y >> 16) - F->p, i = en.y & 0xffff;
+    const int l = (en.y >> 16) - p, i = en.y & 0xffff;
+    double x[9];
+#pragma unroll
+    for (int q = 0; q < 9; ++q) x[q] = a->A[en.x + (size_t)q * a->nv];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
       const int row = 3 * l + c - r0;
       if (row < 0 || row >= kDsRowTile) continue;
 #pragma unroll
-      for (int r = 0; r < 3; ++r)
-        Fl[row * kLd + 3 * i + r] = a->A[en.x + (size_t)(r * 3 + c) * a->nv];
+      for (int r = 0; r < 3; ++r) Fl[row * kLd + 3 * i + r] = x[3 * r + c];
     }
   }
-  if (!wait_children(a, F, kDsSchurDone, F->kschur[0], F->kschur[1], sh)) return false;
-  auto add = [&](int ch, const int (&u)[NR]) {
-    const Table<DsChild> K = table(a->kid + F->c0 + ch);
-    const int nq = 3 * K->q, ld = K->nb;
-    const double* S0 = a->ws + K->so;
-    double s0[NR], s1[NR];
+  const int go = wait_children(a, tk, kDsSchurDone, cnt + kDsPivotDone, lane == 2 ? 1 : 0, sh);
+  if (!go) return false;
+  fetch_next(nx);
+  // a lane takes pivot columns lane and lane + 64 of this wavefront's rows of a child
+  auto gather = [&](int ch, const double* S0, int nq, int ld, double (&s0)[NR], double (&s1)[NR]) {
+    const int c0 = lane < nq ? 8 * lane : kNowhere, c1 = lane + 64 < nq ? 8 * (lane + 64) : kNowhere;
 #pragma unroll
     for (int q = 0; q < NR; ++q) {
-      const double* S = S0 + (size_t)max(u[q], 0) * ld;
-      s0[q] = u[q] >= 0 && lane < nq ? *(S + lane) : 0.0;
-      s1[q] = u[q] >= 0 && lane + 64 < nq ? *(S + lane + 64) : 0.0;
-    }
-#pragma unroll
-    for (int q = 0; q < NR; ++q) {
-      const int r = wave + kWaves * q;
-      if (lane < nq) Fl[r * kLd + sh.map[ch & 1][lane]] += s0[q];
-      if (lane + 64 < nq) Fl[r * kLd + sh.map[ch & 1][lane + 64]] += s1[q];
+      const int br = r0 + wave + kWaves * q;
+      int v = -1;
+      if (ch < 2) v = uni((int)tk.row[ch & 1][br / 3 - r0 / 3]);
+      else if (br < 3 * tk.f.b) v = a->tab[a->kid[tk.f.c0 + ch].inv + p + br / 3];
+      const __amdgpu_buffer_rsrc_t S =
+          buffer(S0 + (size_t)(3 * max(v, 0) + br % 3) * ld, v >= 0 ? 8 * nq : 0);
+      s0[q] = load1(S, c0);
+      s1[q] = load1(S, c1);
     }
   };
-  if (F->nc > 0) add(0, u0);
-  if (F->nc > 1) {
-    sync();
-    add(1, u1);
+  auto add = [&](int ch, int nq, const double (&s0)[NR], const double (&s1)[NR]) {
+    if (lane < nq) {
+      double* x = Fl + wave * kLd + local_of(a, tk, ch, lane);
+#pragma unroll
+      for (int q = 0; q < NR; ++q) x[kWaves * q * kLd] += s0[q];
+    }
+    if (lane + 64 < nq) {
+      double* x = Fl + wave * kLd + local_of(a, tk, ch, lane + 64);
+#pragma unroll
+      for (int q = 0; q < NR; ++q) x[kWaves * q * kLd] += s1[q];
+    }
+  };
+  {
+    // both children's loads are in flight before the first is used; a row is this
+    // wavefront's alone, so the sums need no barrier
+    double s0[2][NR], s1[2][NR];
+    int nq[2];
+#pragma unroll
+    for (int ch = 0; ch < 2; ++ch) {
+      nq[ch] = ch < nc ? 3 * uni(tk.kid[ch].q) : 0;
+      gather(ch, a->ws + (ch < nc ? uni(tk.kid[ch].so) : 0), nq[ch], uni(tk.kid[ch].nb), s0[ch],
+             s1[ch]);
+    }
+    add(0, nq[0], s0[0], s1[0]);
+    add(1, nq[1], s0[1], s1[1]);
   }
-  for (int ch = 2; ch < F->nc; ++ch) {   // rare
-    sync();
-    stage_map(a, table(a->kid + F->c0 + ch), ch & 1, sh);
-    rows_of(ch, u0);
-    sync();
-    add(ch, u0);
+  for (int ch = 2; ch < nc; ++ch) {   // rare
+    const DsChild& K = a->kid[tk.f.c0 + ch];
+    double s0[NR], s1[NR];
+    gather(ch, a->ws + K.so, 3 * K.q, K.nb, s0, s1);
+    add(ch, 3 * K.q, s0, s1);
   }
   sync();
-  double* Bg = a->ws + F->bo + (size_t)r0 * np;
-  for (int r = wave; r < rows; r += kWaves)
-    for (int c = lane; c < np; c += 64) put(Bg + (size_t)r * np + c, Fl[r * kLd + c]);
-  if (!wait_one(a, F->cnt + kDsPivotDone, 1, sh)) return false;
-  const double* X = fac + F->xo;
-  double* W = fac + F->wo + (size_t)r0 * np;
+  put_rows(a->ws + uni(tk.f.bo) + (size_t)r0 * np, Fl, rows, np, tid);
+  if (go == 1 && !wait_one(a, cnt + kDsPivotDone, 1, sh)) return false;
+  const double* X = fac + uni(tk.f.xo);
+  double* W = fac + uni(tk.f.wo) + (size_t)r0 * np;
   switch (np / kDsTile) {
     case 1: border_product<1>(X, Fl, W, rows, wave, lane); break;
     case 2: border_product<2>(X, Fl, W, rows, wave, lane); break;
@@ -599,7 +671,7 @@ __device__ __forceinline__ bool task_border(Table<DsArgs> a, Table<DsFront> F, i
     case 5: border_product<5>(X, Fl, W, rows, wave, lane); break;
     default: border_product<6>(X, Fl, W, rows, wave, lane); break;
   }
-  signal(a, F->cnt + kDsRowsDone + tile / (kDsSchurTile / kDsRowTile));
+  signal(a, cnt + kDsRowsDone + tile / (kDsSchurTile / kDsRowTile), -1, nx, sh);
   return true;
 }
 
@@ -627,260 +699,267 @@ __device__ __forceinline__ void schur_product(const double* w0, const double* b0
 }
 
 // S = (children) - W F_bp^T, one lower 64x64 tile: each wavefront forms a 32x16 block. The
-// children's parts are gathered while the border rows are still being formed; the
-// operands pass through LDS in halves of the inner dimension.
-__device__ __forceinline__ bool task_schur(Table<DsArgs> a, Table<DsFront> F, int ij, double* fac,
+// children's parts travel while the border rows are waited for; the operands pass through
+// LDS in halves of the inner dimension.
+__device__ __forceinline__ bool task_schur(Table<DsArgs> a, const DsTask& tk, Next& nx, double* fac,
                                            double* lds, Shared& sh) {
   double* Wl = lds;
   double* Bl = lds + kDsSchurTile * kLdK;
-  const int tid = thread_id(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid = thread_id(), lane = tid & 63, wave = uni(tid >> 6);
   const int g = lane >> 4, c16 = lane & 15;
-  const int np = F->np, nb = F->nb;
+  const int np = uni(tk.f.np), nb = uni(tk.f.nb), nc = uni(tk.f.nc), cnt = uni(tk.f.cnt);
+  const int ij = uni(tk.a);
   const int I = ij >> 16, J = ij & 0xffff, I0 = I * kDsSchurTile, J0 = J * kDsSchurTile;
   const int i0 = I0 + 32 * (wave >> 2), col = J0 + 16 * (wave & 3) + c16;
-  dbl4 acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
-  int u[2][8], w[2];   // the first children's rows and column of this lane's entries
+  // byte offsets of the tile's rows and columns in the first children's updates
+  unsigned* places = reinterpret_cast<unsigned*>(lds + 2 * kDsSchurTile * kLdK);   // [child][row, col][64]
+  if (tid < 4 * kDsSchurTile) {
+    const int ch = tid >> 7, u = tid & 63, base = tid & 64 ? J0 : I0, x = (base + u) / 3;
+    const int k = x - base / 3, ld = tk.kid[ch].nb;
+    const int v = ch < nc ? (tid & 64 ? tk.col[ch][k] : tk.row[ch][k]) : -1;
+    const int e = 8 * (3 * v + base + u - 3 * x);
+    places[tid] = v < 0 ? kNowhere : tid & 64 ? e : e * ld;
+  }
+  constexpr int per = kDsSchurTile / kDsRowTile;
+  const int group = lane == 2 ? I : J, rows_cnt = cnt + kDsRowsDone + group;
+  const int rows_of = lane == 2 || lane == 3
+                          ? min(per, (nb + kDsRowTile - 1) / kDsRowTile - per * group) : 0;
+  const int go = wait_children(a, tk, kDsSchurDone, rows_cnt, rows_of, sh);
+  if (!go) return false;
+  fetch_next(nx);
+  double x[2][8];
 #pragma unroll
   for (int ch = 0; ch < 2; ++ch) {
-    const bool have = ch < F->nc;
-    const int* inv = a->tab + (have ? table(a->kid + F->c0 + ch)->inv : 0) + F->p;
-    const int v = have && col < 3 * F->b ? inv[col / 3] : -1;
-    w[ch] = v < 0 ? -1 : 3 * v + col % 3;
+    const int ld = ch < nc ? uni(tk.kid[ch].nb) : 0;
+    const __amdgpu_buffer_rsrc_t S = buffer(a->ws + (ch < nc ? uni(tk.kid[ch].so) : 0), 8 * ld * ld);
+    const unsigned* rows = places + 128 * ch + 32 * (wave >> 2) + g;
+    const unsigned c = places[128 * ch + 64 + 16 * (wave & 3) + c16];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int row = i0 + 4 * q + g;
-      const int x = have && row < 3 * F->b && col <= row ? inv[row / 3] : -1;
-      u[ch][q] = x < 0 ? -1 : 3 * x + row % 3;
-    }
+    for (int q = 0; q < 8; ++q) x[ch][q] = load1(S, (int)(rows[4 * q] + c));
   }
-  if (!wait_children(a, F, kDsSchurDone, F->kschur[0], F->kschur[1], sh)) return false;
-#pragma unroll
-  for (int ch = 0; ch < 2; ++ch) {
-    if (ch >= F->nc) continue;
-    const Table<DsChild> K = table(a->kid + F->c0 + ch);
-    const double* S = a->ws + K->so + max(w[ch], 0);
-    double x[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q)
-      x[q] = u[ch][q] >= 0 && w[ch] >= 0 ? *(S + (size_t)u[ch][q] * K->nb) : 0.0;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) acc[q >> 2][q & 3] -= x[q];
-  }
-  for (int ch = 2; ch < F->nc; ++ch) {   // rare
-    const Table<DsChild> K = table(a->kid + F->c0 + ch);
-    const int* inv = a->tab + K->inv + F->p;
-    const int v = col < 3 * F->b ? inv[col / 3] : -1;
-    if (v < 0) continue;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int row = i0 + 4 * q + g;
-      const int x = row < 3 * F->b && col <= row ? inv[row / 3] : -1;
-      if (x >= 0)
-        acc[q >> 2][q & 3] -= a->ws[K->so + (size_t)(3 * x + row % 3) * K->nb + 3 * v + col % 3];
-    }
-  }
-  if (!wait_lanes(a, F->cnt + kDsRowsDone + (lane == 0 ? I : J),
-                  lane < 2 ? min(kDsSchurTile / kDsRowTile,
-                                 (nb + kDsRowTile - 1) / kDsRowTile -
-                                     kDsSchurTile / kDsRowTile * (lane == 0 ? I : J))
-                           : 0,
-                  sh))
-    return false;
-  const double* W = fac + F->wo;
-  const double* B = a->ws + F->bo;
-  // Halves of at most 48 columns: a half is 64 rows of up to 24 double2 per operand, three
-  // per thread (row e / per, pair e % per); the second half travels during the first's
-  // products.
+  if (go == 1 && !wait_lanes(a, rows_cnt, rows_of, 0, sh)) return false;
+  // Halves of at most 48 columns, 16, 32 or 48: eight threads a row, up to three 16-byte
+  // pieces each; the second half travels during the first's products.
+  const __amdgpu_buffer_rsrc_t W = buffer(fac + uni(tk.f.wo), 8 * nb * np);
+  const __amdgpu_buffer_rsrc_t B = buffer(a->ws + uni(tk.f.bo), 8 * nb * np);
   const int k1 = min(np, 48), k2 = np - k1;
-  double2 wv0, wv1, wv2, bv0, bv1, bv2;
-#define PHISFT_DS_LOAD(q, k0, per)                                                             \
-  {                                                                                            \
-    const int e = min(tid + kThreads * q, kDsSchurTile * (per)-1);                             \
-    const int r = e / (per), c = 2 * (e - r * (per));                                          \
-    wv##q = get2(W + (size_t)min(I0 + r, nb - 1) * np + (k0) + c); \
-    bv##q = get2(B + (size_t)min(J0 + r, nb - 1) * np + (k0) + c); \
-  }
-#define PHISFT_DS_STAGE(q, per)                                       \
-  {                                                                   \
-    const int e = min(tid + kThreads * q, kDsSchurTile * (per)-1);    \
-    const int r = e / (per), c = 2 * (e - r * (per));                 \
-    *reinterpret_cast<double2*>(Wl + r * kLdK + c) = wv##q;           \
-    *reinterpret_cast<double2*>(Bl + r * kLdK + c) = bv##q;           \
-  }
-  PHISFT_DS_LOAD(0, 0, k1 / 2)
-  PHISFT_DS_LOAD(1, 0, k1 / 2)
-  PHISFT_DS_LOAD(2, 0, k1 / 2)
-  PHISFT_DS_STAGE(0, k1 / 2)
-  PHISFT_DS_STAGE(1, k1 / 2)
-  PHISFT_DS_STAGE(2, k1 / 2)
-  if (k2 > 0) {
-    PHISFT_DS_LOAD(0, k1, k2 / 2)
-    PHISFT_DS_LOAD(1, k1, k2 / 2)
-    PHISFT_DS_LOAD(2, k1, k2 / 2)
-  }
+  const int sr = tid >> 3, sc = 2 * (tid & 7);
+  const int wat = 8 * ((I0 + sr) * np + sc), bat = 8 * ((J0 + sr) * np + sc);
+  double2 wv[3], bv[3];
+  auto fetch = [&](int k0, int k) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      if (16 * q < k) {
+        wv[q] = load2(W, wat + 8 * k0 + 128 * q);
+        bv[q] = load2(B, bat + 8 * k0 + 128 * q);
+      }
+  };
+  auto stage = [&](int k) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      if (16 * q < k) {
+        *reinterpret_cast<double2*>(Wl + sr * kLdK + sc + 16 * q) = wv[q];
+        *reinterpret_cast<double2*>(Bl + sr * kLdK + sc + 16 * q) = bv[q];
+      }
+  };
+  fetch(0, k1);
+  dbl4 acc[2];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) acc[q >> 2][q & 3] = -(x[0][q] + x[1][q]);
+  stage(k1);
+  if (k2 > 0) fetch(48, k2);
   sync();
   const double* w0 = Wl + (32 * (wave >> 2) + c16) * kLdK;
   const double* b0 = Bl + (16 * (wave & 3) + c16) * kLdK;
   schur_product(w0, b0, k1, g, acc);
   if (k2 > 0) {
     sync();
-    PHISFT_DS_STAGE(0, k2 / 2)
-    PHISFT_DS_STAGE(1, k2 / 2)
-    PHISFT_DS_STAGE(2, k2 / 2)
+    stage(k2);
     sync();
     schur_product(w0, b0, k2, g, acc);
   }
-#undef PHISFT_DS_LOAD
-#undef PHISFT_DS_STAGE
-  if (col < nb) {
-    double* S = a->ws + F->so;
+  for (int ch = 2; ch < nc; ++ch) {   // rare
+    const DsChild& K = a->kid[tk.f.c0 + ch];
+    const int b3 = 3 * uni(tk.f.b);
+    const int* inv = a->tab + K.inv + tk.f.p;
+    const int v = col < b3 ? inv[col / 3] : -1;
+    if (v < 0) continue;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int row = i0 + 16 * i + 4 * q + g;
-        if (row < nb) put(S + (size_t)row * nb + col, -acc[i][q]);
-      }
+    for (int q = 0; q < 8; ++q) {
+      const int row = i0 + 4 * q + g;
+      const int w = row < b3 && col <= row ? inv[row / 3] : -1;
+      if (w >= 0)
+        acc[q >> 2][q & 3] -= a->ws[K.so + (size_t)(3 * w + row % 3) * K.nb + 3 * v + col % 3];
+    }
   }
-  signal(a, F->cnt + kDsSchurDone, I < 2 ? F->cnt + kDsHeadDone : -1);
+  const __amdgpu_buffer_rsrc_t S = buffer(a->ws + uni(tk.f.so), 8 * nb * nb);
+  const int sat = col < nb ? 8 * ((i0 + g) * nb + col) : kNowhere;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) put1(S, sat + 32 * nb * q, -acc[q >> 2][q & 3]);
+  signal(a, cnt + kDsSchurDone, I < 2 ? cnt + kDsHeadDone : -1, nx, sh);
   return true;
 }
 
 // t = b_p + (children), g = (children) - W t of 64 border rows, 16 lanes a row. Every
 // workgroup of a front gathers t itself; W travels while the children are waited for.
-__device__ __forceinline__ bool task_forward(Table<DsArgs> a, Table<DsFront> F, int chunk,
-                                             bool factor, double* fac, double* lds, Shared& sh) {
+__device__ __forceinline__ bool task_forward(Table<DsArgs> a, const DsTask& tk, Next& nx, bool factor,
+                                             double* fac, double* lds, Shared& sh) {
   constexpr int NP = kDsFwdRows * 16 / kThreads;   // rows of a thread
   static_assert(kDsFwdRows == kDsSchurTile, "a chunk is a group of row tiles");
   double* t = lds;
-  const int tid = thread_id(), np = F->np, l16 = tid & 15, nl = F->p + F->b;
+  const int tid = thread_id(), lane = tid & 63, l16 = tid & 15;
+  const int chunk = uni(tk.a), np = uni(tk.f.np), nb = uni(tk.f.nb), nc = uni(tk.f.nc);
+  const int cnt = uni(tk.f.cnt), p = uni(tk.f.p), n3 = 3 * uni(tk.f.b), r0 = chunk * kDsFwdRows;
   // W belongs to this launch only when it factorises too
-  if (factor && F->nb > 0 && !wait_rows(a, F, chunk, chunk + 1, sh)) return false;
+  int go = 1;
+  if (factor) {
+    constexpr int per = kDsSchurTile / kDsRowTile;
+    const int all = (nb + kDsRowTile - 1) / kDsRowTile;
+    int c = cnt + kDsRowsDone + chunk, target = lane == 0 && nb > 0 ? min(per, all - per * chunk) : 0;
+    int want = target;
+    if (lane == 1 || lane == 2) {
+      c = tk.f.kcnt[lane - 1] + kDsForwardDone;
+      want = tk.f.kfwd[lane - 1];
+    }
+    go = wait_lanes(a, c, target, want, sh);
+    if (!go) return false;
+    if (nc > 2) go = 1;
+    fetch_next(nx);
+  }
+  const __amdgpu_buffer_rsrc_t W = buffer(fac + uni(tk.f.wo), 8 * nb * np);
   double w[NP][kSide];
-  int gs[NP][2], ts[2];
 #pragma unroll
   for (int q = 0; q < NP; ++q) {
-    const int r = chunk * kDsFwdRows + (kThreads / 16) * q + (tid >> 4);
+    const int at = 8 * ((r0 + (kThreads / 16) * q + (tid >> 4)) * np + l16);
 #pragma unroll
     for (int k = 0; k < kSide; ++k)
-      w[q][k] = r < F->nb && 16 * k < np ? *(fac + F->wo + (size_t)r * np + 16 * k + l16) : 0.0;
-#pragma unroll
-    for (int ch = 0; ch < 2; ++ch)
-      gs[q][ch] = ch < F->nc && l16 == 0 && r < 3 * F->b ? a->tab[F->gsrc + ch * nl + F->p + r / 3] : -1;
+      if (16 * k < np) w[q][k] = load1(W, at + 128 * k);
   }
-#pragma unroll
-  for (int ch = 0; ch < 2; ++ch)
-    ts[ch] = ch < F->nc && tid < 3 * F->p ? a->tab[F->gsrc + ch * nl + tid / 3] : -1;
   double v = 0.0;
-  if (tid < 3 * F->p) v = a->rhs[(size_t)(tid % 3) * a->nv + a->tab[F->verts + tid / 3]];
-  if (!wait_children(a, F, kDsForwardDone, F->kfwd[0], F->kfwd[1], sh)) return false;
+  if (tid < 3 * p) v = a->rhs[(size_t)(tid % 3) * a->nv + a->tab[tk.f.verts + tid / 3]];
+  if (go == 1 && !wait_children(a, tk, kDsForwardDone, 0, 0, sh)) return false;
+  if (!factor) fetch_next(nx);
   double h[NP], e[2];
 #pragma unroll
-  for (int ch = 0; ch < 2; ++ch) e[ch] = ts[ch] >= 0 ? *(a->ws + ts[ch] + tid % 3) : 0.0;
+  for (int ch = 0; ch < 2; ++ch) {
+    const int x = ch < nc && tid < 3 * p ? tk.col[ch][tid / 3] : -1;
+    e[ch] = x >= 0 ? a->ws[tk.kid[ch].g + 3 * x + tid % 3] : 0.0;
+  }
 #pragma unroll
   for (int q = 0; q < NP; ++q) {
-    const int r = chunk * kDsFwdRows + (kThreads / 16) * q + (tid >> 4);
+    const int r = r0 + (kThreads / 16) * q + (tid >> 4);
     double x[2];
 #pragma unroll
-    for (int ch = 0; ch < 2; ++ch) x[ch] = gs[q][ch] >= 0 ? *(a->ws + gs[q][ch] + r % 3) : 0.0;
+    for (int ch = 0; ch < 2; ++ch) {
+      const int s = ch < nc && l16 == 0 && r < n3 ? tk.row[ch][r / 3 - r0 / 3] : -1;
+      x[ch] = s >= 0 ? a->ws[tk.kid[ch].g + 3 * s + r % 3] : 0.0;
+    }
     h[q] = x[0] + x[1];
-    if (l16 == 0 && r < 3 * F->b)
-      for (int ch = 2; ch < F->nc; ++ch) {
-        const int s = a->tab[F->gsrc + ch * nl + F->p + r / 3];
+    if (l16 == 0 && r < n3)
+      for (int ch = 2; ch < nc; ++ch) {
+        const int s = a->tab[tk.f.gsrc + ch * (p + n3 / 3) + p + r / 3];
         if (s >= 0) h[q] += a->ws[s + r % 3];
       }
   }
   if (tid < np) {
     v += e[0] + e[1];
-    if (tid < 3 * F->p)
-      for (int ch = 2; ch < F->nc; ++ch) {
-        const int s = a->tab[F->gsrc + ch * nl + tid / 3];
+    if (tid < 3 * p)
+      for (int ch = 2; ch < nc; ++ch) {
+        const int s = a->tab[tk.f.gsrc + ch * (p + n3 / 3) + tid / 3];
         if (s >= 0) v += a->ws[s + tid % 3];
       }
     t[tid] = v;
-    if (chunk == 0) put(a->ws + F->t + tid, v);
+    if (chunk == 0) put(a->ws + tk.f.t + tid, v);
   }
   sync();
 #pragma unroll
   for (int q = 0; q < NP; ++q) {
-    const int r = chunk * kDsFwdRows + (kThreads / 16) * q + (tid >> 4);
+    const int r = r0 + (kThreads / 16) * q + (tid >> 4);
     double s = 0.0;
 #pragma unroll
     for (int k = 0; k < kSide; ++k)
       if (16 * k < np) s += w[q][k] * t[16 * k + l16];
     s = row_sum(s);
-    if (l16 == 0 && r < 3 * F->b) put(a->ws + F->g + r, h[q] - s);
+    if (l16 == 0 && r < n3) put(a->ws + tk.f.g + r, h[q] - s);
   }
-  signal(a, F->cnt + kDsForwardDone);
+  signal(a, cnt + kDsForwardDone, -1, nx, sh);
   return true;
 }
 
 // x_p = X t - W^T x_b of 32 pivot unknowns, the border rows spread over 16 groups of
 // threads; X, the first rows of W and the places of x_b travel while the parent is
 // waited for.
-__device__ __forceinline__ bool task_backward(Table<DsArgs> a, Table<DsFront> F, int chunk,
-                                              bool factor, double* fac, double* lds, Shared& sh) {
+__device__ __forceinline__ bool task_backward(Table<DsArgs> a, const DsTask& tk, Next& nx, bool factor,
+                                              double* fac, double* lds, Shared& sh) {
   constexpr int G = kThreads / kDsBwdCols, NW = 20, NX = 3 * kDsMaxPiv / G, NB = 2;
   double* xb = lds;
   double* t = xb + kDsMaxBorder;
   double* part = t + 3 * kDsMaxPiv;          // [G][33]
-  const int tid = thread_id(), np = F->np, n3 = 3 * F->b;
+  const int tid = thread_id(), lane = tid & 63;
+  const int np = uni(tk.f.np), n3 = 3 * uni(tk.f.b), cnt = uni(tk.f.cnt);
   const int cl = tid % kDsBwdCols, rg = tid / kDsBwdCols;
-  const int c = chunk * kDsBwdCols + cl;
-  if (factor) {
-    if (!wait_one(a, F->cnt + kDsPivotDone, 1, sh)) return false;
-    if (!wait_rows(a, F, 0, (F->nb + kDsSchurTile - 1) / kDsSchurTile, sh)) return false;
+  const int c = uni(tk.a) * kDsBwdCols + cl;
+  // the parent's solution, or at a root its own right-hand side
+  const int pcnt = uni(tk.f.pcnt), nfwd = uni(tk.f.nfwd);
+  const int last = pcnt < 0 ? cnt + kDsForwardDone : pcnt + kDsBackwardDone;
+  const int nlast = pcnt < 0 ? nfwd : uni(tk.f.pbwd);
+  int go = 1;
+  if (factor) {   // X and W are complete: the forward pass read all rows of W
+    const int cw = lane == 0 ? cnt + kDsPivotDone : lane == 1 ? cnt + kDsForwardDone : last;
+    const int target = lane == 0 ? 1 : lane == 1 ? nfwd : 0;
+    go = wait_lanes(a, cw, target, lane == 2 ? nlast : target, sh);
+    if (!go) return false;
+    fetch_next(nx);
   }
-  const double* X = fac + F->xo + c;
-  const double* W = fac + F->wo + c;
+  const int nb = uni(tk.f.nb);
+  const __amdgpu_buffer_rsrc_t X = buffer(fac + uni(tk.f.xo), 8 * np * np);
+  const __amdgpu_buffer_rsrc_t W = buffer(fac + uni(tk.f.wo), 8 * nb * np);
+  const int at = c < np ? 8 * (rg * np + c) : kNowhere;
+  const int* xsrc = a->tab + uni(tk.f.xsrc);
   double w[NW], x[NX];
   int xs[NB];
 #pragma unroll
   for (int q = 0; q < NB; ++q) {
     const int r = tid + kThreads * q;
-    xs[q] = r < n3 ? a->tab[F->xsrc + r / 3] + r % 3 : -1;
+    xs[q] = r < n3 ? xsrc[r / 3] + r % 3 : -1;
   }
 #pragma unroll
   for (int q = 0; q < NW; ++q) {
-    const int r = rg + G * q;
-    w[q] = c < np && r < n3 ? W[(size_t)r * np] : 0.0;
+    if (G * q < nb) w[q] = load1(W, at + 8 * G * np * q);
   }
 #pragma unroll
   for (int q = 0; q < NX; ++q) {
-    const int k = rg + G * q;
-    x[q] = c < np && k < np ? *(X + (size_t)k * np) : 0.0;
+    if (G * q < np) x[q] = load1(X, at + 8 * G * np * q);
   }
-  if (!wait_one(a, F->pcnt < 0 ? F->cnt + kDsForwardDone : F->pcnt + kDsBackwardDone,
-                F->pcnt < 0 ? F->nfwd : F->pbwd, sh))
-    return false;
+  if (go == 1 && !wait_one(a, last, nlast, sh)) return false;
+  if (!factor) fetch_next(nx);
+  // zero on the padding rows, whose W is zero
 #pragma unroll
   for (int q = 0; q < NB; ++q)
-    if (xs[q] >= 0) xb[tid + kThreads * q] = a->ws[xs[q]];
-  for (int r = tid + kThreads * NB; r < n3; r += kThreads)
-    xb[r] = a->ws[a->tab[F->xsrc + r / 3] + r % 3];
-  if (tid < np) t[tid] = a->ws[F->t + tid];
+    if (tid + kThreads * q < nb) xb[tid + kThreads * q] = xs[q] >= 0 ? a->ws[xs[q]] : 0.0;
+  for (int r = tid + kThreads * NB; r < nb; r += kThreads)
+    xb[r] = r < n3 ? a->ws[xsrc[r / 3] + r % 3] : 0.0;
+  if (tid < np) t[tid] = a->ws[tk.f.t + tid];
   sync();
   double s = 0.0, u = 0.0;
 #pragma unroll
   for (int q = 0; q < NX; ++q)
-    if (rg + G * q < np) s += x[q] * t[rg + G * q];
+    if (G * q < np) s += x[q] * t[rg + G * q];
 #pragma unroll
   for (int q = 0; q < NW; ++q)
-    if (rg + G * q < n3) u += w[q] * xb[rg + G * q];
-  if (c < np) {
+    if (G * q < nb) u += w[q] * xb[rg + G * q];
 #pragma unroll 8
-    for (int r = rg + G * NW; r < n3; r += G) u += W[(size_t)r * np] * xb[r];
-  }
+  for (int r = G * NW; r < nb; r += G) u += load1(W, at + 8 * r * np) * xb[rg + r];
   part[rg * 33 + cl] = s - u;
   sync();
   if (tid < kDsBwdCols && c < np) {
     double v = 0.0;
 #pragma unroll
     for (int q = 0; q < G; ++q) v += part[q * 33 + cl];
-    put(a->ws + F->x + c, v);
-    if (c < 3 * F->p) a->sol[(size_t)(c % 3) * a->nv + a->tab[F->verts + c / 3]] = v;
+    put(a->ws + tk.f.x + c, v);
+    if (c < 3 * tk.f.p) a->sol[(size_t)(c % 3) * a->nv + a->tab[tk.f.verts + c / 3]] = v;
   }
-  signal(a, F->cnt + kDsBackwardDone);
+  signal(a, cnt + kDsBackwardDone, -1, nx, sh);
   return true;
 }
 
@@ -900,30 +979,31 @@ __global__ void __launch_bounds__(kThreads, 4) k_ds_run(const DsArgs* __restrict
   extern __shared__ __align__(16) double lds[];
   __shared__ Shared sh;
   int* queue = args->queue;
+  Next nx{tasks, ntasks, 0, 0, 0};
   if (threadIdx.x == 0)
-    sh.next = __hip_atomic_fetch_add(queue, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    nx.number = __hip_atomic_fetch_add(queue, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  fetch_next(nx);
+  if (threadIdx.x < 64) reinterpret_cast<unsigned long long*>(&sh.rec[0])[threadIdx.x] = nx.rec;
+  if (threadIdx.x == 0) sh.next[0] = nx.number;
+  sync();
 #pragma unroll 1
   for (;;) {
-    sync();
-    const int at = __builtin_amdgcn_readfirstlane(sh.next);
-    if (at >= ntasks) return;
-    sync();
-    int next = 0;   // the next task's number travels while this one runs
-    if (threadIdx.x == 0)
-      next = __hip_atomic_fetch_add(queue, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (uni(sh.next[nx.slot]) >= ntasks) return;
+    const DsTask& tk = sh.rec[nx.slot];
+    nx.slot ^= 1;
+    if (threadIdx.x == 0)   // the next task's number travels while this one runs
+      nx.number = __hip_atomic_fetch_add(queue, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const DsArgs* ap = args;
     asm volatile("" : "+s"(ap));
     const Table<DsArgs> a = table(ap);
-    const Table<DsTask> tk = table(tasks + at);
-    const Table<DsFront> F = table(a->fr + tk->front);
+    const int kind = uni(tk.kind);
     bool go = true;
-    if (tk->kind == kDsPivot) go = task_pivot(a, F, fac, lds, sh);
-    else if (tk->kind == kDsBorder) go = task_border(a, F, tk->a, fac, lds, sh);
-    else if (tk->kind == kDsSchur) go = task_schur(a, F, tk->a, fac, lds, sh);
-    else if (tk->kind == kDsForward) go = task_forward(a, F, tk->a, factor != 0, fac, lds, sh);
-    else go = task_backward(a, F, tk->a, factor != 0, fac, lds, sh);
+    if (kind == kDsPivot) go = task_pivot(a, tk, nx, fac, lds, sh);
+    else if (kind == kDsBorder) go = task_border(a, tk, nx, fac, lds, sh);
+    else if (kind == kDsSchur) go = task_schur(a, tk, nx, fac, lds, sh);
+    else if (kind == kDsForward) go = task_forward(a, tk, nx, factor != 0, fac, lds, sh);
+    else go = task_backward(a, tk, nx, factor != 0, fac, lds, sh);
     if (!go) return;
-    if (threadIdx.x == 0) sh.next = next;
   }
 }
 
@@ -941,16 +1021,16 @@ __global__ void __launch_bounds__(256) k_ds_add(DsArgs a, DsAccept o, const doub
 // sums in order and accepts the solve when |b - A x| <= tol |b|. With o.again only the
 // sheets not accepted before are looked at.
 __global__ void __launch_bounds__(256) k_ds_resid(DsArgs a, DsAccept o,
-                                                  const DsTask* __restrict__ tasks) {
+                                                  const DsRows* __restrict__ tasks) {
   __shared__ double part[4][3][kDsResRows];
   __shared__ int s_last;
-  const DsTask tk = tasks[blockIdx.x];
-  const int inst = tk.front, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const DsRows tk = tasks[blockIdx.x];
+  const int inst = tk.sheet, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // the next solve's counters, queue and abort flag start at zero
   for (int e = blockIdx.x * 256 + tid; e < o.clear_ints; e += gridDim.x * 256) a.count[e] = 0;
   if (o.again && o.done[inst]) return;   // every workgroup of the sheet
   const int end = o.inst_voff[inst] + o.inst_nv[inst];
-  const int i = tk.a + lane, nv = a.nv;
+  const int i = tk.row0 + lane, nv = a.nv;
   double y[3] = {0.0, 0.0, 0.0};
   if (i < end)
     for (int k = wave; k < a.maxnz; k += 4) {
@@ -1038,7 +1118,7 @@ void launch_ds_add(const DsArgs& a, const DsAccept& o, const double* dx, const i
   hipLaunchKernelGGL(k_ds_add, dim3((a.nv + 255) / 256), dim3(256), 0, st, a, o, dx, vert_inst);
 }
 
-void launch_ds_resid(const DsArgs& a, const DsAccept& o, const DsTask* tasks, int ntasks,
+void launch_ds_resid(const DsArgs& a, const DsAccept& o, const DsRows* tasks, int ntasks,
                      hipStream_t st) {
   hipLaunchKernelGGL(k_ds_resid, dim3(ntasks), dim3(256), 0, st, a, o, tasks);
 }

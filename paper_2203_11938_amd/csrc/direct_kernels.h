@@ -49,7 +49,7 @@ void launch_ds_run(const DsArgs* args, double* fac, const DsTask* tasks, int nta
                    int grid, const int* done, int ninst, hipStream_t st);
 void launch_ds_add(const DsArgs& a, const DsAccept& o, const double* dx, const int* vert_inst,
                    hipStream_t st);
-void launch_ds_resid(const DsArgs& a, const DsAccept& o, const DsTask* tasks, int ntasks,
+void launch_ds_resid(const DsArgs& a, const DsAccept& o, const DsRows* tasks, int ntasks,
                      hipStream_t st);
 
 }  // namespace phisft

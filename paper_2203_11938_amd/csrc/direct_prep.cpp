@@ -299,6 +299,7 @@ void build_direct_plan(int nv, int maxnz, const std::vector<int>& ell_col,
       C.nschur = schurs(O);
       C.nfwd = O.nfwd;
       C.nb = O.nb;
+      C.g = O.g;
       C.so = O.so;
       C.q = 0;
       C.inv = (int)P.tab.size();
@@ -325,7 +326,49 @@ void build_direct_plan(int nv, int maxnz, const std::vector<int>& ell_col,
   // below, so they come right after those: the pivot sweeps, the longest links of the
   // chain, then run beside the bulk of the Schur tiles.
   constexpr int HR = 2 * kDsSchurTile / kDsRowTile;   // row tiles of the head
-  auto push = [&](int kind, int q, int a) { P.factor_tasks.push_back({kind, q, a}); };
+  auto record = [&](std::vector<DsTask>& list, int kind, int q, int a) {
+    list.emplace_back();
+    DsTask& t = list.back();
+    const DsFront& F = P.fronts[q];
+    t = DsTask{};
+    t.kind = kind;
+    t.front = q;
+    t.a = a;
+    t.f = F;
+    for (int k = 0; k < std::min(F.nc, 2); ++k) {
+      const DsChild& C = P.kids[F.c0 + k];
+      t.kid[k] = C;
+      if (kind == kDsBackward) continue;
+      const int* inv = P.tab.data() + C.inv;
+      // the vertices of border rows [r0, r0 + n)
+      auto rows_of = [&](short* out, int r0, int n) {
+        const int v0 = r0 / 3, v1 = std::min(F.b, (r0 + n + 2) / 3);
+        for (int v = v0; v < v0 + 24; ++v) out[v - v0] = v < v1 ? (short)inv[F.p + v] : -1;
+      };
+      if (kind == kDsBorder) rows_of(t.row[k], a * kDsRowTile, kDsRowTile);
+      if (kind == kDsForward) rows_of(t.row[k], a * kDsFwdRows, kDsFwdRows);
+      if (kind == kDsSchur) {
+        rows_of(t.row[k], (a >> 16) * kDsSchurTile, kDsSchurTile);
+        rows_of(t.col[k], (a & 0xffff) * kDsSchurTile, kDsSchurTile);
+      }
+      if (kind == kDsForward)
+        for (int l = 0; l < F.p; ++l) t.col[k][l] = (short)inv[l];
+      if (kind == kDsPivot || kind == kDsBorder)
+        for (int u = 0; u < C.q; ++u) t.col[k][u] = (short)P.tab[C.map + u];
+    }
+    if (kind == kDsBorder) {
+      t.lo = P.tab[F.blist + a] / 2;
+      t.hi = P.tab[F.blist + a + 1] / 2;
+    }
+  };
+  size_t nfac = 0, nsol = 0;
+  for (const DsFront& F : P.fronts) {
+    nsol += F.nfwd + tiles(F.np, kDsBwdCols);
+    nfac += 1 + tiles(F.nb, kDsRowTile) + schurs(F);
+  }
+  P.solve_tasks.reserve(nsol);
+  P.factor_tasks.reserve(nsol + nfac);
+  auto push = [&](int kind, int q, int a) { record(P.factor_tasks, kind, q, a); };
   auto pivots = [&](int l) {
     for (int q = P.level0[l]; q < P.level0[l + 1]; ++q) push(kDsPivot, q, 0);
   };
@@ -346,17 +389,17 @@ void build_direct_plan(int nv, int maxnz, const std::vector<int>& ell_col,
     for (int q = q0; q < q1; ++q)
       for (int r = 0; r < P.fronts[q].nfwd; ++r) {
         push(kDsForward, q, r);
-        P.solve_tasks.push_back({kDsForward, q, r});
+        record(P.solve_tasks, kDsForward, q, r);
       }
   }
   for (int q = nf - 1; q >= 0; --q)
     for (int c = 0; c < tiles(P.fronts[q].np, kDsBwdCols); ++c) {
       push(kDsBackward, q, c);
-      P.solve_tasks.push_back({kDsBackward, q, c});
+      record(P.solve_tasks, kDsBackward, q, c);
     }
   P.res0.assign(1, 0);
   for (int b = 0; b < ninst; ++b) {
-    for (int r = 0; r < inst_nv[b]; r += kDsResRows) P.res_tasks.push_back({0, b, inst_voff[b] + r});
+    for (int r = 0; r < inst_nv[b]; r += kDsResRows) P.res_tasks.push_back({b, inst_voff[b] + r});
     P.res0.push_back((int)P.res_tasks.size());
   }
   P.ok = P.tab.size() < (size_t)1 << 31 && P.work_doubles < 1LL << 40 &&

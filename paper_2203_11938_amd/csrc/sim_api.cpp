@@ -71,7 +71,8 @@ struct sim_s {
   bool use_direct = false;
   DsPlan dp;
   DsArgs da{};
-  const DsTask *ds_factor = nullptr, *ds_solve = nullptr, *ds_res = nullptr;
+  const DsTask *ds_factor = nullptr, *ds_solve = nullptr;
+  const DsRows* ds_res = nullptr;
   const DsArgs* ds_args = nullptr;        // device copy of da
   const DsArgs* ds_corr = nullptr;        // the same for a correction: A dx = r
   double *ds_r = nullptr, *ds_dx = nullptr;
