@@ -14,6 +14,8 @@ constexpr int kDsSchurTile = 64;    // tile of the border update
 constexpr int kDsRowTile = 32;      // border rows per task of W = B X
 constexpr int kDsFwdRows = 64;      // border rows per task of the forward pass
 constexpr int kDsBwdCols = 32;      // pivot columns per task of the backward pass
+constexpr int kDsQueues = 8;        // task queues, one per die (XCD)
+constexpr int kDsOneQueue = 512;     // with fewer factorisation tasks all are in one
 constexpr int kDsResRows = 64;      // rows per workgroup of the residual
 
 // One front: p pivot vertices eliminated together and the b later vertices they couple
@@ -97,6 +99,9 @@ struct DsPlan {
   // tasks in an order in which every task comes after those it waits for: factorisation
   // with both passes of one right-hand side, and the two passes alone
   std::vector<DsTask> factor_tasks, solve_tasks;
+  // queue of each task: of the workgroups of one die, whose cache then holds what the
+  // tasks of a subtree share
+  std::vector<unsigned char> factor_queue, solve_queue;
   std::vector<DsRows> res_tasks;   // of the residual
   std::vector<int> res0;           // [sheets + 1]
   long long factor_doubles = 0, work_doubles = 0;

@@ -18,11 +18,12 @@
 // What bounds it: the chain of fronts from a leaf to the root (15 of a 64x64 sheet), each
 // a pivot sweep and three hand-offs between workgroups, not the arithmetic (1.3 GFLOP).
 // A forward and adjoint of 60 steps on that sheet took 140 ms with the iterative solver
-// (100 to 300 iterations of 5 to 12 us a solve) and take 51 ms with this one; 40 solves of a
-// 17x17 sheet 67 and 11 ms, 30 forward and adjoint steps of a 200x200 sheet 427 and 225 ms.
-// Workgroups take the tasks in a topological order from one queue and wait on per-front
-// counters, so the only tasks ever waited for have been taken by workgroups that run:
-// no co-residency is needed, and a launch per level and kind (75 launches of at least
+// (100 to 300 iterations of 5 to 12 us a solve) and take 49 ms with this one; 40 solves of a
+// 17x17 sheet 67 and 11 ms, 30 forward and adjoint steps of a 200x200 sheet 427 and 213 ms.
+// Workgroups take the tasks in a topological order and wait on per-front counters, so the
+// only tasks ever waited for have been taken by workgroups that run (one of each queue is
+// enough: the order within every queue is part of one order of all tasks, and a workgroup
+// changes queues empty-handed), and a launch per level and kind (75 launches of at least
 // 4 us each on that sheet) is saved. Every array that one task writes and another reads
 // is written once per launch, on cache lines of its own, with write-through stores, and
 // read only after its counter, so ordinary cached loads see it. All waits are bounded: a
@@ -224,16 +225,18 @@ __device__ __forceinline__ Table<T> table(const T* p) {
 
 struct Shared {
   int go, bad;
-  int next[2];     // the number of the task whose record is in rec
+  int next[2];     // >= 0: rec holds a task
   DsTask rec[2];   // this task's and the next one's record, in turn
 };
 
 // What wavefront 0 holds of the next task while this one runs.
 struct Next {
   const DsTask* tasks;
-  int ntasks;
+  int list;        // of DsArgs::q0
+  int queue;       // the queue this workgroup takes from,
+  int base, count; // its first task and their number
   int slot;        // of Shared::rec for the next task
-  int number;
+  int number;      // in its queue; -1: the queue is empty, -2: all are
   unsigned long long rec;   // 8 bytes of its record per lane
 };
 
@@ -311,13 +314,55 @@ __device__ __forceinline__ int wait_children(Table<DsArgs> a, const DsTask& tk, 
   return go;
 }
 
-// Starts the load of the next task's record; after the task's first wait, when the task's
+__device__ __forceinline__ void claim(Table<DsArgs> a, Next& nx) {
+  if (threadIdx.x == 0)
+    nx.number = __hip_atomic_fetch_add(a->queue + kDsLine * nx.queue, 1, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ void load_record(Next& nx) {
+  nx.rec = reinterpret_cast<const unsigned long long*>(nx.tasks + nx.base + nx.number)[threadIdx.x];
+}
+
+// Starts the load of the next task's record; some time into the task, when the next one's
 // number has come back from the queue.
 __device__ __forceinline__ void fetch_next(Next& nx) {
   if (threadIdx.x >= 64) return;
   nx.number = uni(nx.number);
-  if (nx.number < nx.ntasks)
-    nx.rec = reinterpret_cast<const unsigned long long*>(nx.tasks + nx.number)[threadIdx.x];
+  if (nx.number >= nx.count) nx.number = -1;
+  else load_record(nx);
+}
+
+// Takes a task from the first queue that has one, its own first. Only when no task is
+// held: a task of another queue may come before the one being run, and waiting for it
+// behind that one could be waiting for itself.
+__device__ __forceinline__ void find_task(Table<DsArgs> a, Next& nx, bool first, Shared& sh) {
+  if (threadIdx.x < 64) {
+    const Table<int> q0 = a->q0[nx.list];
+    for (;;) {
+      const int q = (nx.queue + threadIdx.x) % kDsQueues;
+      int head = 0;
+      if (!first && threadIdx.x < kDsQueues)
+        head = __hip_atomic_load(a->queue + kDsLine * q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const bool some = threadIdx.x < kDsQueues && head < q0[q + 1] - q0[q];
+      first = false;
+      const unsigned long long m = __ballot(some);
+      nx.number = -2;
+      if (m == 0) break;
+      nx.queue = (nx.queue + __builtin_ctzll(m)) % kDsQueues;
+      nx.base = q0[nx.queue];
+      nx.count = q0[nx.queue + 1] - nx.base;
+      claim(a, nx);
+      nx.number = uni(nx.number);
+      if (nx.number < nx.count) {
+        load_record(nx);
+        reinterpret_cast<unsigned long long*>(&sh.rec[nx.slot])[threadIdx.x] = nx.rec;
+        break;
+      }
+    }
+    if (threadIdx.x == 0) sh.next[nx.slot] = nx.number;
+  }
+  sync();
 }
 
 // Counts a task as done once every wavefront's stores have completed (put() writes
@@ -377,7 +422,6 @@ __device__ __forceinline__ bool task_pivot(Table<DsArgs> a, const DsTask& tk, Ne
       }
   }
   if (!wait_children(a, tk, kDsHeadDone, 0, 0, sh)) return false;
-  fetch_next(nx);
   // A lane takes columns lane and lane + 64 of every eighth row (at most 96); the loads of
   // the first two children are all in flight before the first is used.
   constexpr int NR = 3 * kDsMaxPiv / kWaves, N0 = 64 / kWaves, N1 = NR - N0;
@@ -422,6 +466,7 @@ __device__ __forceinline__ bool task_pivot(Table<DsArgs> a, const DsTask& tk, Ne
     sync();
     add(ch, 3 * K.q, s0, s1);
   }
+  fetch_next(nx);
   sync();
   const int g = lane >> 4, c16 = lane & 15;
   constexpr int NS = (kSide * (kSide + 1) / 2 + kWaves - 2) / (kWaves - 1);
@@ -610,7 +655,6 @@ __device__ __forceinline__ bool task_border(Table<DsArgs> a, const DsTask& tk, N
   }
   const int go = wait_children(a, tk, kDsSchurDone, cnt + kDsPivotDone, lane == 2 ? 1 : 0, sh);
   if (!go) return false;
-  fetch_next(nx);
   // a lane takes pivot columns lane and lane + 64 of this wavefront's rows of a child
   auto gather = [&](int ch, const double* S0, int nq, int ld, double (&s0)[NR], double (&s1)[NR]) {
     const int c0 = lane < nq ? 8 * lane : kNowhere, c1 = lane + 64 < nq ? 8 * (lane + 64) : kNowhere;
@@ -660,6 +704,7 @@ __device__ __forceinline__ bool task_border(Table<DsArgs> a, const DsTask& tk, N
   }
   sync();
   put_rows(a->ws + uni(tk.f.bo) + (size_t)r0 * np, Fl, rows, np, tid);
+  fetch_next(nx);
   if (go == 1 && !wait_one(a, cnt + kDsPivotDone, 1, sh)) return false;
   const double* X = fac + uni(tk.f.xo);
   double* W = fac + uni(tk.f.wo) + (size_t)r0 * np;
@@ -726,7 +771,6 @@ __device__ __forceinline__ bool task_schur(Table<DsArgs> a, const DsTask& tk, Ne
                           ? min(per, (nb + kDsRowTile - 1) / kDsRowTile - per * group) : 0;
   const int go = wait_children(a, tk, kDsSchurDone, rows_cnt, rows_of, sh);
   if (!go) return false;
-  fetch_next(nx);
   double x[2][8];
 #pragma unroll
   for (int ch = 0; ch < 2; ++ch) {
@@ -768,6 +812,7 @@ __device__ __forceinline__ bool task_schur(Table<DsArgs> a, const DsTask& tk, Ne
   for (int q = 0; q < 8; ++q) acc[q >> 2][q & 3] = -(x[0][q] + x[1][q]);
   stage(k1);
   if (k2 > 0) fetch(48, k2);
+  fetch_next(nx);
   sync();
   const double* w0 = Wl + (32 * (wave >> 2) + c16) * kLdK;
   const double* b0 = Bl + (16 * (wave & 3) + c16) * kLdK;
@@ -824,7 +869,6 @@ __device__ __forceinline__ bool task_forward(Table<DsArgs> a, const DsTask& tk, 
     go = wait_lanes(a, c, target, want, sh);
     if (!go) return false;
     if (nc > 2) go = 1;
-    fetch_next(nx);
   }
   const __amdgpu_buffer_rsrc_t W = buffer(fac + uni(tk.f.wo), 8 * nb * np);
   double w[NP][kSide];
@@ -838,7 +882,6 @@ __device__ __forceinline__ bool task_forward(Table<DsArgs> a, const DsTask& tk, 
   double v = 0.0;
   if (tid < 3 * p) v = a->rhs[(size_t)(tid % 3) * a->nv + a->tab[tk.f.verts + tid / 3]];
   if (go == 1 && !wait_children(a, tk, kDsForwardDone, 0, 0, sh)) return false;
-  if (!factor) fetch_next(nx);
   double h[NP], e[2];
 #pragma unroll
   for (int ch = 0; ch < 2; ++ch) {
@@ -871,6 +914,7 @@ __device__ __forceinline__ bool task_forward(Table<DsArgs> a, const DsTask& tk, 
     t[tid] = v;
     if (chunk == 0) put(a->ws + tk.f.t + tid, v);
   }
+  fetch_next(nx);
   sync();
 #pragma unroll
   for (int q = 0; q < NP; ++q) {
@@ -909,7 +953,6 @@ __device__ __forceinline__ bool task_backward(Table<DsArgs> a, const DsTask& tk,
     const int target = lane == 0 ? 1 : lane == 1 ? nfwd : 0;
     go = wait_lanes(a, cw, target, lane == 2 ? nlast : target, sh);
     if (!go) return false;
-    fetch_next(nx);
   }
   const int nb = uni(tk.f.nb);
   const __amdgpu_buffer_rsrc_t X = buffer(fac + uni(tk.f.xo), 8 * np * np);
@@ -932,7 +975,6 @@ __device__ __forceinline__ bool task_backward(Table<DsArgs> a, const DsTask& tk,
     if (G * q < np) x[q] = load1(X, at + 8 * G * np * q);
   }
   if (go == 1 && !wait_one(a, last, nlast, sh)) return false;
-  if (!factor) fetch_next(nx);
   // zero on the padding rows, whose W is zero
 #pragma unroll
   for (int q = 0; q < NB; ++q)
@@ -940,6 +982,7 @@ __device__ __forceinline__ bool task_backward(Table<DsArgs> a, const DsTask& tk,
   for (int r = tid + kThreads * NB; r < nb; r += kThreads)
     xb[r] = r < n3 ? a->ws[xsrc[r / 3] + r % 3] : 0.0;
   if (tid < np) t[tid] = a->ws[tk.f.t + tid];
+  fetch_next(nx);
   sync();
   double s = 0.0, u = 0.0;
 #pragma unroll
@@ -969,7 +1012,7 @@ __device__ __forceinline__ bool task_backward(Table<DsArgs> a, const DsTask& tk,
 __global__ void __launch_bounds__(kThreads, 4) k_ds_run(const DsArgs* __restrict__ args,
                                                         double* __restrict__ fac,
                                                         const DsTask* __restrict__ tasks,
-                                                        int ntasks, int factor,
+                                                        int factor,
                                                         const int* __restrict__ done, int ninst) {
   if (done) {   // a correction: nothing to do when every sheet is solved
     int n = 0;
@@ -978,24 +1021,21 @@ __global__ void __launch_bounds__(kThreads, 4) k_ds_run(const DsArgs* __restrict
   }
   extern __shared__ __align__(16) double lds[];
   __shared__ Shared sh;
-  int* queue = args->queue;
-  Next nx{tasks, ntasks, 0, 0, 0};
-  if (threadIdx.x == 0)
-    nx.number = __hip_atomic_fetch_add(queue, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  fetch_next(nx);
-  if (threadIdx.x < 64) reinterpret_cast<unsigned long long*>(&sh.rec[0])[threadIdx.x] = nx.rec;
-  if (threadIdx.x == 0) sh.next[0] = nx.number;
-  sync();
+  Next nx{tasks, factor, (int)blockIdx.x % kDsQueues, 0, 0, 0, 0, 0};
+  find_task(table(args), nx, true, sh);
 #pragma unroll 1
   for (;;) {
-    if (uni(sh.next[nx.slot]) >= ntasks) return;
+    if (uni(sh.next[nx.slot]) < 0) {
+      sync();
+      find_task(table(args), nx, false, sh);
+      if (uni(sh.next[nx.slot]) < 0) return;
+    }
     const DsTask& tk = sh.rec[nx.slot];
     nx.slot ^= 1;
-    if (threadIdx.x == 0)   // the next task's number travels while this one runs
-      nx.number = __hip_atomic_fetch_add(queue, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const DsArgs* ap = args;
     asm volatile("" : "+s"(ap));
     const Table<DsArgs> a = table(ap);
+    claim(a, nx);   // the next task's number travels while this one runs
     const int kind = uni(tk.kind);
     bool go = true;
     if (kind == kDsPivot) go = task_pivot(a, tk, nx, fac, lds, sh);
@@ -1110,7 +1150,7 @@ hipError_t ds_prepare(int* blocks_per_cu) {
 void launch_ds_run(const DsArgs* args, double* fac, const DsTask* tasks, int ntasks, bool factor,
                    int grid, const int* done, int ninst, hipStream_t st) {
   hipLaunchKernelGGL(k_ds_run, dim3(std::min(grid, ntasks)), dim3(kThreads), kLds * sizeof(double),
-                     st, args, fac, tasks, ntasks, factor ? 1 : 0, done, ninst);
+                     st, args, fac, tasks, factor ? 1 : 0, done, ninst);
 }
 
 void launch_ds_add(const DsArgs& a, const DsAccept& o, const double* dx, const int* vert_inst,

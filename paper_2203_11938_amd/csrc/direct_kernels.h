@@ -18,9 +18,12 @@ struct DsArgs {
   const double* rhs;   // [3][nv]
   double* sol;         // [3][nv]
   int* count;          // counters, queue and abort flag; zero before a launch
-  int* queue;
+  int* queue;          // [kDsQueues] heads, kDsLine ints apart
   int* abort_flag;
+  int q0[2][kDsQueues + 1];   // the queues' tasks in the lists: passes alone, factorisation
 };
+
+constexpr int kDsLine = 32;   // ints of a cache line
 
 // Acceptance of a solve per sheet: done[inst] = 1 when |b - A x| <= tol |b| (with one
 // iteration recorded), else 0: the iterative solver then takes the sheet. The counters of
@@ -42,8 +45,8 @@ struct DsAccept {
 };
 
 hipError_t ds_prepare(int* blocks_per_cu);
-// Runs the tasks in order on at most `grid` workgroups; args: device copy of DsArgs; fac: X
-// and W of every front; factor: the list factorises. With
+// Runs a list of ntasks tasks, queue after queue, on at most `grid` workgroups; args:
+// device copy of DsArgs; fac: X and W of every front; factor: the list factorises. With
 // `done` ([ninst]) nothing runs when every sheet is marked.
 void launch_ds_run(const DsArgs* args, double* fac, const DsTask* tasks, int ntasks, bool factor,
                    int grid, const int* done, int ninst, hipStream_t st);

@@ -398,17 +398,29 @@ sim_status setup_direct(sim_t* s, const std::vector<HostSheet>& sheets) {
   TRY(upload(s, P.fronts, &a.fr));
   TRY(upload(s, P.kids, &a.kid));
   TRY(upload(s, P.tab, &a.tab));
-  TRY(upload(s, P.factor_tasks, &s->ds_factor));
-  TRY(upload(s, P.solve_tasks, &s->ds_solve));
+  // a queue's tasks are contiguous, in their order
+  auto by_queue = [](const std::vector<DsTask>& list, const std::vector<unsigned char>& queue,
+                     int (&q0)[kDsQueues + 1]) {
+    std::fill(q0, q0 + kDsQueues + 1, 0);
+    for (unsigned char q : queue) ++q0[q + 1];
+    for (int q = 0; q < kDsQueues; ++q) q0[q + 1] += q0[q];
+    int at[kDsQueues];
+    std::copy(q0, q0 + kDsQueues, at);
+    std::vector<DsTask> out(list.size());
+    for (size_t k = 0; k < list.size(); ++k) out[at[queue[k]]++] = list[k];
+    return out;
+  };
+  TRY(upload(s, by_queue(P.factor_tasks, P.factor_queue, a.q0[1]), &s->ds_factor));
+  TRY(upload(s, by_queue(P.solve_tasks, P.solve_queue, a.q0[0]), &s->ds_solve));
   TRY(upload(s, P.res_tasks, &s->ds_res));
   void* q = nullptr;
   TRY(alloc(s, (size_t)P.factor_doubles * 8, &q)); s->ds_fac.assign(1, (double*)q);
   TRY(alloc(s, (size_t)P.work_doubles * 8, &q)); a.ws = (double*)q;
-  const int counters = (P.counters + 31) / 32 * 32 + 64;   // + queue and abort flag
+  const int counters = (P.counters + kDsLine - 1) / kDsLine * kDsLine + kDsLine * (kDsQueues + 1);
   TRY(alloc(s, 4 * (size_t)counters, &q)); a.count = (int*)q;
   HIPCHECK(s, hipMemset(a.count, 0, 4 * (size_t)counters));
-  a.queue = a.count + counters - 64;
-  a.abort_flag = a.count + counters - 32;
+  a.queue = a.count + counters - kDsLine * (kDsQueues + 1);
+  a.abort_flag = a.count + counters - kDsLine;
   s->dacc.clear_ints = counters;
   a.nv = L.nv;
   a.maxnz = L.maxnz;
