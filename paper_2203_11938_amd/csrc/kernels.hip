@@ -673,6 +673,14 @@ __device__ __forceinline__ bool inv3(const double a[9], double o[9]) {
   return true;
 }
 
+// The rows' workgroup of a block: consecutive ones on one die (blocks go to the eight dies
+// in turn), whose cache then serves the elements that neighbouring rows share. The grid
+// is rounded up to whole turns. 64 sheets of 16 to 64 a side: k_assemble 320 to 298 us,
+// k_adj_rows 73 to 56 us; 200x200: 111 to 98, 34 to 26 us.
+__device__ __forceinline__ int die_block() {
+  return (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+}
+
 template <typename T, typename TM, int L>
 __global__ void __launch_bounds__(256) k_assemble(Mesh m, Elem el, AssembleArgs<T, TM> a) {
   // L lanes per row (4, or 16 on small meshes, which would otherwise occupy few CUs),
@@ -685,8 +693,9 @@ __global__ void __launch_bounds__(256) k_assemble(Mesh m, Elem el, AssembleArgs<
   constexpr int RW = 64 / L;   // rows per wavefront
   const int lane = threadIdx.x & 63;
   const int g = L == 4 ? lane >> 4 : lane & 15, rw = L == 4 ? lane & 15 : lane >> 4;
-  const int i0 = (blockIdx.x * 4 + (int)(threadIdx.x >> 6)) * RW + rw;
+  const int i0 = (die_block() * 4 + (int)(threadIdx.x >> 6)) * RW + rw;
   const int nv = m.nv;
+  if (i0 - rw >= nv) return;   // a wavefront past the rows
   const bool live = i0 < nv;
   const int i = live ? i0 : nv - 1;
   const int inst = m.vert_inst[i];
@@ -3108,9 +3117,9 @@ __global__ void __launch_bounds__(256) k_adj_elements(Mesh m, Elem el, AdjArgs<T
 template <typename T>
 __global__ void __launch_bounds__(256) k_adj_rows(Mesh m, Elem el, AdjArgs<T> a) {
   const int lane = threadIdx.x & 63, g = lane & 15;
-  const int i0 = blockIdx.x * 16 + (int)(threadIdx.x >> 4);
+  const int i0 = die_block() * 16 + (int)(threadIdx.x >> 4);
   const int nv = m.nv;
-  if (blockIdx.x * 16 + (int)((threadIdx.x >> 6) << 2) >= nv) return;   // a wavefront past the rows
+  if (i0 - (lane >> 4) >= nv) return;   // a wavefront past the rows
   const bool live = i0 < nv;   // lanes past the last row work on a copy of it
   const int i = live ? i0 : nv - 1;
   const double h = a.h, h2 = a.h * a.h;
@@ -3357,7 +3366,7 @@ template <typename T, typename TM>
 void launch_assemble(const Mesh& m, const Elem& el, const AssembleArgs<T, TM>& a, hipStream_t st) {
   // sixteen lanes per row for every mesh size: the same summation order whatever the
   // handle holds, so a sheet in a batch assembles bit for bit as on its own
-  hipLaunchKernelGGL((k_assemble<T, TM, 16>), dim3(blocks_for(m.nv, 16)), dim3(256), 0, st, m, el, a);
+  hipLaunchKernelGGL((k_assemble<T, TM, 16>), dim3(blocks_for(m.nv, 8 * 16) * 8), dim3(256), 0, st, m, el, a);
 }
 
 template <typename TM>
@@ -3551,7 +3560,7 @@ void launch_adj_elements(const Mesh& m, const Elem& el, const AdjArgs<T>& a, hip
 
 template <typename T>
 void launch_adj_rows(const Mesh& m, const Elem& el, const AdjArgs<T>& a, hipStream_t st) {
-  hipLaunchKernelGGL(k_adj_rows<T>, dim3(blocks_for(m.nv, 16)), dim3(256), 0, st, m, el, a);
+  hipLaunchKernelGGL(k_adj_rows<T>, dim3(blocks_for(m.nv, 8 * 16) * 8), dim3(256), 0, st, m, el, a);
 }
 
 template <typename T>
