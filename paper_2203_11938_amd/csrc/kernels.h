@@ -95,15 +95,16 @@ hipError_t pcg_occupancy(int rows, size_t lds, int maxnz, int mat_home, bool coa
                          bool split, int* blocks_per_cu);
 template <typename TM>
 void launch_pcg(const Mesh& m, const SolverPlan& plan, const SolverWork& w, const Coarse& cs,
-                const PcgArgs<TM>& a, hipStream_t st);
+                const PcgArgs<TM>& a, hipStream_t st, bool cleared = false);
 // Coarse operator of the step at positions x and assembled matrix A: frames,
 // Galerkin product and its in-place blocked symmetric sweep (one launch per group of
 // sheets; sweep_groups: first workgroup of each group, then the total). No-op without
-// a coarse space.
+// a coarse space. True when it also cleared the solver's arrays: the next launch_pcg need
+// not (cleared).
 template <typename TM>
-void launch_coarse_setup(const Mesh& m, const Coarse& c, const double* x, const TM* A,
-                         long long coarse_doubles, const std::vector<int>& sweep_groups,
-                         hipStream_t st);
+bool launch_coarse_setup(const Mesh& m, const SolverWork& w, const Coarse& c, const double* x,
+                         const TM* A, long long coarse_doubles,
+                         const std::vector<int>& sweep_groups, hipStream_t st);
 // Dynamic LDS of the sweep kernel and its co-resident workgroups per CU for a given
 // number of tiles held per workgroup.
 size_t gj_sweep_lds(int tiles_per_wg);

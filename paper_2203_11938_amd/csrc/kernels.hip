@@ -809,11 +809,58 @@ __global__ void __launch_bounds__(256) k_assemble(Mesh m, Elem el, AssembleArgs<
 // sheet) and its inverse by a blocked symmetric sweep. The PCG applies A_c^-1 as a
 // dense product with the rows of the inverse that its workgroup needs.
 
-// One wavefront per aggregate: centroid of the free vertices at x and the offsets
-// x_i - c of its members (zero on pinned members and where rotations are unused).
-__global__ void __launch_bounds__(64) k_coarse_frame(Mesh m, Coarse c, const double* __restrict__ x) {
-  const int a = blockIdx.x, lane = threadIdx.x, nv = m.nv;
-  if (c.done && c.done[c.agg_inst[a]]) return;
+// Arrays of the solver to clear: barriers, abort flag, tagged publications.
+struct ZeroRanges {
+  int* p[4];
+  int n[4];
+  const int* done;   // with it: nothing to do when every sheet is solved
+  int ninst;
+};
+
+// Whether every sheet is marked (done may be nullptr: none is).
+__device__ __forceinline__ bool all_done(const int* done, int ninst) {
+  if (!done) return false;
+  int n = 0;
+  for (int b = 0; b < ninst; ++b) n += done[b];
+  return n == ninst;
+}
+
+__device__ __forceinline__ void zero_ranges(const ZeroRanges& z, int k0, int stride) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    for (int k = k0; k < z.n[r]; k += stride) z.p[r][k] = 0;
+}
+
+__global__ void __launch_bounds__(256) k_zero_ranges(ZeroRanges z) {
+  if (all_done(z.done, z.ninst)) return;
+  zero_ranges(z, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
+}
+
+// First launch of a step's coarse operators. Blocks [0, nframe), one wavefront per
+// aggregate: centroid of the free vertices at x and the offsets x_i - c of its members
+// (zero on pinned members and where rotations are unused). The other blocks set the
+// matrices to zero, with a unit diagonal on the unused modes of every aggregate and the
+// padding rows of every sheet, the sheets' success flags, the sweep's flags and the
+// solver's arrays. (Launches that find every sheet solved directly are paid for all the
+// same, 3 us each; eight a solve before the launches of this kind were merged, now four.)
+__global__ void __launch_bounds__(256) k_coarse_prepare(Mesh m, Coarse c, const double* __restrict__ x,
+                                                        int nframe, ZeroRanges z) {
+  if ((int)blockIdx.x >= nframe) {
+    if (all_done(c.done, m.ninst)) return;
+    const int k0 = ((int)blockIdx.x - nframe) * 256 + threadIdx.x;
+    const int stride = ((int)gridDim.x - nframe) * 256;
+    zero_ranges(z, k0, stride);
+    for (int k = k0; k < m.ninst * c.sw_stride; k += stride) c.sw_sync[k] = 0;
+    for (int b = 0; b < m.ninst; ++b) {
+      const int np = c.inst_np[b];
+      double* M = c.mat + c.inst_coff[b];
+      if (k0 == 0) c.ok[b] = 1;
+      for (long k = k0; k < (long)np * np; k += stride) M[k] = 0.0;
+    }
+    return;
+  }
+  const int a = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63, nv = m.nv;
+  if (a >= c.nagg || (c.done && c.done[c.agg_inst[a]])) return;
   const int v0 = c.agg_v0[a], v1 = c.agg_v0[a + 1];
   double s[3] = {0.0, 0.0, 0.0}, cnt = 0.0;
   for (int i = v0 + lane; i < v1; i += 64) {
@@ -851,14 +898,14 @@ __device__ __forceinline__ void mul33(const double* A, const double* B, double* 
 // matrix slots of P_i^T A_ij P_j with P_i = [I | -[r_i]x], i.e.
 //   [[A, -A R_j], [R_i A, -R_i A R_j]];
 // written at (a, b) and, transposed, at (b, a). Unused modes give zero rows and
-// columns (their unit diagonal is set by k_coarse_dead). The threads take the slots in
+// columns with a unit diagonal. The threads take the slots in
 // turn (four wavefronts keep more of the dependent gathers in flight); each wavefront
 // reduces its 36 sums together by recursive halving, then the wavefronts' sums are
 // added in order.
 template <typename TM>
-__global__ void __launch_bounds__(256) k_coarse_assemble(Mesh m, Coarse c, const TM* __restrict__ A) {
-  __shared__ double s_part[4][36];
-  const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nv = m.nv;
+__device__ __forceinline__ void coarse_pair(const Mesh& m, const Coarse& c, const TM* __restrict__ A,
+                                            int p, double (*s_part)[36]) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nv = m.nv;
   const int a = c.pair_a[p], b = c.pair_b[p];
   if (c.done && c.done[c.agg_inst[a]]) return;
   double acc[36];
@@ -901,9 +948,16 @@ __global__ void __launch_bounds__(256) k_coarse_assemble(Mesh m, Coarse c, const
   const int ma = c.agg_modes[a], mb = c.agg_modes[b];
   const int r = tid / 6, q = tid % 6;
   const double sum = ((s_part[0][tid] + s_part[1][tid]) + s_part[2][tid]) + s_part[3][tid];
-  const double val = (r < ma && q < mb) ? sum : 0.0;
+  const double val = (r < ma && q < mb) ? sum : a == b && r == q ? 1.0 : 0.0;
   M[(size_t)(6 * la + r) * np + 6 * lb + q] = val;
   if (a != b) M[(size_t)(6 * lb + q) * np + 6 * la + r] = val;
+}
+
+// LDS written by a wavefront's lanes is read by others of the same wavefront.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
 // Middle level, one wavefront per run of kMid vertices: offsets of its members from
@@ -912,10 +966,10 @@ __global__ void __launch_bounds__(256) k_coarse_assemble(Mesh m, Coarse c, const
 // zero row and column in the inverse; a block that is not positive definite gives a
 // zero inverse (the run then adds nothing to the preconditioner).
 template <typename TM>
-__global__ void __launch_bounds__(64) k_mid_setup(Mesh m, Coarse c, const double* __restrict__ x,
-                                                  const TM* __restrict__ A) {
-  __shared__ double sr[3][kMid];
-  const int a = blockIdx.x, lane = threadIdx.x, nv = m.nv;
+__device__ __forceinline__ void mid_block(const Mesh& m, const Coarse& c, const double* __restrict__ x,
+                                          const TM* __restrict__ A, int a, double (*sr)[kMid],
+                                          double* s_acc) {
+  const int lane = threadIdx.x & 63, nv = m.nv;
   const int v0 = c.mid_v0[a], v1 = c.mid_v0[a + 1], modes = c.mid_modes[a];
   if (c.done && c.done[m.vert_inst[v0]]) return;
   const int i = v0 + lane;
@@ -932,7 +986,7 @@ __global__ void __launch_bounds__(64) k_mid_setup(Mesh m, Coarse c, const double
       if (mem) c.mid_crel[k * nv + i] = r;
     }
   }
-  __syncthreads();
+  wave_lds_sync();
   double acc[36];
 #pragma unroll
   for (int e = 0; e < 36; ++e) acc[e] = 0.0;
@@ -960,7 +1014,6 @@ __global__ void __launch_bounds__(64) k_mid_setup(Mesh m, Coarse c, const double
       }
   }
   // the 36 sums by recursive halving (lane l holds sum l), gathered for lane 0
-  __shared__ double s_acc[36];
   {
     double v[64];
 #pragma unroll
@@ -968,7 +1021,7 @@ __global__ void __launch_bounds__(64) k_mid_setup(Mesh m, Coarse c, const double
     const double t = wave_sums_scatter<64>(v, lane);
     if (lane < 36) s_acc[lane] = t;
   }
-  __syncthreads();
+  wave_lds_sync();
   if (lane == 0) {
 #pragma unroll
     for (int e = 0; e < 36; ++e) acc[e] = s_acc[e];
@@ -1000,24 +1053,31 @@ __global__ void __launch_bounds__(64) k_mid_setup(Mesh m, Coarse c, const double
   }
 }
 
-// Unit diagonal for the unused modes of every aggregate and for the padding rows
-// of every sheet (threads past the aggregates handle the sheets, and set the sheet's
-// success flag); the threads after those clear the sweep's flags.
-__global__ void __launch_bounds__(256) k_coarse_dead(Coarse c, int ninst) {
-  const int a = blockIdx.x * blockDim.x + threadIdx.x;
-  if (a < c.nagg) {
-    const int inst = c.agg_inst[a], np = c.inst_np[inst], la = a - c.inst_agg0[inst];
-    double* M = c.mat + c.inst_coff[inst];
-    for (int q = c.agg_modes[a]; q < 6; ++q) M[(size_t)(6 * la + q) * np + 6 * la + q] = 1.0;
-  } else if (a < c.nagg + ninst) {
-    const int inst = a - c.nagg, np = c.inst_np[inst];
-    double* M = c.mat + c.inst_coff[inst];
-    for (int r = c.inst_nc[inst]; r < np; ++r) M[(size_t)r * np + r] = 1.0;
-    c.ok[inst] = 1;
-  } else if (a < c.nagg + ninst + ninst * c.sw_stride) {
-    c.sw_sync[a - c.nagg - ninst] = 0;
+// Second launch of a step's coarse operators: the pairs' blocks of the coarse matrices, the
+// middle level's blocks (four to a workgroup) and, last, the unit diagonal of the sheets'
+// padding rows and of aggregates that are pinned altogether (which have no pair).
+template <typename TM>
+__global__ void __launch_bounds__(256) k_coarse_operators(Mesh m, Coarse c, const double* __restrict__ x,
+                                                          const TM* __restrict__ A) {
+  __shared__ double s[4][3 * kMid + 36];
+  const int b = blockIdx.x, nmid = (c.nmid + 3) / 4, wave = threadIdx.x >> 6;
+  if (b < c.npair) {
+    coarse_pair(m, c, A, b, reinterpret_cast<double (*)[36]>(&s[0][0]));
+  } else if (b < c.npair + nmid) {
+    const int a = 4 * (b - c.npair) + wave;
+    if (a < c.nmid)
+      mid_block(m, c, x, A, a, reinterpret_cast<double (*)[kMid]>(&s[wave][0]), &s[wave][3 * kMid]);
+  } else {
+    const int i = (b - c.npair - nmid) * 4 + wave;
+    if (i >= m.ninst || (c.done && c.done[i])) return;
+    const int np = c.inst_np[i];
+    double* M = c.mat + c.inst_coff[i];
+    const int nc = c.inst_nc[i], a0 = c.inst_agg0[i];
+    for (int r = threadIdx.x & 63; r < np; r += 64)
+      if (r >= nc || c.agg_modes[a0 + r / 6] == 0) M[(size_t)r * np + r] = 1.0;
   }
 }
+
 
 // Reciprocal by Newton-Raphson refinement of the hardware estimate (two steps of
 // x <- x + x (1 - a x), each squaring the relative error).
@@ -3283,36 +3343,6 @@ __global__ void k_fill_int(int* p, int n, int v) {
 
 // Zeroes up to four int ranges in one launch (grid-stride; the solver's counters,
 // abort flag and tagged buffers before each launch).
-struct ZeroRanges {
-  int* p[4];
-  int n[4];
-  const int* done;   // with it: nothing to do when every sheet is solved
-  int ninst;
-};
-
-// Whether every sheet is marked (done may be nullptr: none is).
-__device__ __forceinline__ bool all_done(const int* done, int ninst) {
-  if (!done) return false;
-  int n = 0;
-  for (int b = 0; b < ninst; ++b) n += done[b];
-  return n == ninst;
-}
-
-__global__ void __launch_bounds__(256) k_zero_ranges(ZeroRanges z) {
-  if (all_done(z.done, z.ninst)) return;
-  const int stride = gridDim.x * blockDim.x;
-#pragma unroll
-  for (int r = 0; r < 4; ++r)
-    for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < z.n[r]; k += stride) z.p[r][k] = 0;
-}
-
-// Clears the coarse matrices before their assembly.
-__global__ void __launch_bounds__(256) k_coarse_clear(Coarse c, int ninst, long n) {
-  if (all_done(c.done, ninst)) return;
-  const long stride = (long)gridDim.x * blockDim.x;
-  for (long k = (long)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += stride) c.mat[k] = 0.0;
-}
-
 __global__ void k_fill_double(double* p, long n, double v) {
   long k = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (k < n) p[k] = v;
@@ -3443,14 +3473,9 @@ static void launch_pcg_v(dim3 grid, dim3 block, size_t lds, hipStream_t st, cons
   hipLaunchKernelGGL((k_pcg<TM, L, C, O>), grid, block, lds, st, m, pg, w, cs, a);
 }
 
-template <typename TM>
-void launch_pcg(const Mesh& m, const SolverPlan& plan, const SolverWork& w, const Coarse& cs,
-                const PcgArgs<TM>& a, hipStream_t st) {
-  const bool coarse = cs.nagg > 0;
-  size_t lds = pcg_lds_bytes<TM>(m.maxnz, plan.rows, plan.mat_home, coarse ? cs.max_nc : 0,
-                                 plan.max_halo, coarse ? plan.xl_floats : 0);
+static ZeroRanges solver_ranges(const Mesh& m, const SolverWork& w, bool coarse, const int* done) {
   ZeroRanges z{};
-  z.done = a.done;
+  z.done = done;
   z.ninst = m.ninst;
   z.p[0] = w.barrier;
   z.n[0] = w.barrier_ints;
@@ -3462,9 +3487,21 @@ void launch_pcg(const Mesh& m, const SolverPlan& plan, const SolverWork& w, cons
     z.p[3] = reinterpret_cast<int*>(w.tred);
     z.n[3] = w.tred_ints;
   }
-  const int most = std::max(std::max(z.n[0], z.n[2]), z.n[3]);
-  hipLaunchKernelGGL(k_zero_ranges, dim3(std::min(blocks_for(most, 256), 1024)), dim3(256), 0,
-                     st, z);
+  return z;
+}
+
+template <typename TM>
+void launch_pcg(const Mesh& m, const SolverPlan& plan, const SolverWork& w, const Coarse& cs,
+                const PcgArgs<TM>& a, hipStream_t st, bool cleared) {
+  const bool coarse = cs.nagg > 0;
+  size_t lds = pcg_lds_bytes<TM>(m.maxnz, plan.rows, plan.mat_home, coarse ? cs.max_nc : 0,
+                                 plan.max_halo, coarse ? plan.xl_floats : 0);
+  if (!cleared) {
+    const ZeroRanges z = solver_ranges(m, w, coarse, a.done);
+    const int most = std::max(std::max(z.n[0], z.n[2]), z.n[3]);
+    hipLaunchKernelGGL(k_zero_ranges, dim3(std::min(blocks_for(most, 256), 1024)), dim3(256), 0,
+                       st, z);
+  }
   // one launch per solver group (a set of whole sheets whose workgroups are co-resident)
   for (int g = 0; g < plan.ngroups; ++g) {
     SolverPlan pg = plan;
@@ -3497,18 +3534,17 @@ void launch_pcg(const Mesh& m, const SolverPlan& plan, const SolverWork& w, cons
 }
 
 template <typename TM>
-void launch_coarse_setup(const Mesh& m, const Coarse& c, const double* x, const TM* A,
-                         long long coarse_doubles, const std::vector<int>& sweep_groups,
-                         hipStream_t st) {
-  if (c.nagg == 0) return;
-  hipLaunchKernelGGL(k_coarse_frame, dim3(c.nagg), dim3(64), 0, st, m, c, x);
-  hipLaunchKernelGGL(k_coarse_clear, dim3(std::min(blocks_for(coarse_doubles, 256), 2048)), dim3(256),
-                     0, st, c, m.ninst, (long)coarse_doubles);
-  if (c.npair > 0)
-    hipLaunchKernelGGL((k_coarse_assemble<TM>), dim3(c.npair), dim3(256), 0, st, m, c, A);
-  if (c.nmid > 0) hipLaunchKernelGGL((k_mid_setup<TM>), dim3(c.nmid), dim3(64), 0, st, m, c, x, A);
-  hipLaunchKernelGGL(k_coarse_dead, dim3(blocks_for(c.nagg + m.ninst + m.ninst * c.sw_stride, 256)),
-                     dim3(256), 0, st, c, m.ninst);
+bool launch_coarse_setup(const Mesh& m, const SolverWork& w, const Coarse& c, const double* x,
+                         const TM* A, long long coarse_doubles,
+                         const std::vector<int>& sweep_groups, hipStream_t st) {
+  if (c.nagg == 0) return false;
+  const int nframe = blocks_for(c.nagg, 4);
+  const int nclear = std::min(blocks_for(coarse_doubles, 256), 1024);
+  hipLaunchKernelGGL(k_coarse_prepare, dim3(nframe + nclear), dim3(256), 0, st, m, c, x, nframe,
+                     solver_ranges(m, w, true, c.done));
+  hipLaunchKernelGGL((k_coarse_operators<TM>),
+                     dim3(c.npair + blocks_for(c.nmid, 4) + blocks_for(m.ninst, 4)), dim3(256), 0,
+                     st, m, c, x, A);
   // one launch per group of whole sheets whose workgroups are co-resident
   const size_t lds = gj_sweep_lds(c.sw_tpw);
   for (size_t g = 0; g + 1 < sweep_groups.size(); ++g) {
@@ -3516,6 +3552,7 @@ void launch_coarse_setup(const Mesh& m, const Coarse& c, const double* x, const 
     if (n > 0)
       hipLaunchKernelGGL(k_gj_sweep, dim3(n), dim3(256), lds, st, c, m.ninst, sweep_groups[g]);
   }
+  return true;
 }
 
 size_t gj_sweep_lds(int tiles_per_wg) {
@@ -3589,9 +3626,10 @@ PHISFT_INSTANTIATE_ASM(double, double)
   template hipError_t pcg_prepare<T>(size_t, int, int, bool, int);                               \
   template hipError_t pcg_occupancy<T>(int, size_t, int, int, bool, int, bool, int*);            \
   template void launch_pcg<T>(const Mesh&, const SolverPlan&, const SolverWork&, const Coarse&, \
-                              const PcgArgs<T>&, hipStream_t);                                   \
-  template void launch_coarse_setup<T>(const Mesh&, const Coarse&, const double*, const T*,      \
-                                       long long, const std::vector<int>&, hipStream_t);         \
+                              const PcgArgs<T>&, hipStream_t, bool);                             \
+  template bool launch_coarse_setup<T>(const Mesh&, const SolverWork&, const Coarse&,            \
+                                       const double*, const T*, long long,                       \
+                                       const std::vector<int>&, hipStream_t);                    \
   template void launch_update<T>(const Mesh&, const double*, const double*, const double*,        \
                                  double, double*, double*, T*, int*, hipStream_t);               \
   template void launch_init_state<T>(const Mesh&, const T*, const T*, double*, double*, int*,    \

@@ -319,7 +319,7 @@ sim_status autotune(sim_t* s, const std::vector<HostPlan>& cands, const std::vec
   a.b = s->rhs;
   a.status = s->status;
   launch_assemble<double, TM>(s->mesh, s->el, a, st);
-  launch_coarse_setup<TM>(s->mesh, s->coarse, x, a.A, s->L.coarse_doubles, s->sweep_groups, st);
+  launch_coarse_setup<TM>(s->mesh, s->sw, s->coarse, x, a.A, s->L.coarse_doubles, s->sweep_groups, st);
   PcgArgs<TM> c{};
   c.A = a.A;
   c.Jinv = a.Jinv;
@@ -933,16 +933,19 @@ void solve_step(sim_t* s, int step, const double* xp, PcgArgs<TM> c, bool reuse,
       }
       Coarse cs = s->coarse;
       cs.done = c.done = o.done;
-      launch_coarse_setup<TM>(s->mesh, cs, xp, c.A, s->L.coarse_doubles, s->sweep_groups, st);
-      launch_pcg<TM>(s->mesh, s->plan, s->sw, cs, c, st);
+      const bool cleared = launch_coarse_setup<TM>(s->mesh, s->sw, cs, xp, c.A, s->L.coarse_doubles,
+                                                   s->sweep_groups, st);
+      launch_pcg<TM>(s->mesh, s->plan, s->sw, cs, c, st, cleared);
     });
     return;
   }
   bool have = false;
   const Coarse cs = coarse_for_step(s, step, &have);
+  bool cleared = false;
   if (!(reuse && have))
-    launch_coarse_setup<TM>(s->mesh, cs, xp, c.A, s->L.coarse_doubles, s->sweep_groups, st);
-  timed(s, st, [&] { launch_pcg<TM>(s->mesh, s->plan, s->sw, cs, c, st); });
+    cleared = launch_coarse_setup<TM>(s->mesh, s->sw, cs, xp, c.A, s->L.coarse_doubles,
+                                      s->sweep_groups, st);
+  timed(s, st, [&] { launch_pcg<TM>(s->mesh, s->plan, s->sw, cs, c, st, cleared); });
 }
 
 // ---------------------------------------------------------- step sequences
