@@ -8,7 +8,12 @@ namespace phisft {
 
 constexpr int kDsTile = 16;      // matrix-core tile: unknowns are padded to it
 constexpr int kDsMaxPiv = 32;    // pivot vertices of a front at most (96 unknowns)
-constexpr int kDsLeaf = 24;      // a piece of at most this many vertices is not cut further
+// A piece of at most this many vertices is not cut further, in sheets of at most
+// kDsSmallSheet vertices and in larger ones. Small sheets are bound by the pivot sweeps on
+// the chain, which small leaves shorten (48 against 24: 10x10 +6 %, 20x20 +3 %, 29x29 the
+// same); large ones gain from fewer fronts (32x32 -3 %, 64x64 -6 to -9 %, 200x200 -2 %;
+// 64 and more lose again there).
+constexpr int kDsLeafSmall = 24, kDsLeaf = 48, kDsSmallSheet = 900;
 constexpr int kDsMaxBorder = 4096;  // border unknowns of a front at most (LDS vectors)
 constexpr int kDsSchurTile = 64;    // tile of the border update
 constexpr int kDsRowTile = 32;      // border rows per task of W = B X

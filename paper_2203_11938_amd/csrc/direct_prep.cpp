@@ -23,6 +23,7 @@ struct Builder {
   const std::vector<double>& xr;
   std::vector<std::vector<int>> chunks;   // pivots of each front, elimination order
   std::vector<int> mark;
+  int leaf = 0;
 
   int neighbour(int i, int k) const { return col[(size_t)k * nv + i]; }
 
@@ -108,7 +109,7 @@ struct Builder {
   }
 
   void dissect(std::vector<int> s) {
-    if ((int)s.size() <= kDsLeaf) {
+    if ((int)s.size() <= leaf) {
       emit(std::move(s));
       return;
     }
@@ -139,6 +140,7 @@ void build_direct_plan(int nv, int maxnz, const std::vector<int>& ell_col,
   for (int b = 0; b < ninst; ++b) {
     std::vector<int> s(inst_nv[b]);
     for (int q = 0; q < inst_nv[b]; ++q) s[q] = inst_voff[b] + q;
+    B.leaf = inst_nv[b] <= kDsSmallSheet ? kDsLeafSmall : kDsLeaf;
     B.dissect(std::move(s));
   }
   const int nf = (int)B.chunks.size();
