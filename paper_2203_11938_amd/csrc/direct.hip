@@ -15,15 +15,15 @@
 // (k_ds_resid). A later solve with the same factor runs the forward and backward tasks
 // alone.
 //
-// What bounds it: the chain of fronts from a leaf to the root (15 of a 64x64 sheet), each
+// What bounds it: the chain of fronts from a leaf to the root (13 of a 64x64 sheet), each
 // a pivot sweep and three hand-offs between workgroups, not the arithmetic (1.3 GFLOP).
 // A forward and adjoint of 60 steps on that sheet took 140 ms with the iterative solver
-// (100 to 300 iterations of 5 to 12 us a solve) and take 49 ms with this one; 40 solves of a
-// 17x17 sheet 67 and 11 ms, 30 forward and adjoint steps of a 200x200 sheet 427 and 213 ms.
+// (100 to 300 iterations of 5 to 12 us a solve) and take 45 ms with this one; 40 steps of a
+// 17x17 sheet 66 and 10.8 ms, 30 forward and adjoint steps of a 200x200 sheet 434 and 209 ms.
 // Workgroups take the tasks in a topological order and wait on per-front counters, so the
 // only tasks ever waited for have been taken by workgroups that run (one of each queue is
 // enough: the order within every queue is part of one order of all tasks, and a workgroup
-// changes queues empty-handed), and a launch per level and kind (75 launches of at least
+// changes queues empty-handed), and a launch per level and kind (65 launches of at least
 // 4 us each on that sheet) is saved. Every array that one task writes and another reads
 // is written once per launch, on cache lines of its own, with write-through stores, and
 // read only after its counter, so ordinary cached loads see it. All waits are bounded: a
