@@ -117,9 +117,12 @@ struct DsPlan {
 };
 
 // xr: rest positions [nv][3] in the internal vertex order; ell_col, inst_voff and inst_nv
-// as in HostLayout. plan.ok is false when a front's border exceeds kDsMaxBorder.
+// as in HostLayout. plan.ok is false when a front's border exceeds kDsMaxBorder,
+// or when workspace and one factor exceed max_doubles (0: no limit; found before the tables
+// and tasks are built).
 void build_direct_plan(int nv, int maxnz, const std::vector<int>& ell_col,
                        const std::vector<int>& inst_voff, const std::vector<int>& inst_nv,
-                       const std::vector<double>& xr, DsPlan& plan);
+                       const std::vector<double>& xr, DsPlan& plan,
+                       double max_doubles = 0.0);
 
 }  // namespace phisft

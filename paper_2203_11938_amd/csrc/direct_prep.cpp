@@ -133,7 +133,7 @@ int up16(int n) { return (n + kDsTile - 1) / kDsTile * kDsTile; }
 
 void build_direct_plan(int nv, int maxnz, const std::vector<int>& ell_col,
                        const std::vector<int>& inst_voff, const std::vector<int>& inst_nv,
-                       const std::vector<double>& xr, DsPlan& P) {
+                       const std::vector<double>& xr, DsPlan& P, double max_doubles) {
   P = DsPlan{};
   const int ninst = (int)inst_voff.size();
   Builder B{nv, maxnz, ell_col, xr, {}, std::vector<int>(nv, 0)};
@@ -228,6 +228,7 @@ void build_direct_plan(int nv, int maxnz, const std::vector<int>& ell_col,
     F.bo = F.so + (long long)F.nb * F.nb;
     P.work_doubles = F.bo + (long long)F.nb * F.np;
   }
+  if (max_doubles > 0.0 && (double)P.factor_doubles + (double)P.work_doubles > max_doubles) return;
   // index tables
   std::vector<int> local(nv, -1);
   std::vector<std::vector<std::pair<int, int>>> rows;

@@ -386,9 +386,9 @@ bool want_direct(const sim_t* s, const sim_options& o) {
 sim_status setup_direct(sim_t* s, const std::vector<HostSheet>& sheets) {
   const HostLayout& L = s->L;
   DsPlan& P = s->dp;
-  build_direct_plan(L.nv, L.maxnz, L.ell_col, L.inst_voff, L.inst_nv, rest_internal(s, sheets), P);
-  const double bytes = 8.0 * ((double)P.factor_doubles + (double)P.work_doubles);
-  if (!P.ok || bytes > kDirectWorkCap) return SIM_OK;
+  build_direct_plan(L.nv, L.maxnz, L.ell_col, L.inst_voff, L.inst_nv, rest_internal(s, sheets), P,
+                    kDirectWorkCap / 8.0);
+  if (!P.ok) return SIM_OK;
   int dev = 0, ncu = 0, per_cu = 0;
   HIPCHECK(s, hipGetDevice(&dev));
   HIPCHECK(s, hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
@@ -825,7 +825,13 @@ sim_status setup(sim_t* s, const std::vector<HostSheet>& sheets, double dt, cons
     TRY(alloc(s, 3 * state_bytes(s), &s->tmp));
     TRY(alloc(s, (size_t)s->ckpt * state_bytes(s), &s->seg));
   }
-  if (want_direct(s, o)) TRY(setup_direct(s, sheets));
+  if (want_direct(s, o)) {
+    try {
+      TRY(setup_direct(s, sheets));
+    } catch (const std::bad_alloc&) {   // no host memory for the plan: solved iteratively
+      s->dp = DsPlan{};
+    }
+  }
   HIPCHECK(s, hipMemset(s->status, 0, 4 * (ni + 1)));
   HIPCHECK(s, hipMemset(s->it_fwd, 0, st * 4));
   HIPCHECK(s, hipMemset(s->it_rec, 0, st * 4));
