@@ -93,6 +93,10 @@ enum DsCounter {
   kDsHeadDone = 0, kDsSchurDone, kDsPivotDone, kDsForwardDone, kDsBackwardDone, kDsRowsDone
 };
 
+// Words in which a workgroup's consecutive waits hand over their outcomes, in turn.
+constexpr int kDsGoWords = 2;
+constexpr int ds_next_word(int word) { return (word + 1) % kDsGoWords; }
+
 // Elimination plan of all sheets of a handle. Fronts are sorted by level: a front's
 // children are all on lower levels.
 struct DsPlan {

@@ -224,7 +224,7 @@ __device__ __forceinline__ Table<T> table(const T* p) {
 }
 
 struct Shared {
-  int go, bad;
+  int go[kDsGoWords], bad;
   int next[2];     // >= 0: rec holds a task
   DsTask rec[2];   // this task's and the next one's record, in turn
 };
@@ -236,6 +236,7 @@ struct Next {
   int queue;       // the queue this workgroup takes from,
   int base, count; // its first task and their number
   int slot;        // of Shared::rec for the next task
+  int turn;        // of Shared::go for the next wait; the same in every thread
   int number;      // in its queue; -1: the queue is empty, -2: all are
   unsigned long long rec;   // 8 bytes of its record per lane
 };
@@ -256,9 +257,15 @@ __device__ __forceinline__ long long uni(long long v) {
 
 // Waits (bounded) until every lane's counter of wavefront 0 reaches the lane's target (0:
 // nothing to wait for). Every thread calls. 0 when the launch is to end, else 1, or 3 when
-// the counters have also reached `want`. Also a barrier of the workgroup.
-__device__ __forceinline__ int wait_lanes(Table<DsArgs> a, int c, int target, int want,
+// the counters have also reached `want`. Also a barrier of the workgroup. Thread 0 hands the
+// outcome over in two words in turn, for waits may follow each other without another
+// barrier: it writes a word again only past the next wait's barrier, which every
+// wavefront enters after it has read this wait's outcome. With one word a wavefront that
+// reads late would take the next wait's outcome for this one's.
+__device__ __forceinline__ int wait_lanes(Table<DsArgs> a, int c, int target, int want, Next& nx,
                                           Shared& sh) {
+  int& word = sh.go[nx.turn];
+  nx.turn = ds_next_word(nx.turn);
   if (threadIdx.x < 64) {
     int go = 1;
     for (int spins = 0;;) {
@@ -279,20 +286,20 @@ __device__ __forceinline__ int wait_lanes(Table<DsArgs> a, int c, int target, in
         }
       }
     }
-    if (threadIdx.x == 0) sh.go = go;
+    if (threadIdx.x == 0) word = go;
   }
   sync();
-  return uni(sh.go);
+  return uni(word);
 }
 
-__device__ __forceinline__ bool wait_one(Table<DsArgs> a, int c, int target, Shared& sh) {
-  return wait_lanes(a, c, threadIdx.x == 0 ? target : 0, 0, sh) != 0;
+__device__ __forceinline__ bool wait_one(Table<DsArgs> a, int c, int target, Next& nx, Shared& sh) {
+  return wait_lanes(a, c, threadIdx.x == 0 ? target : 0, 0, nx, sh) != 0;
 }
 
 // Waits for the children's counters `which` (and looks whether the counters c2 of lanes 2
 // and up have reached their `want`): as wait_lanes.
 __device__ __forceinline__ int wait_children(Table<DsArgs> a, const DsTask& tk, int which, int c2,
-                                             int want, Shared& sh) {
+                                             int want, Next& nx, Shared& sh) {
   const int lane = thread_id();
   int c = c2, target = 0;
   if (lane < 2) {
@@ -301,7 +308,7 @@ __device__ __forceinline__ int wait_children(Table<DsArgs> a, const DsTask& tk, 
                                                                              : tk.f.kfwd[lane];
   }
   const int nc = uni(tk.f.nc);
-  int go = wait_lanes(a, c, target, lane < 2 ? target : want, sh);
+  int go = wait_lanes(a, c, target, lane < 2 ? target : want, nx, sh);
   for (int base = 2; go && base < nc; base += 64) {   // rare: more than two children
     target = 0;
     if (lane < 64 && base + lane < nc) {
@@ -309,7 +316,7 @@ __device__ __forceinline__ int wait_children(Table<DsArgs> a, const DsTask& tk, 
       c = K.cnt + which;
       target = which == kDsHeadDone ? K.nhead : which == kDsSchurDone ? K.nschur : K.nfwd;
     }
-    go = wait_lanes(a, c, target, 0, sh) ? 1 : 0;
+    go = wait_lanes(a, c, target, 0, nx, sh) ? 1 : 0;
   }
   return go;
 }
@@ -421,7 +428,7 @@ __device__ __forceinline__ bool task_pivot(Table<DsArgs> a, const DsTask& tk, Ne
         lds[(3 * l + c) * kLd + 3 * i + r] = x[3 * r + c];
       }
   }
-  if (!wait_children(a, tk, kDsHeadDone, 0, 0, sh)) return false;
+  if (!wait_children(a, tk, kDsHeadDone, 0, 0, nx, sh)) return false;
   // A lane takes columns lane and lane + 64 of every eighth row (at most 96); the loads of
   // the first two children are all in flight before the first is used.
   constexpr int NR = 3 * kDsMaxPiv / kWaves, N0 = 64 / kWaves, N1 = NR - N0;
@@ -653,7 +660,7 @@ __device__ __forceinline__ bool task_border(Table<DsArgs> a, const DsTask& tk, N
       for (int r = 0; r < 3; ++r) Fl[row * kLd + 3 * i + r] = x[3 * r + c];
     }
   }
-  const int go = wait_children(a, tk, kDsSchurDone, cnt + kDsPivotDone, lane == 2 ? 1 : 0, sh);
+  const int go = wait_children(a, tk, kDsSchurDone, cnt + kDsPivotDone, lane == 2 ? 1 : 0, nx, sh);
   if (!go) return false;
   // a lane takes pivot columns lane and lane + 64 of this wavefront's rows of a child
   auto gather = [&](int ch, const double* S0, int nq, int ld, double (&s0)[NR], double (&s1)[NR]) {
@@ -705,7 +712,7 @@ __device__ __forceinline__ bool task_border(Table<DsArgs> a, const DsTask& tk, N
   sync();
   put_rows(a->ws + uni(tk.f.bo) + (size_t)r0 * np, Fl, rows, np, tid);
   fetch_next(nx);
-  if (go == 1 && !wait_one(a, cnt + kDsPivotDone, 1, sh)) return false;
+  if (go == 1 && !wait_one(a, cnt + kDsPivotDone, 1, nx, sh)) return false;
   const double* X = fac + uni(tk.f.xo);
   double* W = fac + uni(tk.f.wo) + (size_t)r0 * np;
   switch (np / kDsTile) {
@@ -769,7 +776,7 @@ __device__ __forceinline__ bool task_schur(Table<DsArgs> a, const DsTask& tk, Ne
   const int group = lane == 2 ? I : J, rows_cnt = cnt + kDsRowsDone + group;
   const int rows_of = lane == 2 || lane == 3
                           ? min(per, (nb + kDsRowTile - 1) / kDsRowTile - per * group) : 0;
-  const int go = wait_children(a, tk, kDsSchurDone, rows_cnt, rows_of, sh);
+  const int go = wait_children(a, tk, kDsSchurDone, rows_cnt, rows_of, nx, sh);
   if (!go) return false;
   double x[2][8];
 #pragma unroll
@@ -781,7 +788,7 @@ __device__ __forceinline__ bool task_schur(Table<DsArgs> a, const DsTask& tk, Ne
 #pragma unroll
     for (int q = 0; q < 8; ++q) x[ch][q] = load1(S, (int)(rows[4 * q] + c));
   }
-  if (go == 1 && !wait_lanes(a, rows_cnt, rows_of, 0, sh)) return false;
+  if (go == 1 && !wait_lanes(a, rows_cnt, rows_of, 0, nx, sh)) return false;
   // Halves of at most 48 columns, 16, 32 or 48: eight threads a row, up to three 16-byte
   // pieces each; the second half travels during the first's products.
   const __amdgpu_buffer_rsrc_t W = buffer(fac + uni(tk.f.wo), 8 * nb * np);
@@ -866,7 +873,7 @@ __device__ __forceinline__ bool task_forward(Table<DsArgs> a, const DsTask& tk, 
       c = tk.f.kcnt[lane - 1] + kDsForwardDone;
       want = tk.f.kfwd[lane - 1];
     }
-    go = wait_lanes(a, c, target, want, sh);
+    go = wait_lanes(a, c, target, want, nx, sh);
     if (!go) return false;
     if (nc > 2) go = 1;
   }
@@ -881,7 +888,7 @@ __device__ __forceinline__ bool task_forward(Table<DsArgs> a, const DsTask& tk, 
   }
   double v = 0.0;
   if (tid < 3 * p) v = a->rhs[(size_t)(tid % 3) * a->nv + a->tab[tk.f.verts + tid / 3]];
-  if (go == 1 && !wait_children(a, tk, kDsForwardDone, 0, 0, sh)) return false;
+  if (go == 1 && !wait_children(a, tk, kDsForwardDone, 0, 0, nx, sh)) return false;
   double h[NP], e[2];
 #pragma unroll
   for (int ch = 0; ch < 2; ++ch) {
@@ -951,7 +958,7 @@ __device__ __forceinline__ bool task_backward(Table<DsArgs> a, const DsTask& tk,
   if (factor) {   // X and W are complete: the forward pass read all rows of W
     const int cw = lane == 0 ? cnt + kDsPivotDone : lane == 1 ? cnt + kDsForwardDone : last;
     const int target = lane == 0 ? 1 : lane == 1 ? nfwd : 0;
-    go = wait_lanes(a, cw, target, lane == 2 ? nlast : target, sh);
+    go = wait_lanes(a, cw, target, lane == 2 ? nlast : target, nx, sh);
     if (!go) return false;
   }
   const int nb = uni(tk.f.nb);
@@ -974,7 +981,7 @@ __device__ __forceinline__ bool task_backward(Table<DsArgs> a, const DsTask& tk,
   for (int q = 0; q < NX; ++q) {
     if (G * q < np) x[q] = load1(X, at + 8 * G * np * q);
   }
-  if (go == 1 && !wait_one(a, last, nlast, sh)) return false;
+  if (go == 1 && !wait_one(a, last, nlast, nx, sh)) return false;
   // zero on the padding rows, whose W is zero
 #pragma unroll
   for (int q = 0; q < NB; ++q)
@@ -1021,7 +1028,7 @@ __global__ void __launch_bounds__(kThreads, 4) k_ds_run(const DsArgs* __restrict
   }
   extern __shared__ __align__(16) double lds[];
   __shared__ Shared sh;
-  Next nx{tasks, factor, (int)blockIdx.x % kDsQueues, 0, 0, 0, 0, 0};
+  Next nx{tasks, factor, (int)blockIdx.x % kDsQueues, 0, 0, 0, 0, 0, 0};
   find_task(table(args), nx, true, sh);
 #pragma unroll 1
   for (;;) {

@@ -21,6 +21,7 @@ def lib(tmp_path_factory):
     out = str(tmp_path_factory.mktemp("direct") / "libdirect_check.so")
     subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-I" + CSRC,
                     os.path.join(HERE, "host", "direct_check.cpp"),
+                    os.path.join(HERE, "host", "wait_check.cpp"),
                     os.path.join(CSRC, "direct_prep.cpp"), "-o", out], check=True)
     return ctypes.CDLL(out)
 
@@ -115,3 +116,11 @@ def test_plan_solves_the_system(lib, name):
     # backward-stable elimination: eps times the condition number, with room for the
     # explicit pivot inverses
     assert np.abs(x.T.ravel() - ref).max() <= 64 * np.finfo(float).eps * cond * np.abs(ref).max()
+
+
+def test_waits_hand_over_their_own_outcome(lib):
+    """A wavefront may read a wait's outcome late, when wavefront 0 is already through with
+    the next wait: with one word it then reads that one's; with the words the solver uses
+    in turn, never."""
+    assert lib.wait_check(1) > 0
+    assert lib.wait_check(0) == 0
