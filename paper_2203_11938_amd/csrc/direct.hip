@@ -1015,9 +1015,10 @@ __device__ __forceinline__ bool task_backward(Table<DsArgs> a, const DsTask& tk,
 
 // The tables come through a device copy of DsArgs that every task reads anew: as kernel
 // arguments their pointers would stay in scalar registers across the task loop, whose
-// spills then cost vector registers in every task.
+// spills then cost vector registers in every task. (fac is not restrict: what it points to
+// is written by other workgroups during the launch.)
 __global__ void __launch_bounds__(kThreads, 4) k_ds_run(const DsArgs* __restrict__ args,
-                                                        double* __restrict__ fac,
+                                                        double* fac,
                                                         const DsTask* __restrict__ tasks,
                                                         int factor,
                                                         const int* __restrict__ done, int ninst) {
