@@ -177,8 +177,11 @@ typedef struct {
                                is left to the library: rows_per_block, matrix_home,
                                matrix_precision and coarse_size at their defaults,
                                cg_tol >= 1e-12, cg_max_iter not below
-                               min(20000, 3 x the largest sheet's vertices), and at
-                               most 16 GB for one factorisation                         */
+                               min(20000, 3 x the largest sheet's vertices), and, for
+                               all sheets of the handle together, at most 16 GB and half
+                               the device memory free at creation for one factorisation
+                               (else, or where that memory cannot be had, all sheets are
+                               solved iteratively)                                      */
   int32_t checkpoint_every; /* k > 0: keep every k-th state, recompute in the adjoint;
                                0: keep every state                                      */
   double gravity[3];        /* m/s^2                                                    */

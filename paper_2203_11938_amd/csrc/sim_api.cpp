@@ -150,6 +150,8 @@ constexpr double kFactorStoreCap = 32.0 * (1 << 30);
 // memory of the direct solver's workspace and one factor: sheets beyond it are solved
 // iteratively
 constexpr double kDirectWorkCap = 16.0 * (1 << 30);
+// and at most this share of the memory that is free at creation: the rest is the program's
+constexpr double kDirectFreeShare = 0.5;
 // tightest tolerance given to the direct solver
 constexpr double kDirectMinTol = 1e-12;
 // below this tolerance a solve whose residual misses it is corrected once by the solution
@@ -389,6 +391,10 @@ sim_status setup_direct(sim_t* s, const std::vector<HostSheet>& sheets) {
   build_direct_plan(L.nv, L.maxnz, L.ell_col, L.inst_voff, L.inst_nv, rest_internal(s, sheets), P,
                     kDirectWorkCap / 8.0);
   if (!P.ok) return SIM_OK;
+  size_t fre = 0, total = 0;
+  HIPCHECK(s, hipMemGetInfo(&fre, &total));
+  if (8.0 * ((double)P.factor_doubles + (double)P.work_doubles) > kDirectFreeShare * (double)fre)
+    return SIM_E_NOMEM;
   int dev = 0, ncu = 0, per_cu = 0;
   HIPCHECK(s, hipGetDevice(&dev));
   HIPCHECK(s, hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
@@ -448,6 +454,27 @@ sim_status setup_direct(sim_t* s, const std::vector<HostSheet>& sheets) {
   TRY(alloc(s, 4 * (size_t)L.ninst, &q)); o.done = (int*)q;
   s->ds_step.assign(1, 0);
   s->use_direct = true;
+  return SIM_OK;
+}
+
+// Sets the direct solver up, or leaves the handle to the iterative solver, with all memory
+// given back, where host or device memory does not suffice.
+sim_status try_direct(sim_t* s, const std::vector<HostSheet>& sheets) {
+  const size_t held = s->allocs.size(), bytes = s->dev_bytes;
+  sim_status st = SIM_E_NOMEM;
+  try {
+    st = setup_direct(s, sheets);
+  } catch (const std::bad_alloc&) {
+  }
+  if (st != SIM_E_NOMEM) return st;
+  (void)hipGetLastError();
+  s->err.clear();
+  for (size_t k = held; k < s->allocs.size(); ++k) (void)hipFree(s->allocs[k]);
+  s->allocs.resize(held);
+  s->dev_bytes = bytes;
+  s->dp = DsPlan{};
+  s->ds_fac.clear();
+  s->ds_corr = nullptr;
   return SIM_OK;
 }
 
@@ -825,13 +852,6 @@ sim_status setup(sim_t* s, const std::vector<HostSheet>& sheets, double dt, cons
     TRY(alloc(s, 3 * state_bytes(s), &s->tmp));
     TRY(alloc(s, (size_t)s->ckpt * state_bytes(s), &s->seg));
   }
-  if (want_direct(s, o)) {
-    try {
-      TRY(setup_direct(s, sheets));
-    } catch (const std::bad_alloc&) {   // no host memory for the plan: solved iteratively
-      s->dp = DsPlan{};
-    }
-  }
   HIPCHECK(s, hipMemset(s->status, 0, 4 * (ni + 1)));
   HIPCHECK(s, hipMemset(s->it_fwd, 0, st * 4));
   HIPCHECK(s, hipMemset(s->it_rec, 0, st * 4));
@@ -856,6 +876,8 @@ sim_status setup(sim_t* s, const std::vector<HostSheet>& sheets, double dt, cons
     s->stats.autotuned = 1;
   }
   TRY(apply_plan(s, feasible[best]));
+  // last: its memory is optional, what the handle cannot do without comes first
+  if (want_direct(s, o)) TRY(try_direct(s, sheets));
   HIPCHECK(s, hipDeviceSynchronize());
   s->stats.n_instances = L.ninst;
   long nnzb = 0;

@@ -1,0 +1,148 @@
+"""Host side of the C ABI, compiled for the CPU over a device of settable memory whose
+kernels are stood for by one number each (host/fake_gpu.cpp): what a handle allocates and
+when, where it falls back, and which factors and coarse operators its solves are given."""
+
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2203_11938_amd import sim as S, workloads as W
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+CSRC = os.path.join(ROOT, "paper_2203_11938_amd", "csrc")
+COUNTS = ("mallocs", "factorised", "passes", "stale_factors", "coarse", "iterated", "stale_coarse")
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("api") / "libfake_sim.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-w", "-D__HIP_PLATFORM_AMD__",
+                    "-I/opt/rocm/include", "-I" + CSRC, "-I" + os.path.join(ROOT, "include"),
+                    os.path.join(HERE, "host", "fake_gpu.cpp"),
+                    *(os.path.join(CSRC, f) for f in ("sim_api.cpp", "mesh_prep.cpp", "direct_prep.cpp")),
+                    "-Wl,-Bsymbolic", "-o", out], check=True)
+    lib = ctypes.CDLL(out)
+    lib.fake_memory.argtypes = [ctypes.c_size_t]
+    lib.fake_used.restype = ctypes.c_size_t
+    lib.sim_destroy.argtypes = [ctypes.c_void_p]
+    return lib
+
+
+class Handle:
+    """A handle over one n x n sheet, its calls on host arrays of the right sizes."""
+
+    def __init__(self, lib, n, memory=1 << 34, fail=0, **options):
+        self.lib = lib
+        lib.fake_memory(memory)
+        lib.fake_fail(fail)
+        opt = S._Options()
+        lib.sim_default_options(ctypes.byref(opt))
+        opt.precision = S.SIM_FP64
+        for k, v in options.items():
+            setattr(opt, k, v)
+        rest, tris = W.grid_sheet(n)
+        tris = np.ascontiguousarray(tris, np.int32)
+        rest = np.ascontiguousarray(rest, np.float64)
+        mesh = S._Mesh(len(rest), len(tris), tris.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)))
+        mat = S._Material(1e3, 1e-4, 0.1)
+        self.h = ctypes.c_void_p()
+        self.status = lib.sim_create(ctypes.byref(mesh), rest.ctypes.data_as(ctypes.c_void_p), None, 0,
+                                     ctypes.byref(mat), ctypes.c_double(0.01), ctypes.byref(opt),
+                                     ctypes.byref(self.h))
+        lib.fake_fail(0)
+        self.x0 = np.zeros((3, len(rest)))
+        self.created = self.counts()
+
+    def counts(self):
+        c = (ctypes.c_int * 8)()
+        self.lib.fake_counts(c, 1)
+        return dict(zip(COUNTS, c))
+
+    def rollout(self, steps, start, stream=None):
+        self.x0[0, 0] = start
+        st = self.lib.sim_rollout(self.h, steps, self.x0.ctypes.data_as(ctypes.c_void_p), None, None,
+                                  None, None, None, 0, None, stream)
+        assert st == S.SIM_OK
+        return self.counts()
+
+    def adjoint(self, stream=None):
+        assert self.lib.sim_adjoint(self.h, None, None, None, None, None, None, stream) == S.SIM_OK
+        return self.counts()
+
+    def stats(self):
+        s = S._Stats()
+        assert self.lib.sim_sync_status(self.h) == S.SIM_OK
+        assert self.lib.sim_get_stats(self.h, ctypes.byref(s)) == S.SIM_OK
+        return s
+
+    def close(self):
+        if self.h:
+            self.lib.sim_destroy(self.h)
+        self.h = None
+
+
+@pytest.fixture
+def make(lib):
+    made = []
+
+    def make(*a, **kw):
+        made.append(Handle(lib, *a, **kw))
+        return made[-1]
+
+    yield make
+    for h in made:
+        h.close()
+    assert lib.fake_used() == 0
+
+
+ITERATIVE = dict(cg_tol=1e-13)   # below what the direct solver is given; all else the same
+
+
+def iterative_bytes(make, n, **options):
+    h = make(n, **ITERATIVE, **options)
+    assert h.status == S.SIM_OK
+    b = h.stats().device_bytes
+    h.close()
+    return b
+
+
+def test_solves_are_direct_and_the_adjoint_reuses_the_factors(make):
+    h = make(24, max_steps=6)
+    assert h.rollout(6, 10.0)["factorised"] == 6
+    assert h.adjoint()["factorised"] == 6       # the first shows that factors are worth keeping
+    for k in range(2):
+        assert h.rollout(6, 20.0 + 100 * k)["factorised"] == 6
+        c = h.adjoint()
+        assert (c["factorised"], c["passes"], c["stale_factors"], c["iterated"]) == (0, 6, 0, 0)
+
+
+def test_a_handle_without_room_for_the_direct_solver_is_iterative(make):
+    """The direct solver's memory is optional: where an allocation of its set-up fails, the
+    handle is created all the same, gives back what that set-up took, and solves
+    iteratively."""
+    need = iterative_bytes(make, 48, max_steps=4)
+    for spare in (0, 1 << 18, 1 << 20, 4 << 20):
+        h = make(48, memory=need + spare, max_steps=4)
+        assert h.status == S.SIM_OK, spare
+        assert h.stats().device_bytes == need and h.lib.fake_used() == need
+        c = h.rollout(4, 1.0)
+        assert (c["factorised"], c["iterated"]) == (0, 4)
+        h.close()
+    # one allocation after the other of those an iterative handle does not make
+    h = make(48, max_steps=4, **ITERATIVE)
+    first = h.created["mallocs"] + 1
+    h.close()
+    h = make(48, max_steps=4)
+    last = h.created["mallocs"]
+    h.close()
+    assert last > first
+    for nth in range(first, last + 1):
+        h = make(48, fail=nth, max_steps=4)
+        assert h.status == S.SIM_OK, nth
+        assert h.stats().device_bytes == need and h.lib.fake_used() == need
+        assert h.rollout(4, 1.0)["iterated"] == 4
+        h.close()
