@@ -81,6 +81,7 @@ struct sim_s {
   std::vector<double*> ds_fac;            // factors of ds_fac.size() steps, kept between
                                           // forward pass and adjoint; never moved (a graph
                                           // captured by the caller holds their addresses)
+  double ds_room = -1.0;                  // bytes that further factors may take, < 0: not set
   bool ds_grad = false;                   // an adjoint has run: the factors are worth keeping
   std::vector<int> ds_step;               // step held by each slot, 0 = none
   void* A = nullptr;
@@ -145,8 +146,9 @@ constexpr int kCoarseMaxAggs = 320;
 // device memory for coarse operators kept between the forward pass and the adjoint
 constexpr double kCoarseStoreCap = 16.0 * (1 << 30);
 // the same for the direct solver's factors, which are taken from free memory when the
-// first adjoint shows that they are used: at most this, and a fifth of what is free
+// first adjoint shows that they are used: at most this, and a fifth of what is free then
 constexpr double kFactorStoreCap = 32.0 * (1 << 30);
+constexpr double kFactorStoreShare = 0.2;
 // memory of the direct solver's workspace and one factor: sheets beyond it are solved
 // iteratively
 constexpr double kDirectWorkCap = 16.0 * (1 << 30);
@@ -488,13 +490,15 @@ void keep_factors(sim_t* s, int steps, hipStream_t stream) {
   if (want <= have) return;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return;
-  size_t fre = 0, total = 0;
-  if (hipMemGetInfo(&fre, &total) != hipSuccess) return;
   const double bytes = 8.0 * (double)s->dp.factor_doubles;
-  const double room = std::min(kFactorStoreCap - have * bytes, 0.2 * (double)fre);
+  if (s->ds_room < 0.0) {   // the first time: what the handle may take in its life
+    size_t fre = 0, total = 0;
+    if (hipMemGetInfo(&fre, &total) != hipSuccess) return;
+    s->ds_room = std::min(kFactorStoreCap - have * bytes, kFactorStoreShare * (double)fre);
+  }
   // growing windows ask again and again: at least double what is held
   int n = std::min(std::max(want, 2 * have), s->ckpt > 0 ? want : s->max_steps) - have;
-  n = (int)std::min((double)n, room / bytes);
+  n = (int)std::min((double)n, s->ds_room / bytes);
   if (n <= 0) return;
   // relaxed: a capture that another thread or stream runs is not disturbed
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
@@ -504,8 +508,10 @@ void keep_factors(sim_t* s, int steps, hipStream_t stream) {
   (void)hipThreadExchangeStreamCaptureMode(&mode);
   if (e != hipSuccess) {
     (void)hipGetLastError();
+    s->ds_room = 0.0;   // not asked for again
     return;
   }
+  s->ds_room -= (double)n * bytes;
   s->allocs.push_back(q);
   s->dev_bytes += (size_t)n * (size_t)bytes;
   for (int k = 0; k < n; ++k)

@@ -146,3 +146,34 @@ def test_a_handle_without_room_for_the_direct_solver_is_iterative(make):
         assert h.stats().device_bytes == need and h.lib.fake_used() == need
         assert h.rollout(4, 1.0)["iterated"] == 4
         h.close()
+
+
+def test_kept_factors_stay_within_a_fifth_of_the_memory_free_at_the_first_adjoint(make):
+    """The bound holds over the handle's life, and calls in the steady state allocate
+    nothing: a handle that does not get a slot per step does not ask again."""
+    h = make(24, max_steps=60)
+    room = h.lib.fake_used() + 5 * 20 * 330000   # a fifth: some 20 factors of this sheet
+    h.lib.fake_memory(room)
+    held = h.stats().device_bytes
+    fifth = (room - h.lib.fake_used()) / 5
+    h.rollout(60, 1.0)
+    first = h.adjoint()
+    got = h.stats().device_bytes - held
+    assert 0 < got <= fifth
+    for k in range(6):
+        a, b = h.rollout(60, 100.0 * k), h.adjoint()
+        assert h.stats().device_bytes - held == got
+        assert a["mallocs"] == 0 and b["mallocs"] == 0
+        assert b["stale_factors"] == 0 and b["iterated"] == 0
+        assert 0 < b["passes"] < 60
+
+
+def test_kept_factors_follow_growing_windows(make):
+    """A program that lengthens its rollouts gets a slot per step as long as they fit."""
+    h = make(24, max_steps=64)
+    for n in range(1, 65):
+        h.rollout(n, 1000.0 * n)
+        h.adjoint()
+    assert h.rollout(64, 5.0)["factorised"] == 64
+    c = h.adjoint()
+    assert (c["factorised"], c["passes"], c["mallocs"]) == (0, 64, 0)
