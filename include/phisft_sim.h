@@ -225,11 +225,14 @@ typedef struct {
   double air_density;       /* rho_air [kg/m^3] of the aerodynamic force (default 1, the
                                value the paper fixes, Sec. 3.4); it acts only in
                                rollouts given a wind velocity                           */
-  int32_t coarse_keep_all;  /* with checkpointing: 0 (default) keeps the coarse
+  int32_t coarse_keep_all;  /* with checkpointing: 0 (default) keeps the solver's
                                operators of one checkpoint segment (device memory
                                bounded by checkpoint_every; recomputed steps rebuild
-                               theirs), 1 keeps every step's when they fit 16 GB (the
-                               recompute then reuses the forward's: faster, more memory) */
+                               theirs), 1 keeps every step's (the recompute then reuses
+                               the forward's: faster, more memory): coarse operators
+                               when they fit 16 GB; factors, of handles solved
+                               directly, as many as fit 32 GB and a fifth of the memory
+                               free at creation                                        */
   int32_t material_model;   /* sim_material_model (default SIM_MATERIAL_ISOTROPIC): sets
                                the material arrays' n_mat (3 or SIM_WANG_PARAMS)        */
 } sim_options;
@@ -265,8 +268,9 @@ typedef struct {
   int64_t graph_replays;      /* calls served by replaying a captured graph */
   int64_t device_bytes;       /* device memory the handle holds (workspace, trajectory or
                                  checkpoints, kept coarse operators, tables; after the
-                                 first adjoint also kept factors, at most 32 GB and at
-                                 most a fifth of the memory then free) */
+                                 first adjoint, or with coarse_keep_all from the start,
+                                 also kept factors, at most 32 GB and at most a fifth of
+                                 the memory then free) */
   int32_t coarse_store_slots; /* steps whose coarse operators are kept for the adjoint */
   int32_t material_params;    /* n_mat of the material arrays (3 or SIM_WANG_PARAMS) */
   int32_t solver_row_teams;   /* 2: register-resident rows split over two wavefront teams
@@ -276,7 +280,7 @@ typedef struct {
 /* Fills *opt with the defaults: FP32 arrays, cg_tol 1e-7, cg_max_iter 20000,
  * store every state, gravity (0,0,-9.81), max_steps 1000, tuned rows per block,
  * exact membrane Hessian, FP64 system matrix, aggregates of 64 vertices, air
- * density 1 kg/m^3, coarse operators of one checkpoint segment kept, isotropic
+ * density 1 kg/m^3, the solver's operators of one checkpoint segment kept, isotropic
  * material. */
 void sim_default_options(sim_options* opt);
 

@@ -480,24 +480,19 @@ sim_status try_direct(sim_t* s, const std::vector<HostSheet>& sheets) {
   return SIM_OK;
 }
 
-// Room for the factors of up to `steps` steps once the handle is used for gradients. The
-// slots held stay where they are; nothing is allocated while the caller's stream is being
-// captured; without room the adjoint factorises again.
-void keep_factors(sim_t* s, int steps, hipStream_t stream) {
-  if (!s->use_direct || !s->ds_grad) return;
+// Takes memory for the factors of up to `want` steps, or of as many as the handle's room
+// holds; of up to `most` where that saves asking again soon. The slots held stay where
+// they are.
+void reserve_factors(sim_t* s, int want, int most) {
   const int have = (int)s->ds_fac.size();
-  const int want = std::min(s->ckpt > 0 ? s->ckpt : steps, s->max_steps);
   if (want <= have) return;
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return;
   const double bytes = 8.0 * (double)s->dp.factor_doubles;
   if (s->ds_room < 0.0) {   // the first time: what the handle may take in its life
     size_t fre = 0, total = 0;
     if (hipMemGetInfo(&fre, &total) != hipSuccess) return;
     s->ds_room = std::min(kFactorStoreCap - have * bytes, kFactorStoreShare * (double)fre);
   }
-  // growing windows ask again and again: at least double what is held
-  int n = std::min(std::max(want, 2 * have), s->ckpt > 0 ? want : s->max_steps) - have;
+  int n = std::min(std::max(want, 2 * have), most) - have;
   n = (int)std::min((double)n, s->ds_room / bytes);
   if (n <= 0) return;
   // relaxed: a capture that another thread or stream runs is not disturbed
@@ -517,6 +512,22 @@ void keep_factors(sim_t* s, int steps, hipStream_t stream) {
   for (int k = 0; k < n; ++k)
     s->ds_fac.push_back(static_cast<double*>(q) + (size_t)k * s->dp.factor_doubles);
   s->ds_step.assign(s->ds_fac.size(), 0);
+}
+
+// Steps whose solver operators (factors or coarse operators) the options ask to keep
+// for the adjoint of a rollout of `steps` steps: all, or with checkpointing those of one
+// segment unless coarse_keep_all.
+int kept_steps(const sim_t* s, int steps) {
+  return s->ckpt > 0 && !s->coarse_keep_all ? std::min(s->ckpt, s->max_steps) : steps;
+}
+
+// Room for the factors once the handle is used for gradients. Nothing is allocated while
+// the caller's stream is being captured; without room the adjoint factorises again.
+void keep_factors(sim_t* s, int steps, hipStream_t stream) {
+  if (!s->use_direct || !s->ds_grad || kept_steps(s, steps) <= (int)s->ds_fac.size()) return;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return;
+  reserve_factors(s, kept_steps(s, steps), kept_steps(s, s->max_steps));
 }
 
 sim_status setup(sim_t* s, const std::vector<HostSheet>& sheets, double dt, const sim_options* opt) {
@@ -884,6 +895,9 @@ sim_status setup(sim_t* s, const std::vector<HostSheet>& sheets, double dt, cons
   TRY(apply_plan(s, feasible[best]));
   // last: its memory is optional, what the handle cannot do without comes first
   if (want_direct(s, o)) TRY(try_direct(s, sheets));
+  // asked for: every step's factor from the start
+  if (s->use_direct && s->ckpt > 0 && s->coarse_keep_all)
+    reserve_factors(s, s->max_steps, s->max_steps);
   HIPCHECK(s, hipDeviceSynchronize());
   s->stats.n_instances = L.ninst;
   long nnzb = 0;

@@ -177,3 +177,42 @@ def test_kept_factors_follow_growing_windows(make):
     assert h.rollout(64, 5.0)["factorised"] == 64
     c = h.adjoint()
     assert (c["factorised"], c["passes"], c["mallocs"]) == (0, 64, 0)
+
+
+@pytest.mark.parametrize("keep_all", [0, 1])
+def test_checkpointed_adjoint_reuses_what_the_option_keeps(make, keep_all):
+    """By default the factors of one segment are kept: the recompute factorises the other
+    segments' steps again, the adjoint reuses those. With coarse_keep_all every step's are:
+    nothing after the forward pass factorises, from the first adjoint on."""
+    h = make(24, max_steps=20, checkpoint_every=5, coarse_keep_all=keep_all)
+    for k in range(3):
+        assert h.rollout(20, 100.0 * k)["factorised"] == 20
+        c = h.adjoint()
+        assert c["stale_factors"] == 0 and c["iterated"] == 0
+        if keep_all:
+            assert (c["factorised"], c["passes"]) == (0, 36)
+        elif k > 0:
+            # the last segment's are all kept; of the others the ends are not recomputed
+            assert (c["factorised"], c["passes"]) == (15, 21)
+
+
+def test_keep_all_keeps_what_fits(make):
+    """Where not every step's factor fits, the recompute still reuses the last ones'."""
+    h = make(24, max_steps=20, checkpoint_every=5)
+    few = h.stats().device_bytes
+    h.rollout(20, 1.0)
+    h.adjoint()
+    factor = (h.stats().device_bytes - few) // 4
+    h.close()
+    h = make(24, max_steps=20, checkpoint_every=5, coarse_keep_all=1)
+    rest = h.stats().device_bytes - 19 * factor
+    h.close()
+    # a fifth of what is free holds 11 more
+    h = make(24, memory=rest + 5 * 11 * factor + 64, max_steps=20, checkpoint_every=5, coarse_keep_all=1)
+    assert h.stats().device_bytes == rest + 11 * factor
+    h.rollout(20, 1.0)
+    c = h.adjoint()
+    # steps 9 to 20 are kept: 1 to 4 and 6 to 8 are recomputed, with 5 and the adjoint's own
+    # reuse of those left
+    assert 0 < c["factorised"] < 15 and c["factorised"] + c["passes"] == 36
+    assert c["stale_factors"] == 0 and c["iterated"] == 0 and c["mallocs"] == 0
