@@ -206,7 +206,8 @@ typedef struct {
                                operators (FP32 A_c^-1, offsets, 6x6 blocks) are kept
                                for the adjoint: without checkpointing for every step
                                when that fits 16 GB, else not at all (rebuilt in the
-                               adjoint); with checkpointing see coarse_keep_all       */
+                               adjoint); with checkpointing see coarse_keep_all;
+                               handles solved directly keep factors instead           */
   int32_t autotune;         /* 1: sim_create times every feasible solver launch shape
                                (rows per workgroup; matrix rows in registers, on one or
                                two wavefront teams, in LDS or streamed; rows of the
@@ -271,7 +272,10 @@ typedef struct {
                                  first adjoint, or with coarse_keep_all from the start,
                                  also kept factors, at most 32 GB and at most a fifth of
                                  the memory then free) */
-  int32_t coarse_store_slots; /* steps whose coarse operators are kept for the adjoint */
+  int32_t coarse_store_slots; /* steps whose coarse operators are kept for the adjoint; of a
+                                 handle solved directly, steps whose factors are asked to
+                                 be (as many are held as fit, from the first adjoint on:
+                                 see device_bytes) */
   int32_t material_params;    /* n_mat of the material arrays (3 or SIM_WANG_PARAMS) */
   int32_t solver_row_teams;   /* 2: register-resident rows split over two wavefront teams
                                  (workgroups of at most 128 rows), else 1 */

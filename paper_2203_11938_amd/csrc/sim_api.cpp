@@ -530,6 +530,30 @@ void keep_factors(sim_t* s, int steps, hipStream_t stream) {
   reserve_factors(s, kept_steps(s, steps), kept_steps(s, s->max_steps));
 }
 
+// Store of the coarse operators of iterative handles, where they fit the cap: store-all,
+// one slot per step (the adjoint reuses the forward's operators). With checkpointing, one
+// per step of a checkpoint segment (memory bounded by the interval; the recomputed steps
+// rebuild theirs, the adjoint reuses those), or, with coarse_keep_all, one per step when
+// they fit (the recompute reuses the forward's too). Else none (every step rebuilds).
+sim_status setup_coarse_store(sim_t* s) {
+  const HostLayout& L = s->L;
+  const size_t nv = L.nv, ni = L.ninst;
+  const double slot_bytes =
+      4.0 * (double)L.coarse_doubles + 8.0 * (6.0 * nv + 36.0 * L.nmid) + 4.0 * ni;
+  int want = kept_steps(s, s->max_steps);
+  if (s->ckpt > 0 && want * slot_bytes > kCoarseStoreCap) want = std::min(s->ckpt, s->max_steps);
+  if (want * slot_bytes > kCoarseStoreCap) return SIM_OK;
+  void* q = nullptr;
+  s->cslots = want;
+  TRY(alloc(s, (size_t)want * L.coarse_doubles * 4, &q)); s->cmat_store = (float*)q;
+  TRY(alloc(s, (size_t)want * 3 * nv * 8, &q)); s->crel_store = (double*)q;
+  TRY(alloc(s, (size_t)want * ni * 4, &q)); s->cok_store = (int*)q;
+  TRY(alloc(s, (size_t)want * 3 * nv * 8, &q)); s->mrel_store = (double*)q;
+  TRY(alloc(s, (size_t)want * L.nmid * 36 * 8, &q)); s->minv_store = (double*)q;
+  s->slot_step.assign(want, 0);
+  return SIM_OK;
+}
+
 sim_status setup(sim_t* s, const std::vector<HostSheet>& sheets, double dt, const sim_options* opt) {
   sim_options o;
   sim_default_options(&o);
@@ -834,25 +858,6 @@ sim_status setup(sim_t* s, const std::vector<HostSheet>& sheets, double dt, cons
     TRY(alloc(s, 4 * ni, &q)); cs.ok = (int*)q;
     TRY(alloc(s, 3 * nv * 8, &q)); cs.mid_crel = (double*)q;
     TRY(alloc(s, (size_t)L.nmid * 36 * 8, &q)); cs.mid_inv = (double*)q;
-    // Store-all: one slot per step when they fit the cap (the adjoint reuses the
-    // forward's operators). With checkpointing: one per step of a checkpoint segment
-    // (memory bounded by the interval; the recomputed steps rebuild theirs, the adjoint
-    // reuses those), or, with coarse_keep_all, one per step when they fit (the
-    // recompute reuses the forward's too). Else none (every step rebuilds).
-    const double slot_bytes =
-        4.0 * (double)L.coarse_doubles + 8.0 * (6.0 * nv + 36.0 * L.nmid) + 4.0 * ni;
-    int want = s->max_steps;
-    if (s->ckpt > 0 && (!s->coarse_keep_all || want * slot_bytes > kCoarseStoreCap))
-      want = std::min(s->ckpt, s->max_steps);
-    if (want * slot_bytes <= kCoarseStoreCap) {
-      s->cslots = want;
-      TRY(alloc(s, (size_t)want * L.coarse_doubles * 4, &q)); s->cmat_store = (float*)q;
-      TRY(alloc(s, (size_t)want * 3 * nv * 8, &q)); s->crel_store = (double*)q;
-      TRY(alloc(s, (size_t)want * ni * 4, &q)); s->cok_store = (int*)q;
-      TRY(alloc(s, (size_t)want * 3 * nv * 8, &q)); s->mrel_store = (double*)q;
-      TRY(alloc(s, (size_t)want * L.nmid * 36 * 8, &q)); s->minv_store = (double*)q;
-      s->slot_step.assign(want, 0);
-    }
   }
   TRY(alloc(s, 4 * (ni + 1), &q)); s->status = (int*)q;
   const size_t st = (size_t)s->max_steps * ni;
@@ -898,6 +903,7 @@ sim_status setup(sim_t* s, const std::vector<HostSheet>& sheets, double dt, cons
   // asked for: every step's factor from the start
   if (s->use_direct && s->ckpt > 0 && s->coarse_keep_all)
     reserve_factors(s, s->max_steps, s->max_steps);
+  if (!s->use_direct && coarse) TRY(setup_coarse_store(s));
   HIPCHECK(s, hipDeviceSynchronize());
   s->stats.n_instances = L.ninst;
   long nnzb = 0;
@@ -905,7 +911,7 @@ sim_status setup(sim_t* s, const std::vector<HostSheet>& sheets, double dt, cons
   s->stats.nnz_blocks = nnzb;
   s->stats.coarse_aggregates = L.nagg;
   s->stats.coarse_max_dim = L.max_nc;
-  s->stats.coarse_store_slots = s->cslots;
+  s->stats.coarse_store_slots = s->use_direct ? kept_steps(s, s->max_steps) : s->cslots;
   return SIM_OK;
 }
 

@@ -216,3 +216,26 @@ def test_keep_all_keeps_what_fits(make):
     # reuse of those left
     assert 0 < c["factorised"] < 15 and c["factorised"] + c["passes"] == 36
     assert c["stale_factors"] == 0 and c["iterated"] == 0 and c["mallocs"] == 0
+
+
+@pytest.mark.parametrize("checkpoint", [0, 10])
+def test_direct_handles_hold_no_coarse_operators_of_steps(make, checkpoint):
+    """The kept coarse operators belong to the iterative solver: a handle solved directly
+    takes no memory for them, and its capacity costs a state and statistics a step; one
+    left to the iterative solver for want of memory keeps them."""
+    V = 48 * 48
+    held = {}
+    for steps in (100, 200):
+        h = make(48, max_steps=steps, checkpoint_every=checkpoint)
+        held[steps] = h.stats().device_bytes
+        assert h.stats().coarse_store_slots == (checkpoint or steps)
+        h.close()
+    states = 10 if checkpoint else 100
+    assert held[200] - held[100] <= states * 48 * V + 100 * 36
+    need = iterative_bytes(make, 48, max_steps=100, checkpoint_every=checkpoint)
+    h = make(48, memory=need, max_steps=100, checkpoint_every=checkpoint)
+    assert h.stats().coarse_store_slots == (checkpoint or 100)
+    h.rollout(100, 1.0)
+    c = h.adjoint()
+    assert c["iterated"] > 0 and c["stale_coarse"] == 0
+    assert c["coarse"] == (90 if checkpoint else 0)   # the rest is kept
