@@ -84,6 +84,11 @@ struct sim_s {
   double ds_room = -1.0;                  // bytes that further factors may take, < 0: not set
   bool ds_grad = false;                   // an adjoint has run: the factors are worth keeping
   std::vector<int> ds_step;               // step held by each slot, 0 = none
+  // slot_step and ds_step say what the calls leave behind in the order they are made. That
+  // does not hold for calls that the caller captures and replays: capture of the last call
+  // (0: made directly), and whether there has been one
+  unsigned long long capture = 0;
+  bool captured = false;
   void* A = nullptr;
   void* Jinv = nullptr;
   double* rhs = nullptr;
@@ -521,12 +526,30 @@ int kept_steps(const sim_t* s, int steps) {
   return s->ckpt > 0 && !s->coarse_keep_all ? std::min(s->ckpt, s->max_steps) : steps;
 }
 
+// The capture that the stream's work goes to, 0: none.
+unsigned long long capture_of(hipStream_t stream) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  unsigned long long id = 0;
+  if (!stream || hipStreamGetCaptureInfo(stream, &st, &id) != hipSuccess) return 0;
+  return st == hipStreamCaptureStatusNone ? 0 : id;
+}
+
+// Whether the slots hold what slot_step and ds_step say when this call's work runs: the
+// call before was made directly too and no graph of the caller's can have come between,
+// or both are part of one capture. Also notes this call.
+bool slots_known(sim_t* s, hipStream_t stream) {
+  const unsigned long long id = capture_of(stream);
+  const bool known = id == s->capture && (id != 0 || !s->captured);
+  s->capture = id;
+  s->captured = s->captured || id != 0;
+  return known;
+}
+
 // Room for the factors once the handle is used for gradients. Nothing is allocated while
 // the caller's stream is being captured; without room the adjoint factorises again.
 void keep_factors(sim_t* s, int steps, hipStream_t stream) {
   if (!s->use_direct || !s->ds_grad || kept_steps(s, steps) <= (int)s->ds_fac.size()) return;
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return;
+  if (capture_of(stream) != 0) return;
   reserve_factors(s, kept_steps(s, steps), kept_steps(s, s->max_steps));
 }
 
@@ -1239,6 +1262,7 @@ sim_status begin_rollout(sim_t* s, int n_steps, const void* x0, const void* forc
   s->material = material ? static_cast<const double*>(material) : s->mat_default;
   s->wind = static_cast<const double*>(wind);
   s->stream = static_cast<hipStream_t>(stream);
+  (void)slots_known(s, s->stream);   // the rollout forms every step's operators itself
   return SIM_OK;
 }
 
@@ -1424,10 +1448,18 @@ sim_status sim_adjoint(sim_t* s, const void* dl_dx, void* dl_dmaterial, void* dl
     s->ds_grad = true;
     keep_factors(s, s->n_steps, s->stream);
   }
-  // the adjoint reads the rollout's states, forces and material: its key includes them
+  if (!slots_known(s, s->stream)) {
+    std::fill(s->slot_step.begin(), s->slot_step.end(), 0);
+    std::fill(s->ds_step.begin(), s->ds_step.end(), 0);
+  }
+  // the adjoint reads the rollout's states, forces and material: its key includes them.
+  // It also has per step whether the step's operators are formed or taken from a slot, so
+  // what the slots hold at its start belongs to the key
   std::vector<uintptr_t> key = {(uintptr_t)dl_dx, (uintptr_t)dl_dmaterial, (uintptr_t)dl_dwind,
                                 (uintptr_t)dl_dforces, (uintptr_t)dl_dx0, (uintptr_t)dl_dv0,
                                 s->ds_fac.size()};
+  key.insert(key.end(), s->slot_step.begin(), s->slot_step.end());
+  key.insert(key.end(), s->ds_step.begin(), s->ds_step.end());
   key.insert(key.end(), s->gfwd.key.begin(), s->gfwd.key.end());
   s->have_adjoint = true;
   return graphed(s, s->gadj, key, s->stream, [&](hipStream_t q) {

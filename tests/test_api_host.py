@@ -239,3 +239,68 @@ def test_direct_handles_hold_no_coarse_operators_of_steps(make, checkpoint):
     c = h.adjoint()
     assert c["iterated"] > 0 and c["stale_coarse"] == 0
     assert c["coarse"] == (90 if checkpoint else 0)   # the rest is kept
+
+
+@pytest.mark.parametrize("options", [dict(), ITERATIVE])
+def test_a_replayed_adjoint_uses_operators_of_its_own_steps(make, options):
+    """A captured adjoint holds, per step, whether it forms the step's factor (or coarse
+    operator) or takes the one kept. With checkpointing it leaves others behind than it
+    found, so a second call after the same rollout is another sequence, not a replay."""
+    h = make(24, max_steps=20, checkpoint_every=5, graph=1, **options)
+    for k in range(4):
+        h.rollout(20, 100.0 * k)
+        for call in range(3):
+            c = h.adjoint()
+            assert (c["stale_factors"], c["stale_coarse"]) == (0, 0), (k, call)
+            assert options or c["iterated"] == 0
+    # each kind of call is replayed when it comes again
+    assert h.stats().graph_replays >= 3
+
+
+@pytest.mark.parametrize("checkpoint", [0, 5])
+def test_captures_of_the_caller(lib, make, checkpoint):
+    """Rollout and adjoint in a graph of the caller's, together and each alone beside direct
+    calls: no solve is given another state's factor."""
+    def captured(h, *calls):
+        st = ctypes.c_void_p(id(h) & 0xfffffff0)
+        g, e = ctypes.c_void_p(), ctypes.c_void_p()
+        lib.hipStreamBeginCapture(st, 0)
+        for f in calls:
+            f(st)
+        lib.hipStreamEndCapture(st, ctypes.byref(g))
+        lib.hipGraphInstantiate(ctypes.byref(e), g, None, None, ctypes.c_size_t(0))
+
+        def replay():
+            lib.hipGraphLaunch(e, None)
+            return h.counts()
+        return replay
+
+    def sound(c):
+        assert c["stale_factors"] == 0 and c["iterated"] == 0
+        return c
+
+    h = make(24, max_steps=20, checkpoint_every=checkpoint)
+    h.rollout(20, 1.0)
+    sound(h.adjoint())
+    both = captured(h, lambda st: h.rollout(20, 0.0, st), lambda st: h.adjoint(st))
+    for k in range(3):
+        h.x0[0, 0] = 10.0 + 50 * k
+        c = sound(both())
+        assert c["passes"] > 0        # the adjoint reuses what the rollout formed
+    # a captured rollout, direct adjoints
+    roll = captured(h, lambda st: h.rollout(20, 0.0, st))
+    for k in range(3):
+        h.x0[0, 0] = 1000.0 + 50 * k
+        sound(roll())
+        sound(h.adjoint())
+        sound(h.adjoint())
+    # direct rollouts, a captured adjoint
+    h.rollout(20, 2000.0)
+    adj = captured(h, lambda st: h.adjoint(st))
+    for k in range(3):
+        h.rollout(20, 3000.0 + 50 * k)
+        sound(adj())
+        sound(adj())
+    # back to direct calls
+    h.rollout(20, 4000.0)
+    sound(h.adjoint())
