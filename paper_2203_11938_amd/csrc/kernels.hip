@@ -838,25 +838,21 @@ __global__ void __launch_bounds__(256) k_zero_ranges(ZeroRanges z) {
 
 // First launch of a step's coarse operators. Blocks [0, nframe), one wavefront per
 // aggregate: centroid of the free vertices at x and the offsets x_i - c of its members
-// (zero on pinned members and where rotations are unused). The other blocks set the
-// matrices to zero, with a unit diagonal on the unused modes of every aggregate and the
-// padding rows of every sheet, the sheets' success flags, the sweep's flags and the
-// solver's arrays. (Launches that find every sheet solved directly are paid for all the
+// (zero on pinned members and where rotations are unused). The other blocks clear the
+// matrices, the sweep's flags and the solver's arrays and set the sheets' success flags. (Launches that find every sheet solved directly are paid for all the
 // same, 3 us each; eight a solve before the launches of this kind were merged, now four.)
 __global__ void __launch_bounds__(256) k_coarse_prepare(Mesh m, Coarse c, const double* __restrict__ x,
-                                                        int nframe, ZeroRanges z) {
+                                                        int nframe, long coarse_doubles,
+                                                        ZeroRanges z) {
   if ((int)blockIdx.x >= nframe) {
     if (all_done(c.done, m.ninst)) return;
     const int k0 = ((int)blockIdx.x - nframe) * 256 + threadIdx.x;
     const int stride = ((int)gridDim.x - nframe) * 256;
     zero_ranges(z, k0, stride);
     for (int k = k0; k < m.ninst * c.sw_stride; k += stride) c.sw_sync[k] = 0;
-    for (int b = 0; b < m.ninst; ++b) {
-      const int np = c.inst_np[b];
-      double* M = c.mat + c.inst_coff[b];
-      if (k0 == 0) c.ok[b] = 1;
-      for (long k = k0; k < (long)np * np; k += stride) M[k] = 0.0;
-    }
+    // all sheets' matrices at once: sheet by sheet 2048 sheets of 8x8 took 0.38 ms longer
+    for (long k = k0; k < coarse_doubles; k += stride) c.mat[k] = 0.0;
+    for (int b = k0; b < m.ninst; b += stride) c.ok[b] = 1;
     return;
   }
   const int a = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63, nv = m.nv;
@@ -3541,7 +3537,7 @@ bool launch_coarse_setup(const Mesh& m, const SolverWork& w, const Coarse& c, co
   const int nframe = blocks_for(c.nagg, 4);
   const int nclear = std::min(blocks_for(coarse_doubles, 256), 1024);
   hipLaunchKernelGGL(k_coarse_prepare, dim3(nframe + nclear), dim3(256), 0, st, m, c, x, nframe,
-                     solver_ranges(m, w, true, c.done));
+                     (long)coarse_doubles, solver_ranges(m, w, true, c.done));
   hipLaunchKernelGGL((k_coarse_operators<TM>),
                      dim3(c.npair + blocks_for(c.nmid, 4) + blocks_for(m.ninst, 4)), dim3(256), 0,
                      st, m, c, x, A);
