@@ -1021,11 +1021,11 @@ __global__ void __launch_bounds__(kThreads, 4) k_ds_run(const DsArgs* __restrict
                                                         double* fac,
                                                         const DsTask* __restrict__ tasks,
                                                         int factor,
-                                                        const int* __restrict__ done, int ninst) {
-  if (done) {   // a correction: nothing to do when every sheet is solved
-    int n = 0;
-    for (int b = 0; b < ninst; ++b) n += done[b];
-    if (n == ninst) return;
+                                                        const int* __restrict__ left) {
+  if (left) {   // a correction: nothing to do when every sheet is solved
+    if (*left == 0) return;
+  } else if (blockIdx.x == 0 && threadIdx.x < 2) {
+    args->left[threadIdx.x] = 0;
   }
   extern __shared__ __align__(16) double lds[];
   __shared__ Shared sh;
@@ -1138,6 +1138,7 @@ __global__ void __launch_bounds__(256) k_ds_resid(DsArgs a, DsAccept o,
   __hip_atomic_store(o.arrived + inst, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const bool ok = isfinite(bb) && rr <= o.tol * o.tol * bb;   // NaN: false
   o.done[inst] = ok ? 1 : 0;
+  if (!ok) __hip_atomic_fetch_add(o.left, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (ok) {
     if (o.iters) o.iters[inst] = bb > 0.0 ? 1 : 0;
     if (o.resid) o.resid[inst] = bb > 0.0 ? sqrt(rr / bb) : 0.0;
@@ -1156,9 +1157,9 @@ hipError_t ds_prepare(int* blocks_per_cu) {
 }
 
 void launch_ds_run(const DsArgs* args, double* fac, const DsTask* tasks, int ntasks, bool factor,
-                   int grid, const int* done, int ninst, hipStream_t st) {
+                   int grid, const int* left, hipStream_t st) {
   hipLaunchKernelGGL(k_ds_run, dim3(std::min(grid, ntasks)), dim3(kThreads), kLds * sizeof(double),
-                     st, args, fac, tasks, factor ? 1 : 0, done, ninst);
+                     st, args, fac, tasks, factor ? 1 : 0, left);
 }
 
 void launch_ds_add(const DsArgs& a, const DsAccept& o, const double* dx, const int* vert_inst,

@@ -20,6 +20,7 @@ struct DsArgs {
   int* count;          // counters, queue and abort flag; zero before a launch
   int* queue;          // [kDsQueues] heads, kDsLine ints apart
   int* abort_flag;
+  int* left;           // [2] set to zero by a launch that is not a correction
   int q0[2][kDsQueues + 1];   // the queues' tasks in the lists: passes alone, factorisation
 };
 
@@ -38,6 +39,7 @@ struct DsAccept {
   int* arrived;           // [sheets], zero between launches
   int clear_ints;         // ints from DsArgs::count
   int* done;              // [sheets]
+  int* left;              // counts the sheets not accepted; zero before
   double* res;            // [3][nv] receives b - A x, or nullptr
   int again;              // 1: leave the sheets accepted before alone
   int* iters;             // [sheets] or nullptr
@@ -47,9 +49,9 @@ struct DsAccept {
 hipError_t ds_prepare(int* blocks_per_cu);
 // Runs a list of ntasks tasks, queue after queue, on at most `grid` workgroups; args:
 // device copy of DsArgs; fac: X and W of every front; factor: the list factorises. With
-// `done` ([ninst]) nothing runs when every sheet is marked.
+// `left` it is a correction: nothing runs when that word is zero.
 void launch_ds_run(const DsArgs* args, double* fac, const DsTask* tasks, int ntasks, bool factor,
-                   int grid, const int* done, int ninst, hipStream_t st);
+                   int grid, const int* left, hipStream_t st);
 void launch_ds_add(const DsArgs& a, const DsAccept& o, const double* dx, const int* vert_inst,
                    hipStream_t st);
 void launch_ds_resid(const DsArgs& a, const DsAccept& o, const DsRows* tasks, int ntasks,

@@ -36,6 +36,7 @@ struct PcgArgs {
   double* resid;       // [ninst] or nullptr
   int* status;
   const int* done;     // [ninst] 1: the sheet is solved already and left alone; or nullptr
+  const int* left;     // with done: the number of sheets that are not
 };
 
 template <typename T>

@@ -813,17 +813,10 @@ __global__ void __launch_bounds__(256) k_assemble(Mesh m, Elem el, AssembleArgs<
 struct ZeroRanges {
   int* p[4];
   int n[4];
-  const int* done;   // with it: nothing to do when every sheet is solved
-  int ninst;
+  const int* left;   // number of sheets not solved yet, with 0 nothing to do; or nullptr
 };
 
-// Whether every sheet is marked (done may be nullptr: none is).
-__device__ __forceinline__ bool all_done(const int* done, int ninst) {
-  if (!done) return false;
-  int n = 0;
-  for (int b = 0; b < ninst; ++b) n += done[b];
-  return n == ninst;
-}
+__device__ __forceinline__ bool none_left(const int* left) { return left && *left == 0; }
 
 __device__ __forceinline__ void zero_ranges(const ZeroRanges& z, int k0, int stride) {
 #pragma unroll
@@ -832,7 +825,7 @@ __device__ __forceinline__ void zero_ranges(const ZeroRanges& z, int k0, int str
 }
 
 __global__ void __launch_bounds__(256) k_zero_ranges(ZeroRanges z) {
-  if (all_done(z.done, z.ninst)) return;
+  if (none_left(z.left)) return;
   zero_ranges(z, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
 }
 
@@ -845,7 +838,7 @@ __global__ void __launch_bounds__(256) k_coarse_prepare(Mesh m, Coarse c, const 
                                                         int nframe, long coarse_doubles,
                                                         ZeroRanges z) {
   if ((int)blockIdx.x >= nframe) {
-    if (all_done(c.done, m.ninst)) return;
+    if (none_left(c.left)) return;
     const int k0 = ((int)blockIdx.x - nframe) * 256 + threadIdx.x;
     const int stride = ((int)gridDim.x - nframe) * 256;
     zero_ranges(z, k0, stride);
@@ -3469,10 +3462,9 @@ static void launch_pcg_v(dim3 grid, dim3 block, size_t lds, hipStream_t st, cons
   hipLaunchKernelGGL((k_pcg<TM, L, C, O>), grid, block, lds, st, m, pg, w, cs, a);
 }
 
-static ZeroRanges solver_ranges(const Mesh& m, const SolverWork& w, bool coarse, const int* done) {
+static ZeroRanges solver_ranges(const Mesh& m, const SolverWork& w, bool coarse, const int* left) {
   ZeroRanges z{};
-  z.done = done;
-  z.ninst = m.ninst;
+  z.left = left;
   z.p[0] = w.barrier;
   z.n[0] = w.barrier_ints;
   z.p[1] = w.abort_flag;
@@ -3493,7 +3485,7 @@ void launch_pcg(const Mesh& m, const SolverPlan& plan, const SolverWork& w, cons
   size_t lds = pcg_lds_bytes<TM>(m.maxnz, plan.rows, plan.mat_home, coarse ? cs.max_nc : 0,
                                  plan.max_halo, coarse ? plan.xl_floats : 0);
   if (!cleared) {
-    const ZeroRanges z = solver_ranges(m, w, coarse, a.done);
+    const ZeroRanges z = solver_ranges(m, w, coarse, a.left);
     const int most = std::max(std::max(z.n[0], z.n[2]), z.n[3]);
     hipLaunchKernelGGL(k_zero_ranges, dim3(std::min(blocks_for(most, 256), 1024)), dim3(256), 0,
                        st, z);
@@ -3537,7 +3529,7 @@ bool launch_coarse_setup(const Mesh& m, const SolverWork& w, const Coarse& c, co
   const int nframe = blocks_for(c.nagg, 4);
   const int nclear = std::min(blocks_for(coarse_doubles, 256), 1024);
   hipLaunchKernelGGL(k_coarse_prepare, dim3(nframe + nclear), dim3(256), 0, st, m, c, x, nframe,
-                     (long)coarse_doubles, solver_ranges(m, w, true, c.done));
+                     (long)coarse_doubles, solver_ranges(m, w, true, c.left));
   hipLaunchKernelGGL((k_coarse_operators<TM>),
                      dim3(c.npair + blocks_for(c.nmid, 4) + blocks_for(m.ninst, 4)), dim3(256), 0,
                      st, m, c, x, A);

@@ -432,6 +432,7 @@ sim_status setup_direct(sim_t* s, const std::vector<HostSheet>& sheets) {
   const int counters = (P.counters + kDsLine - 1) / kDsLine * kDsLine + kDsLine * (kDsQueues + 1);
   TRY(alloc(s, 4 * (size_t)counters, &q)); a.count = (int*)q;
   HIPCHECK(s, hipMemset(a.count, 0, 4 * (size_t)counters));
+  TRY(alloc(s, 2 * sizeof(int), &q)); a.left = (int*)q;
   a.queue = a.count + counters - kDsLine * (kDsQueues + 1);
   a.abort_flag = a.count + counters - kDsLine;
   s->dacc.clear_ints = counters;
@@ -991,25 +992,28 @@ void solve_step(sim_t* s, int step, const double* xp, PcgArgs<TM> c, bool reuse,
       const bool factor = !(reuse && s->ds_step[slot] == step);
       launch_ds_run(s->ds_args, fac, factor ? s->ds_factor : s->ds_solve,
                     (int)(factor ? s->dp.factor_tasks : s->dp.solve_tasks).size(), factor,
-                    s->ds_grid, nullptr, 0, st);
+                    s->ds_grid, nullptr, st);
       s->ds_step[slot] = step;
       DsAccept o = s->dacc;
       o.iters = c.iters;
       o.resid = c.resid;
       o.res = s->ds_r;
+      o.left = s->da.left;
       if (s->ds_corr && s->cg_tol < kDirectAlwaysTol) o.tol = 0.0;
       launch_ds_resid(s->da, o, s->ds_res, (int)s->dp.res_tasks.size(), st);
       if (s->ds_corr) {
         launch_ds_run(s->ds_corr, fac, s->ds_solve, (int)s->dp.solve_tasks.size(), false, s->ds_grid,
-                      o.done, s->L.ninst, st);
+                      o.left, st);
         launch_ds_add(s->da, o, s->ds_dx, s->mesh.vert_inst, st);
         o.res = nullptr;
         o.again = 1;
+        o.left = s->da.left + 1;
         o.tol = s->cg_tol;
         launch_ds_resid(s->da, o, s->ds_res, (int)s->dp.res_tasks.size(), st);
       }
       Coarse cs = s->coarse;
       cs.done = c.done = o.done;
+      cs.left = c.left = o.left;
       const bool cleared = launch_coarse_setup<TM>(s->mesh, s->sw, cs, xp, c.A, s->L.coarse_doubles,
                                                    s->sweep_groups, st);
       launch_pcg<TM>(s->mesh, s->plan, s->sw, cs, c, st, cleared);

@@ -109,6 +109,7 @@ constexpr int kMid = 16;          // vertices per aggregate of the middle level
 struct Coarse {
   int nagg;                    // 0: no coarse space
   const int* done;             // [ninst] 1: the sheet needs no coarse operator; or nullptr
+  const int* left;             // with done: the number of sheets that need one
   int max_nc;
   int max_nb;                  // largest number of 32-tiles per side
   const int* agg_v0;           // [nagg+1]

@@ -43,13 +43,6 @@ void enqueue(hipStream_t st, std::function<void()> f) {
   else f();
 }
 
-bool all(const int* done, int n) {
-  if (!done) return false;
-  for (int b = 0; b < n; ++b)
-    if (!done[b]) return false;
-  return true;
-}
-
 }  // namespace
 
 extern "C" {
@@ -179,7 +172,7 @@ template <typename TM>
 void launch_pcg(const Mesh& m, const SolverPlan&, const SolverWork&, const Coarse& cs,
                 const PcgArgs<TM>& a, hipStream_t st, bool) {
   enqueue(st, [=] {
-    if (all(a.done, m.ninst)) return;
+    if (a.left && *a.left == 0) return;
     ++dev.counts[kIterated];
     if (cs.nagg && cs.xinv[0] != (float)a.A[0]) ++dev.counts[kStaleCoarse];
     a.sol[0] = a.A[0];
@@ -191,7 +184,7 @@ bool launch_coarse_setup(const Mesh& m, const SolverWork&, const Coarse& c, cons
                          long long, const std::vector<int>&, hipStream_t st) {
   if (c.nagg == 0) return false;
   enqueue(st, [=] {
-    if (all(c.done, m.ninst)) return;
+    if (c.left && *c.left == 0) return;
     ++dev.counts[kCoarse];
     c.xinv[0] = (float)A[0];
   });
@@ -227,9 +220,10 @@ hipError_t noalloc_scratch(void** out) {
 
 hipError_t ds_prepare(int* n) { *n = 2; return hipSuccess; }
 void launch_ds_run(const DsArgs* args, double* fac, const DsTask*, int, bool factor, int,
-                   const int* done, int ninst, hipStream_t st) {
+                   const int* left, hipStream_t st) {
   enqueue(st, [=] {
-    if (all(done, ninst)) return;
+    if (left && *left == 0) return;
+    if (!left) args->left[0] = args->left[1] = 0;
     ++dev.counts[factor ? kFactorised : kPasses];
     if (factor) fac[0] = args->A[0];
     else if (fac[0] != args->A[0]) ++dev.counts[kStaleFactors];
@@ -242,7 +236,8 @@ void launch_ds_resid(const DsArgs& a, const DsAccept& o, const DsRows* tasks, in
     for (int k = 0; k < n; ++k) {
       const int b = tasks[k].sheet;
       if (o.again && o.done[b]) continue;
-      o.done[b] = a.sol[0] == a.A[0];
+      o.done[b] = a.sol[0] == a.A[0] && o.tol > 0.0;
+      if (!o.done[b] && (k == 0 || tasks[k - 1].sheet != b)) ++*o.left;
       if (o.iters && o.done[b]) o.iters[b] = 1;
     }
   });

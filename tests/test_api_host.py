@@ -304,3 +304,12 @@ def test_captures_of_the_caller(lib, make, checkpoint):
     # back to direct calls
     h.rollout(20, 4000.0)
     sound(h.adjoint())
+
+
+@pytest.mark.parametrize("tol,corrections", [(1e-8, 0), (5e-10, 0), (5e-12, 6)])
+def test_corrections_run_where_a_sheet_is_left(make, tol, corrections):
+    """Below 1e-9 an unaccepted solve is corrected, below 1e-11 every one is; the launches
+    that follow an accepted solve find no sheet left and do nothing."""
+    h = make(24, max_steps=6, cg_tol=tol)
+    c = h.rollout(6, 1.0)
+    assert (c["factorised"], c["passes"], c["coarse"], c["iterated"]) == (6, corrections, 0, 0)
