@@ -181,7 +181,10 @@ typedef struct {
                                all sheets of the handle together, at most 16 GB and half
                                the device memory free at creation for one factorisation
                                (else, or where that memory cannot be had, all sheets are
-                               solved iteratively)                                      */
+                               solved iteratively), and when that is the faster way:
+                               sim_create counts the iterations of a solve to cg_tol on
+                               the rest state's system, which loose tolerances and short
+                               steps need few of                                        */
   int32_t checkpoint_every; /* k > 0: keep every k-th state, recompute in the adjoint;
                                0: keep every state                                      */
   double gravity[3];        /* m/s^2                                                    */

@@ -300,18 +300,27 @@ sim_status apply_plan(sim_t* s, const HostPlan& P) {
   return SIM_OK;
 }
 
-// Measuring autotuner: builds the step system of the rest state (the sheets at rest,
-// zero velocity, gravity) with the real kernels, then times kTuneIters PCG
-// iterations of every feasible launch shape and keeps the fastest.
-constexpr int kTuneIters = 40;
+// Positions of the sheets' rest shapes in the internal vertex order, [nv][3].
+std::vector<double> rest_internal(const sim_t* s, const std::vector<HostSheet>& sheets) {
+  const HostLayout& L = s->L;
+  std::vector<double> xr(3 * (size_t)L.nv);
+  for (int b = 0; b < L.ninst; ++b)
+    for (int q = 0; q < L.inst_nv[b]; ++q) {
+      const int i = L.inst_voff[b] + q, src = L.vold[i] - L.inst_voff[b];
+      for (int c = 0; c < 3; ++c) xr[3 * (size_t)i + c] = sheets[b].rest[3 * (size_t)src + c];
+    }
+  return xr;
+}
 
+// Assembles the step system of the rest state (xi: rest_internal) and its coarse operators;
+// c receives the solver's operands.
 template <typename TM>
-sim_status autotune(sim_t* s, const std::vector<HostPlan>& cands, const std::vector<double>& xr,
-                    int* pick) {
+sim_status rest_system(sim_t* s, const std::vector<double>& xi, PcgArgs<TM>& c) {
   const int nv = s->L.nv;
-  void* q = nullptr;
-  TRY(alloc(s, 3 * (size_t)nv * 8, &q));
-  double* x = (double*)q;
+  std::vector<double> xr(3 * (size_t)nv);
+  for (int i = 0; i < nv; ++i)
+    for (int k = 0; k < 3; ++k) xr[(size_t)k * nv + i] = xi[3 * (size_t)i + k];
+  double* x = s->gx;   // the adjoint's, free at creation
   HIPCHECK(s, hipMemcpy(x, xr.data(), 3 * (size_t)nv * 8, hipMemcpyHostToDevice));
   hipStream_t st = nullptr;
   launch_fill_double(s->gv, 3L * nv, 0.0, st);
@@ -329,14 +338,28 @@ sim_status autotune(sim_t* s, const std::vector<HostPlan>& cands, const std::vec
   a.status = s->status;
   launch_assemble<double, TM>(s->mesh, s->el, a, st);
   launch_coarse_setup<TM>(s->mesh, s->sw, s->coarse, x, a.A, s->L.coarse_doubles, s->sweep_groups, st);
-  PcgArgs<TM> c{};
+  c = PcgArgs<TM>{};
   c.A = a.A;
   c.Jinv = a.Jinv;
   c.rhs = s->rhs;
   c.sol = s->sol;
+  c.status = s->status;
+  return SIM_OK;
+}
+
+// Measuring autotuner: builds the step system of the rest state (the sheets at rest,
+// zero velocity, gravity) with the real kernels, then times kTuneIters PCG
+// iterations of every feasible launch shape and keeps the fastest.
+constexpr int kTuneIters = 40;
+
+template <typename TM>
+sim_status autotune(sim_t* s, const std::vector<HostPlan>& cands, const std::vector<double>& xi,
+                    int* pick) {
+  hipStream_t st = nullptr;
+  PcgArgs<TM> c;
+  TRY(rest_system<TM>(s, xi, c));
   c.tol = 0.0;  // never met: every trial runs kTuneIters iterations
   c.max_iter = kTuneIters;
-  c.status = s->status;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   HIPCHECK(s, hipEventCreate(&e0));
   HIPCHECK(s, hipEventCreate(&e1));
@@ -366,18 +389,6 @@ sim_status autotune(sim_t* s, const std::vector<HostPlan>& cands, const std::vec
   return SIM_OK;
 }
 
-// Positions of the sheets' rest shapes in the internal vertex order, [nv][3].
-std::vector<double> rest_internal(const sim_t* s, const std::vector<HostSheet>& sheets) {
-  const HostLayout& L = s->L;
-  std::vector<double> xr(3 * (size_t)L.nv);
-  for (int b = 0; b < L.ninst; ++b)
-    for (int q = 0; q < L.inst_nv[b]; ++q) {
-      const int i = L.inst_voff[b] + q, src = L.vold[i] - L.inst_voff[b];
-      for (int c = 0; c < 3; ++c) xr[3 * (size_t)i + c] = sheets[b].rest[3 * (size_t)src + c];
-    }
-  return xr;
-}
-
 // The direct solver serves handles that leave the solver to the library. An explicit
 // launch shape, matrix home, matrix precision or coarse space asks for the iterative
 // solver, and so does an iteration cap below the dimension (CG's own bound), which may
@@ -392,16 +403,106 @@ bool want_direct(const sim_t* s, const sim_options& o) {
          o.cg_tol >= kDirectMinTol;
 }
 
+// Time of a factorisation with one solve, us: the chain of fronts of the largest sheet and
+// its tasks, beside which the other sheets' tasks run, and the residual and the empty
+// launches after it. Within 15 % of the times measured on 17x17 (0.13 ms) to 300x300
+// (8.5 ms) sheets and on batches of up to 64 sheets of 64x64 (6.3 ms).
+double direct_us(const HostLayout& L, const DsPlan& P) {
+  int tiles = 0, most = 0;
+  for (int l = 0; l < P.levels(); ++l) {
+    int np = 0;
+    for (int q = P.level0[l]; q < P.level0[l + 1]; ++q) np = std::max(np, P.fronts[q].np);
+    tiles += np / kDsTile;
+  }
+  for (int n : L.inst_nv) most = std::max(most, n);
+  const double task = 0.024, all = task * (double)P.factor_tasks.size();
+  const double own = all * most / L.nv;
+  return 25.0 + std::hypot(5.5 * tiles + own, all - own);
+}
+
+// Time of an iteration on a launch of n workgroups whose coarse operators are nc wide, us:
+// 8.3 on the 2 of a 17x17 sheet, 9.0 on the 16 of 64x64 (nc 384), 12 on the 157 of 200x200
+// (nc 1920) and the 256 of 16 sheets of 64x64, 31 on 512, which no longer have a CU each.
+double iteration_us(int n, int nc) {
+  return n <= 256 ? 8.3 + 0.0019 * nc + 3.0 * std::pow(n / 256.0, 3) : 31.0 * n / 512.0;
+}
+
+// Whether the direct solver is the faster one: compares its time with that of the iterative
+// solver, which depends on the number of its iterations. Those are counted on the system of
+// the rest state, with gravity and seeded noise for its loads (no times are taken: the
+// choice is the same wherever it is made, except that autotune may have changed the
+// iterative solver's launch). Handles of 1e-7 and steps of 5 to 10 ms on up to 32 sheets are
+// all direct (forward 1.1 to 3 times faster); 64x64 at 1e-3 and 1 ms (18 iterations) takes
+// 0.43 ms a step iteratively and 0.58 directly, 200x200 at 1e-7 and 0.1 ms (55 iterations)
+// 1.9 and 3.6, 256 sheets of 16x16 at 1e-7 (45) 0.73 and 0.90. The line lies where a handle's
+// first step with its adjoint takes the same: two factorisations, or two iterative solves,
+// of which the second has its coarse operators from the first.
+sim_status direct_pays(sim_t* s, const std::vector<double>& xi, bool* pays) {
+  const HostLayout& L = s->L;
+  const std::vector<int>& g0 = s->plan_h.group_wg0;
+  const int ng = (int)g0.size() - 1;
+  const int nc = kGjTile * s->coarse.max_nb;
+  const double setup = 40.0 + 0.5 * nc, most = direct_us(L, s->dp) + 0.5 * setup;
+  double all = 0.0;   // an iteration of every launch
+  for (int g = 0; g < ng; ++g) all += iteration_us(g0[g + 1] - g0[g], nc);
+  *pays = true;
+  if (setup >= most) return SIM_OK;
+  // with several launches some may end early and others go on
+  const double last = std::ceil((most - setup) / all) * (ng > 1 ? 4.0 : 1.0);
+  PcgArgs<double> c;
+  TRY(rest_system<double>(s, xi, c));
+  // gravity, as assembled, and noise of a twentieth of it (without gravity noise alone):
+  // noise alone takes up to 1.4 times the iterations at loose tolerances
+  std::vector<double> b(3 * (size_t)L.nv, 0.0);
+  HIPCHECK(s, hipMemcpy(b.data(), s->rhs, b.size() * 8, hipMemcpyDeviceToHost));
+  double rms = 0.0;
+  for (double v : b) rms += v * v;
+  rms = std::sqrt(rms / (double)b.size());
+  const double noise = rms > 0.0 && std::isfinite(rms) ? 0.05 * rms : 1.0;
+  for (int i = 0; i < L.nv; ++i)
+    for (int k = 0; k < 3 && !L.pinned[i]; ++k) {   // splitmix64 of the sheet's own index
+      unsigned long long z =
+          (3ull * (i - L.inst_voff[L.vert_inst[i]]) + k + 1) * 0x9e3779b97f4a7c15ull;
+      z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
+      z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
+      b[(size_t)k * L.nv + i] += noise * (double)(long long)(z ^ (z >> 31)) / 5.3e18;
+    }
+  HIPCHECK(s, hipMemcpy(s->rhs, b.data(), b.size() * 8, hipMemcpyHostToDevice));
+  c.tol = s->cg_tol;
+  c.max_iter = (int)std::min(last, (double)s->cg_max_iter);
+  c.iters = s->it_fwd;
+  launch_pcg<double>(s->mesh, s->plan, s->sw, s->coarse, c, nullptr);
+  std::vector<int> iters(L.ninst), words(L.ninst + 1);
+  HIPCHECK(s, hipMemcpy(iters.data(), s->it_fwd, 4 * iters.size(), hipMemcpyDeviceToHost));
+  HIPCHECK(s, hipMemcpy(words.data(), s->status, 4 * words.size(), hipMemcpyDeviceToHost));
+  HIPCHECK(s, hipMemset(s->it_fwd, 0, 4 * iters.size()));
+  HIPCHECK(s, hipMemset(s->status, 0, 4 * words.size()));
+  double us = setup;
+  for (int g = 0; g < ng; ++g) {
+    int n = 0;
+    for (int k = 0; k < L.ninst; ++k) {
+      const int w = s->plan_h.inst_wg0[k];
+      if (w >= g0[g] && w < g0[g + 1]) n = std::max(n, words[1 + k] ? c.max_iter : iters[k]);
+    }
+    us += n * iteration_us(g0[g + 1] - g0[g], nc);
+  }
+  *pays = us >= most;
+  return SIM_OK;
+}
+
 sim_status setup_direct(sim_t* s, const std::vector<HostSheet>& sheets) {
   const HostLayout& L = s->L;
   DsPlan& P = s->dp;
-  build_direct_plan(L.nv, L.maxnz, L.ell_col, L.inst_voff, L.inst_nv, rest_internal(s, sheets), P,
-                    kDirectWorkCap / 8.0);
+  const std::vector<double> xi = rest_internal(s, sheets);
+  build_direct_plan(L.nv, L.maxnz, L.ell_col, L.inst_voff, L.inst_nv, xi, P, kDirectWorkCap / 8.0);
   if (!P.ok) return SIM_OK;
   size_t fre = 0, total = 0;
   HIPCHECK(s, hipMemGetInfo(&fre, &total));
   if (8.0 * ((double)P.factor_doubles + (double)P.work_doubles) > kDirectFreeShare * (double)fre)
     return SIM_E_NOMEM;
+  bool pays = false;
+  TRY(direct_pays(s, xi, &pays));
+  if (!pays) return SIM_OK;
   int dev = 0, ncu = 0, per_cu = 0;
   HIPCHECK(s, hipGetDevice(&dev));
   HIPCHECK(s, hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
@@ -474,6 +575,7 @@ sim_status try_direct(sim_t* s, const std::vector<HostSheet>& sheets) {
     st = setup_direct(s, sheets);
   } catch (const std::bad_alloc&) {
   }
+  if (st == SIM_OK && !s->use_direct) s->dp = DsPlan{};
   if (st != SIM_E_NOMEM) return st;
   (void)hipGetLastError();
   s->err.clear();
@@ -912,12 +1014,9 @@ sim_status setup(sim_t* s, const std::vector<HostSheet>& sheets, double dt, cons
   s->stats.autotune_candidates = (int)feasible.size();
   if (o.autotune && feasible.size() > 1) {
     const std::vector<double> xi = rest_internal(s, sheets);
-    std::vector<double> xr(3 * nv);
-    for (size_t i = 0; i < nv; ++i)
-      for (int c = 0; c < 3; ++c) xr[(size_t)c * nv + i] = xi[3 * i + c];
     int pick = best;
-    TRY(s->mprec == SIM_FP64 ? autotune<double>(s, feasible, xr, &pick)
-                             : autotune<float>(s, feasible, xr, &pick));
+    TRY(s->mprec == SIM_FP64 ? autotune<double>(s, feasible, xi, &pick)
+                             : autotune<float>(s, feasible, xi, &pick));
     best = pick;
     s->stats.autotuned = 1;
   }

@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 #include <sys/mman.h>
 
+#include <algorithm>
 #include <cstring>
 #include <functional>
 #include <map>
@@ -32,6 +33,7 @@ struct {
   std::map<hipStream_t, Capture> captures;
   unsigned long long ids = 0;
   int counts[8] = {};
+  int iterations = 1000;   // of a solve, at most its cap
   int fail_in = 0;   // > 0: the allocation that fails, counted from now
 } dev;
 
@@ -49,6 +51,7 @@ extern "C" {
 
 // what the tests set and read
 void fake_memory(size_t bytes) { dev.total = bytes; }
+void fake_iterations(int n) { dev.iterations = n; }
 void fake_fail(int nth) { dev.fail_in = nth; }
 size_t fake_used() { return dev.used; }
 void fake_counts(int* out, int clear) {
@@ -176,7 +179,7 @@ void launch_pcg(const Mesh& m, const SolverPlan&, const SolverWork&, const Coars
     ++dev.counts[kIterated];
     if (cs.nagg && cs.xinv[0] != (float)a.A[0]) ++dev.counts[kStaleCoarse];
     a.sol[0] = a.A[0];
-    for (int b = 0; a.iters && b < m.ninst; ++b) a.iters[b] = 100;
+    for (int b = 0; a.iters && b < m.ninst; ++b) a.iters[b] = std::min(dev.iterations, a.max_iter);
   });
 }
 template <typename TM>

@@ -35,10 +35,11 @@ def lib(tmp_path_factory):
 class Handle:
     """A handle over one n x n sheet, its calls on host arrays of the right sizes."""
 
-    def __init__(self, lib, n, memory=1 << 34, fail=0, **options):
+    def __init__(self, lib, n, memory=1 << 34, fail=0, iterations=1000, **options):
         self.lib = lib
         lib.fake_memory(memory)
         lib.fake_fail(fail)
+        lib.fake_iterations(iterations)
         opt = S._Options()
         lib.sim_default_options(ctypes.byref(opt))
         opt.precision = S.SIM_FP64
@@ -313,3 +314,18 @@ def test_corrections_run_where_a_sheet_is_left(make, tol, corrections):
     h = make(24, max_steps=6, cg_tol=tol)
     c = h.rollout(6, 1.0)
     assert (c["factorised"], c["passes"], c["coarse"], c["iterated"]) == (6, corrections, 0, 0)
+
+
+@pytest.mark.parametrize("n,few,many", [(17, 6, 20), (32, 16, 30), (64, 34, 60), (111, 55, 100)])
+def test_solver_follows_the_iterations_it_would_take(make, n, few, many):
+    """A handle whose solves the iterative solver would end within a few iterations (loose
+    tolerances, short steps) is left to it: a factorisation would take longer. The counts
+    stand on either side of the measured break-even."""
+    for iterations, direct in ((few, False), (many, True)):
+        h = make(n, iterations=iterations, max_steps=2)
+        assert h.stats().cg_iters_max == 0 and h.stats().device_status == 0   # nothing left behind
+        c = h.rollout(2, 1.0)
+        assert (c["factorised"], c["iterated"]) == ((2, 0) if direct else (0, 2)), iterations
+        h.close()
+    h = make(4, iterations=4, max_steps=2)      # a single front
+    assert h.rollout(2, 1.0)["factorised"] == 2
