@@ -116,8 +116,15 @@ struct DsPlan {
   long long factor_doubles = 0, work_doubles = 0;
   int counters = 0;
   int max_np = 0, max_nb = 0;
-  double flops = 0.0;        // of one factorisation
   int levels() const { return (int)level0.size() - 1; }
+  // Frees the lists and tables (512 bytes a task: 52 MB of a 200x200 sheet).
+  void drop_tables() {
+    const long long f = factor_doubles, w = work_doubles;
+    *this = DsPlan{};
+    ok = true;
+    factor_doubles = f;
+    work_doubles = w;
+  }
 };
 
 // xr: rest positions [nv][3] in the internal vertex order; ell_col, inst_voff and inst_nv

@@ -9,7 +9,6 @@ namespace phisft {
 
 // Device tables, workspace and operands of one factorisation or solve.
 struct DsArgs {
-  const DsFront* fr;
   const DsChild* kid;
   const int* tab;
   int nv, maxnz;

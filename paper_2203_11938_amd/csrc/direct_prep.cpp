@@ -220,8 +220,6 @@ void build_direct_plan(int nv, int maxnz, const std::vector<int>& ell_col,
     P.factor_doubles = F.wo + (long long)F.nb * F.np;
     P.max_np = std::max(P.max_np, F.np);
     P.max_nb = std::max(P.max_nb, F.nb);
-    P.flops += 2.0 * F.np * (double)F.np * F.np + 2.0 * F.nb * (double)F.np * F.np +
-               (double)F.nb * F.nb * F.np;
   }
   for (DsFront& F : P.fronts) {
     F.so = P.work_doubles;

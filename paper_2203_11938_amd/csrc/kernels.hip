@@ -824,6 +824,7 @@ __device__ __forceinline__ void zero_ranges(const ZeroRanges& z, int k0, int str
     for (int k = k0; k < z.n[r]; k += stride) z.p[r][k] = 0;
 }
 
+// Zeroes them in one launch (grid-stride; before each launch of the solver).
 __global__ void __launch_bounds__(256) k_zero_ranges(ZeroRanges z) {
   if (none_left(z.left)) return;
   zero_ranges(z, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
@@ -3330,8 +3331,6 @@ __global__ void k_fill_int(int* p, int n, int v) {
   if (k < n) p[k] = v;
 }
 
-// Zeroes up to four int ranges in one launch (grid-stride; the solver's counters,
-// abort flag and tagged buffers before each launch).
 __global__ void k_fill_double(double* p, long n, double v) {
   long k = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (k < n) p[k] = v;

@@ -69,10 +69,11 @@ struct sim_s {
   // direct solver (use_direct): plan, device tables and the factors of kept steps; slot of
   // step s: (s - 1) % slots
   bool use_direct = false;
-  DsPlan dp;
+  DsPlan dp;                              // its lists and tables only until they are uploaded
   DsArgs da{};
   const DsTask *ds_factor = nullptr, *ds_solve = nullptr;
   const DsRows* ds_res = nullptr;
+  int ds_nfactor = 0, ds_nsolve = 0, ds_nres = 0;   // their lengths
   const DsArgs* ds_args = nullptr;        // device copy of da
   const DsArgs* ds_corr = nullptr;        // the same for a correction: A dx = r
   double *ds_r = nullptr, *ds_dx = nullptr;
@@ -509,7 +510,6 @@ sim_status setup_direct(sim_t* s, const std::vector<HostSheet>& sheets) {
   HIPCHECK(s, ds_prepare(&per_cu));
   s->ds_grid = std::max(1, per_cu * ncu);
   DsArgs& a = s->da;
-  TRY(upload(s, P.fronts, &a.fr));
   TRY(upload(s, P.kids, &a.kid));
   TRY(upload(s, P.tab, &a.tab));
   // a queue's tasks are contiguous, in their order
@@ -561,6 +561,10 @@ sim_status setup_direct(sim_t* s, const std::vector<HostSheet>& sheets) {
   TRY(alloc(s, 4 * (size_t)L.ninst, &q)); o.arrived = (int*)q;
   HIPCHECK(s, hipMemset(o.arrived, 0, 4 * (size_t)L.ninst));
   TRY(alloc(s, 4 * (size_t)L.ninst, &q)); o.done = (int*)q;
+  s->ds_nfactor = (int)P.factor_tasks.size();
+  s->ds_nsolve = (int)P.solve_tasks.size();
+  s->ds_nres = (int)P.res_tasks.size();
+  P.drop_tables();
   s->ds_step.assign(1, 0);
   s->use_direct = true;
   return SIM_OK;
@@ -1090,8 +1094,7 @@ void solve_step(sim_t* s, int step, const double* xp, PcgArgs<TM> c, bool reuse,
       double* fac = s->ds_fac[slot];
       const bool factor = !(reuse && s->ds_step[slot] == step);
       launch_ds_run(s->ds_args, fac, factor ? s->ds_factor : s->ds_solve,
-                    (int)(factor ? s->dp.factor_tasks : s->dp.solve_tasks).size(), factor,
-                    s->ds_grid, nullptr, st);
+                    factor ? s->ds_nfactor : s->ds_nsolve, factor, s->ds_grid, nullptr, st);
       s->ds_step[slot] = step;
       DsAccept o = s->dacc;
       o.iters = c.iters;
@@ -1099,16 +1102,15 @@ void solve_step(sim_t* s, int step, const double* xp, PcgArgs<TM> c, bool reuse,
       o.res = s->ds_r;
       o.left = s->da.left;
       if (s->ds_corr && s->cg_tol < kDirectAlwaysTol) o.tol = 0.0;
-      launch_ds_resid(s->da, o, s->ds_res, (int)s->dp.res_tasks.size(), st);
+      launch_ds_resid(s->da, o, s->ds_res, s->ds_nres, st);
       if (s->ds_corr) {
-        launch_ds_run(s->ds_corr, fac, s->ds_solve, (int)s->dp.solve_tasks.size(), false, s->ds_grid,
-                      o.left, st);
+        launch_ds_run(s->ds_corr, fac, s->ds_solve, s->ds_nsolve, false, s->ds_grid, o.left, st);
         launch_ds_add(s->da, o, s->ds_dx, s->mesh.vert_inst, st);
         o.res = nullptr;
         o.again = 1;
         o.left = s->da.left + 1;
         o.tol = s->cg_tol;
-        launch_ds_resid(s->da, o, s->ds_res, (int)s->dp.res_tasks.size(), st);
+        launch_ds_resid(s->da, o, s->ds_res, s->ds_nres, st);
       }
       Coarse cs = s->coarse;
       cs.done = c.done = o.done;
