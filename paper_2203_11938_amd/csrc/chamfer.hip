@@ -2,10 +2,10 @@
 // evaluation metric, Sec. 4.2, Eq. 10):
 //   Ch(G, M) = 1/|G| sum_g min_m |g - m|^2 + 1/|M| sum_m min_g |m - g|^2.
 //
-// Small sets: both nearest-neighbour searches run in one launch of k_chamfer_nn. A workgroup takes
-// a block of 1024 query points (four per lane, coordinates in registers) and a tile of
-// at most kChTile database points staged in LDS as three coordinate arrays (every lane reads the
-// same point: an LDS broadcast), and keeps each query's smallest squared distance and
+// Small sets: both nearest-neighbour searches run in one launch of k_chamfer_nn. A workgroup
+// takes a block of 1024 query points (four per lane, coordinates in registers) and a tile
+// of at most kChTile database points staged in LDS as three coordinate arrays (every lane
+// reads the same point: an LDS broadcast), and keeps each query's smallest squared distance and
 // its index; the tiles of one query block go to different workgroups, which merge their
 // results with a 64-bit atomic minimum on (distance bits << 32 | index). Non-negative
 // floats order like their bit patterns, so the merged value is the smallest distance
@@ -15,15 +15,16 @@
 // distances), the means are accumulated in FP64 in a fixed order.
 //
 // Large sets: all pairs are bound by the vector ALUs (65536 against 40000 points: 800 us;
-// sorted 126 us), and nearly all of them are far apart. Both sets are sorted into the cells of a 32^3 grid
-// in Morton order (one counting sort), every 64 consecutive points get their bounding box,
-// and a workgroup of four wavefronts searches for 64 sorted queries: it visits only the
-// blocks whose box is no further from a query than the best point found so far. The
-// bounds are formed with the operations of the distance itself, each of which rounds
-// monotonically, so a skipped point's distance is larger as computed; equal distances are
-// decided by the index. So both ways give the same bits, also for infinities and NaN
-// (which no bound excludes and no comparison selects). The sort's order within a cell
-// varies from run to run; the results do not depend on it.
+// sorted 121 to 138 us over seeds, 130 on average), and nearly all of them are far apart.
+// Each set is sorted into the cells of a 32^3 grid of its own in Morton order (one counting
+// sort), every 64 consecutive points get their bounding box, and a workgroup of four
+// wavefronts searches for 64 sorted queries: it visits only the blocks whose box is no
+// further from a query than the best point found so far. The bounds are formed with the
+// operations of the distance itself, each of which rounds monotonically, so a skipped
+// point's distance is larger as computed; equal distances are decided by the index. So both
+// ways give the same bits, also for infinities and NaN (whose distances no comparison
+// selects). The sort's order within a cell varies from run to run; the results do not
+// depend on it.
 
 #include <hip/hip_runtime.h>
 
@@ -40,6 +41,7 @@ constexpr int kChBlockQ = kChThreads * kChQ;     // query points per workgroup
 constexpr int kChTile = 2048;                    // database points per workgroup (LDS) at most
 constexpr int kChTileMin = 64;                   // and at least: 5000 by 289 points in tiles
                                                  // of 2048 kept 8 CUs busy, 196 us; now 19
+constexpr int kChTilePlain = 1024;               // at most, of sets not worth sorting
 constexpr int kChGrid = 1024;                    // workgroups that fill the chip
 
 struct ChamferPass {
@@ -78,62 +80,75 @@ __device__ __forceinline__ float dist2(float dx, float dy, float dz) {
   return fmaf(dz, dz, fmaf(dx, dx, dy * dy));
 }
 
-// Workgroups [0, nb0) serve pass 0 (queries G, database M), the rest pass 1 (M into G):
+// All pairs. Blocks [0, nb0) serve pass 0 (queries G, database M), the rest pass 1 (M into G):
 // block b of a pass covers query block b % qblocks and database tile b / qblocks.
-__global__ void __launch_bounds__(kChThreads) k_chamfer_nn(ChamferPass p0, ChamferPass p1,
-                                                           int nb0, int ntile, int* bad) {
-  __shared__ float sx[kChTile], sy[kChTile], sz[kChTile];
-  const bool second = (int)blockIdx.x >= nb0;
-  const ChamferPass& p = second ? p1 : p0;
-  const int b = second ? (int)blockIdx.x - nb0 : (int)blockIdx.x;
-  const int qb = b % p.qblocks, tile = b / p.qblocks;
-  const int d0 = tile * ntile, nloc = min(ntile, p.nd - d0);
+struct ChamferPairs {
+  ChamferPass p[2];
+  long nb0, nb;
+  int ntile;        // points of a tile, at most T
+};
+
+template <int T>
+__device__ __forceinline__ void all_pairs(const ChamferPairs& c, float (*s)[T], int* bad) {
   const int tid = threadIdx.x;
-  for (int j = tid; j < nloc; j += kChThreads) {
-    sx[j] = p.db[d0 + j];
-    sy[j] = p.db[p.nd + d0 + j];
-    sz[j] = p.db[2 * p.nd + d0 + j];
-  }
-  float qx[kChQ], qy[kChQ], qz[kChQ], bd[kChQ];
-  int bi[kChQ];
-#pragma unroll
-  for (int k = 0; k < kChQ; ++k) {
-    // lanes past the last query search with a copy of it and store nothing
-    const int i = min(qb * kChBlockQ + k * kChThreads + tid, p.nq - 1);
-    qx[k] = p.q[i];
-    qy[k] = p.q[p.nq + i];
-    qz[k] = p.q[2 * p.nq + i];
-    bd[k] = INFINITY;
-    bi[k] = 0;
-  }
-  // every point is a query of exactly one block of its pass (tile 0 checks it)
-  if (tile == 0) {
-    bool fin = true;
-#pragma unroll
-    for (int k = 0; k < kChQ; ++k) fin = fin && isfinite(qx[k]) && isfinite(qy[k]) && isfinite(qz[k]);
-    if (!fin) atomicOr(bad, 1);
-  }
-  __syncthreads();
-  for (int j = 0; j < nloc; ++j) {
-    const float x = sx[j], y = sy[j], z = sz[j];
+  for (long blk = blockIdx.x; blk < c.nb; blk += gridDim.x) {
+    const bool second = blk >= c.nb0;
+    const ChamferPass& p = second ? c.p[1] : c.p[0];
+    const long b = second ? blk - c.nb0 : blk;
+    const int qb = (int)(b % p.qblocks), tile = (int)(b / p.qblocks);
+    const int d0 = tile * c.ntile, nloc = min(c.ntile, p.nd - d0);
+    for (int j = tid; j < nloc; j += kChThreads) {
+      s[0][j] = p.db[d0 + j];
+      s[1][j] = p.db[p.nd + d0 + j];
+      s[2][j] = p.db[2 * p.nd + d0 + j];
+    }
+    float qx[kChQ], qy[kChQ], qz[kChQ], bd[kChQ];
+    int bi[kChQ];
 #pragma unroll
     for (int k = 0; k < kChQ; ++k) {
-      const float d = dist2(qx[k] - x, qy[k] - y, qz[k] - z);
-      if (d < bd[k]) {   // strictly smaller: the first index among equal distances stays
-        bd[k] = d;
-        bi[k] = j;
+      // lanes past the last query search with a copy of it and store nothing
+      const int i = min(qb * kChBlockQ + k * kChThreads + tid, p.nq - 1);
+      qx[k] = p.q[i];
+      qy[k] = p.q[p.nq + i];
+      qz[k] = p.q[2 * p.nq + i];
+      bd[k] = INFINITY;
+      bi[k] = 0;
+    }
+    // every point is a query of exactly one block of its pass (tile 0 checks it)
+    if (tile == 0) {
+      bool fin = true;
+#pragma unroll
+      for (int k = 0; k < kChQ; ++k) fin = fin && isfinite(qx[k]) && isfinite(qy[k]) && isfinite(qz[k]);
+      if (!fin) atomicOr(bad, 1);
+    }
+    __syncthreads();
+    for (int j = 0; j < nloc; ++j) {
+      const float x = s[0][j], y = s[1][j], z = s[2][j];
+#pragma unroll
+      for (int k = 0; k < kChQ; ++k) {
+        const float d = dist2(qx[k] - x, qy[k] - y, qz[k] - z);
+        if (d < bd[k]) {   // strictly smaller: the first index among equal distances stays
+          bd[k] = d;
+          bi[k] = j;
+        }
       }
     }
-  }
 #pragma unroll
-  for (int k = 0; k < kChQ; ++k) {
-    const int i = qb * kChBlockQ + k * kChThreads + tid;
-    if (i < p.nq && nloc > 0) {
-      const unsigned long long v =
-          ((unsigned long long)__float_as_uint(bd[k]) << 32) | (unsigned)(d0 + bi[k]);
-      atomicMin(p.best + i, v);
+    for (int k = 0; k < kChQ; ++k) {
+      const int i = qb * kChBlockQ + k * kChThreads + tid;
+      if (i < p.nq && nloc > 0) {
+        const unsigned long long v =
+            ((unsigned long long)__float_as_uint(bd[k]) << 32) | (unsigned)(d0 + bi[k]);
+        atomicMin(p.best + i, v);
+      }
     }
+    __syncthreads();   // the tile is read, the next one may come
   }
+}
+
+__global__ void __launch_bounds__(kChThreads) k_chamfer_nn(ChamferPairs c, int* bad) {
+  __shared__ float s[3][kChTile];
+  all_pairs<kChTile>(c, s, bad);
 }
 
 // Unpacks the minima of both sets (distance and index, either output optional) and sums
@@ -220,66 +235,14 @@ struct ChamferSet {
   int split;           // workgroups that share a block of queries
 };
 
+// Grid of a set: lowest corner and cells per length. plain: its points are so concentrated
+// that sorting cannot tell them apart; all pairs are then looked at instead.
 struct ChamferGrid {
-  unsigned* lim;       // [6] keys of the highest -x, -y, -z, x, y, z; zero before
-  int* bad;
+  float lo[3], scale;
+  int plain;
 };
 
-// Order-preserving map of floats to unsigned (NaN apart); zero is below every float.
-__device__ __forceinline__ unsigned float_key(float v) {
-  const unsigned u = __float_as_uint(v);
-  return u & 0x80000000u ? ~u : u | 0x80000000u;
-}
-__device__ __forceinline__ float key_float(unsigned k) {
-  return __uint_as_float(k & 0x80000000u ? k & 0x7fffffffu : ~k);
-}
-
-__global__ void __launch_bounds__(256) k_chamfer_clear(ChamferSet a, ChamferSet b, ChamferGrid g) {
-  const int k = blockIdx.x * 256 + threadIdx.x;
-  if (k < kChCells) {
-    a.head[k] = 0;
-    b.head[k] = 0;
-  }
-  if (k < 6) g.lim[k] = 0;
-  if (k == 6) *g.bad = 0;
-  for (int i = k; i < a.n; i += gridDim.x * 256) a.best[i] = kChNone;
-  for (int i = k; i < b.n; i += gridDim.x * 256) b.best[i] = kChNone;
-}
-
-// Common bounding box of the finite coordinates of both sets.
-__global__ void __launch_bounds__(256) k_chamfer_bounds(ChamferSet a, ChamferSet b, ChamferGrid g) {
-  const int lane = threadIdx.x & 63;
-  float hi[6];
-  for (int q = 0; q < 6; ++q) hi[q] = -INFINITY;
-  bool fin = true;
-  for (long k = (long)blockIdx.x * 256 + threadIdx.x; k < (long)a.n + b.n; k += gridDim.x * 256l) {
-    const ChamferSet& s = k < a.n ? a : b;
-    const int i = (int)(k < a.n ? k : k - a.n);
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-      const float v = s.p[(size_t)r * s.n + i];
-      if (!isfinite(v)) {
-        fin = false;
-        continue;
-      }
-      hi[r] = fmaxf(hi[r], -v);
-      hi[3 + r] = fmaxf(hi[3 + r], v);
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < 6; ++q)
-    for (int o = 32; o > 0; o >>= 1) hi[q] = fmaxf(hi[q], __shfl_xor(hi[q], o));
-  __shared__ float s_hi[4][6];
-  if (lane == 0)
-    for (int q = 0; q < 6; ++q) s_hi[threadIdx.x >> 6][q] = hi[q];
-  if (!__all(fin) && lane == 0) atomicOr(g.bad, 1);
-  __syncthreads();
-  if (threadIdx.x < 6) {
-    float v = s_hi[0][threadIdx.x];
-    for (int w = 1; w < 4; ++w) v = fmaxf(v, s_hi[w][threadIdx.x]);
-    atomicMax(g.lim + threadIdx.x, float_key(v));
-  }
-}
+__device__ __forceinline__ bool use_all_pairs(const ChamferGrid* g) { return g[0].plain || g[1].plain; }
 
 __device__ __forceinline__ int spread3(int v) {   // 5 bits, two zeros between
   v = (v | v << 8) & 0x100f;
@@ -288,66 +251,174 @@ __device__ __forceinline__ int spread3(int v) {   // 5 bits, two zeros between
 }
 
 // A point's cell; any cell is right, near ones together are fast.
-__device__ __forceinline__ int cell_of(const float* lo, float scale, float x, float y, float z) {
+__device__ __forceinline__ int cell_of(const ChamferGrid& g, float x, float y, float z) {
   const float c[3] = {x, y, z};
   int r = 0;
 #pragma unroll
   for (int k = 0; k < 3; ++k)
-    r |= spread3((int)fminf(fmaxf((c[k] - lo[k]) * scale, 0.0f), 31.0f)) << k;
+    r |= spread3((int)fminf(fmaxf((c[k] - g.lo[k]) * g.scale, 0.0f), 31.0f)) << k;
   return r;
 }
 
-__global__ void __launch_bounds__(256) k_chamfer_count(ChamferSet a, ChamferSet b, ChamferGrid g) {
-  const long k = (long)blockIdx.x * 256 + threadIdx.x;
-  if (k >= (long)a.n + b.n) return;
-  const ChamferSet& s = k < a.n ? a : b;
-  const int i = (int)(k < a.n ? k : k - a.n);
-  float lo[3], ext = 0.0f;
+// Median of 64 values, one a lane of a wavefront (NaN last), the same in every lane: sorted
+// by a bitonic network.
+__device__ __forceinline__ float median64(float v, int lane) {
+  v = v == v ? v : INFINITY;
 #pragma unroll
-  for (int r = 0; r < 3; ++r) {
-    lo[r] = -key_float(g.lim[r]);
-    ext = fmaxf(ext, key_float(g.lim[3 + r]) - lo[r]);
-  }
-  const float scale = ext > 0.0f ? 32.0f / ext : 0.0f;
-  const int c = cell_of(lo, scale, s.p[i], s.p[(size_t)s.n + i], s.p[2 * (size_t)s.n + i]);
-  s.where[i] = make_int2(c, atomicAdd(s.head + c, 1));
+  for (int size = 2; size <= 64; size *= 2)
+#pragma unroll
+    for (int o = size / 2; o > 0; o /= 2) {
+      const float w = __shfl_xor(v, o);
+      const bool low = ((lane & o) == 0) == ((lane & size) == 0);
+      v = low ? fminf(v, w) : fmaxf(v, w);
+    }
+  return __shfl(v, 32);
 }
 
-// Counts to first places, one workgroup per set.
-__global__ void __launch_bounds__(1024) k_chamfer_scan(ChamferSet a, ChamferSet b) {
-  __shared__ int s_w[16];
-  int* head = blockIdx.x == 0 ? a.head : b.head;
-  constexpr int per = kChCells / 1024;
-  const int tid = threadIdx.x, lane = tid & 63;
-  int4 v[per / 4];
-  int sum = 0;
+// First launch: the last two workgroups find the sets' grids, the others clear. A grid
+// spans the bulk of 1024 of the set's points: of every 16 the lowest and highest
+// coordinates, and of those the medians (about the outer 4 % at each end, so a set may
+// hold a few outliers, which end up in the outermost cells), widened by a thirty-second. With a
+// grid over all points one outlier far away put the rest into one cell: 65536 against
+// 40000 points took 2284 us, all pairs 825, this way 134. Cells of a sixteenth of the
+// grid's length then count how often two of the points meet: surfaces about 1 time in 200,
+// lines 1 in 16; from 1 in 6 on the set is searched plainly (half of it in one place: 1 in 4).
+constexpr int kChSample = 1024;
+__global__ void __launch_bounds__(kChSample) k_chamfer_start(ChamferSet a, ChamferSet b,
+                                                             ChamferGrid* grid, int* bad) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nclear = gridDim.x - 2;
+  if ((int)blockIdx.x < nclear) {
+    const int k = blockIdx.x * kChSample + tid, stride = nclear * kChSample;
+    for (int i = k; i < kChCells; i += stride) a.head[i] = b.head[i] = 0;
+    for (long i = k; i < a.n; i += stride) a.best[i] = kChNone;
+    for (long i = k; i < b.n; i += stride) b.best[i] = kChNone;
+    if (k == 0) *bad = 0;
+    return;
+  }
+  __shared__ float s_end[6][64];   // lowest and highest of every 16 points
+  __shared__ float s_med[6];
+  __shared__ int s_cell[16 * 16 * 16], s_met;
+  const int which = blockIdx.x - nclear;
+  const ChamferSet& s = which == 0 ? a : b;
+  // golden-ratio steps: even strides would meet the same columns of an ordered grid
+  const int i = (int)((unsigned long long)(tid * 2654435769u) * (unsigned)s.n >> 32);
+  float c[3];
 #pragma unroll
-  for (int q = 0; q < per / 4; ++q) {
-    v[q] = reinterpret_cast<const int4*>(head + per * tid)[q];
-    sum += v[q].x + v[q].y + v[q].z + v[q].w;
+  for (int r = 0; r < 3; ++r) {
+    c[r] = s.p[(size_t)r * s.n + i];
+    float lo = c[r], hi = c[r];
+    for (int o = 8; o > 0; o >>= 1) {
+      lo = fminf(lo, __shfl_xor(lo, o));
+      hi = fmaxf(hi, __shfl_xor(hi, o));
+    }
+    if ((lane & 15) == 0) {
+      s_end[r][tid >> 4] = lo;
+      s_end[3 + r][tid >> 4] = hi;
+    }
   }
-  int up = sum;   // inclusive over the wavefront
-  for (int o = 1; o < 64; o <<= 1) {
-    const int t = __shfl_up(up, o);
-    if (lane >= o) up += t;
-  }
-  if (lane == 63) s_w[tid >> 6] = up;
+  for (int k = tid; k < 16 * 16 * 16; k += kChSample) s_cell[k] = 0;
+  if (tid == 0) s_met = 0;
   __syncthreads();
-  int at = up - sum;
-  for (int w = 0; w < tid >> 6; ++w) at += s_w[w];
+  if (wave < 6) {
+    const float m = median64(s_end[wave][lane], lane);
+    if (lane == 0) s_med[wave] = m;
+  }
+  __syncthreads();
+  ChamferGrid g;
+  float ext = 0.0f;
 #pragma unroll
-  for (int q = 0; q < per / 4; ++q) {
+  for (int r = 0; r < 3; ++r) ext = fmaxf(ext, s_med[3 + r] - s_med[r]);
+  const bool some = ext > 0.0f && isfinite(ext);
+#pragma unroll
+  for (int r = 0; r < 3; ++r) g.lo[r] = some ? s_med[r] - 0.03125f * ext : 0.0f;
+  g.scale = some ? 32.0f / (1.0625f * ext) : 0.0f;
+  // Morton order: the upper four bits of each coordinate are the upper twelve of the cell
+  const int met = atomicAdd(&s_cell[cell_of(g, c[0], c[1], c[2]) >> 3], 1);
+  int sum = met;
+  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+  if (lane == 0) atomicAdd(&s_met, sum);
+  __syncthreads();
+  if (tid == 0) {
+    g.plain = s_met > kChSample * kChSample / 2 / 6;
+    grid[which] = g;
+  }
+}
+
+// Cells and places within them. Points of a wavefront that share a cell take their places
+// together: with an atomic addition each, 65536 points in one cell took 0.7 ms.
+__global__ void __launch_bounds__(256) k_chamfer_count(ChamferSet a, ChamferSet b,
+                                                       const ChamferGrid* grid, int nba, int* bad) {
+  if (use_all_pairs(grid)) return;
+  const bool second = (int)blockIdx.x >= nba;
+  const ChamferSet& s = second ? b : a;
+  const int lane = threadIdx.x & 63;
+  const long k = ((long)blockIdx.x - (second ? nba : 0)) * 256 + threadIdx.x;
+  const bool live = k < s.n;
+  const int i = (int)(live ? k : s.n - 1);
+  const float x = s.p[i], y = s.p[(size_t)s.n + i], z = s.p[2 * (size_t)s.n + i];
+  if (!__all(isfinite(x) && isfinite(y) && isfinite(z)) && lane == 0) atomicOr(bad, 1);
+  const int c = cell_of(grid[second ? 1 : 0], x, y, z);
+  int leader = lane, place = 0, count = 1;
+  unsigned long long todo = __ballot(live);
+  for (int turn = 0; turn < 8 && todo; ++turn) {   // the rest has cells of few points each
+    const int l = __builtin_ctzll(todo);
+    const unsigned long long same = __ballot(live && c == __builtin_amdgcn_readlane(c, l));
+    if (live && same >> lane & 1) {
+      leader = l;
+      place = __popcll(same & ((1ull << lane) - 1));
+      count = __popcll(same);
+    }
+    todo &= ~same;
+  }
+  int first = 0;
+  if (live && lane == leader) first = atomicAdd(s.head + c, count);
+  first = __shfl(first, leader);
+  if (live) s.where[i] = make_int2(c, first + place);
+}
+
+// Counts to first places, one workgroup per set, in 8 chunks of 16 bytes a thread (with 128
+// contiguous bytes a thread, whose loads touch 64 lines a wavefront, 9.7 us).
+__global__ void __launch_bounds__(1024) k_chamfer_scan(ChamferSet a, ChamferSet b,
+                                                       const ChamferGrid* grid) {
+  if (use_all_pairs(grid)) return;
+  constexpr int kChunks = kChCells / 4096;
+  __shared__ int s_w[16 * kChunks];   // [chunk][wavefront]
+  int4* head = reinterpret_cast<int4*>(blockIdx.x == 0 ? a.head : b.head);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int4 v[kChunks];
+  int up[kChunks];   // inclusive over the wavefront
+#pragma unroll
+  for (int q = 0; q < kChunks; ++q) v[q] = head[1024 * q + tid];
+#pragma unroll
+  for (int q = 0; q < kChunks; ++q) {
+    up[q] = v[q].x + v[q].y + v[q].z + v[q].w;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(up[q], o);
+      if (lane >= o) up[q] += t;
+    }
+    if (lane == 63) s_w[16 * q + wave] = up[q];
+  }
+  __syncthreads();
+  int before = 0;   // of this thread's entry of s_w
+  if (tid < 16 * kChunks)
+    for (int k = 0; k < tid; ++k) before += s_w[k];
+  __syncthreads();
+  if (tid < 16 * kChunks) s_w[tid] = before;
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kChunks; ++q) {
     int4 o;
-    o.x = at;
+    o.x = s_w[16 * q + wave] + up[q] - (v[q].x + v[q].y + v[q].z + v[q].w);
     o.y = o.x + v[q].x;
     o.z = o.y + v[q].y;
     o.w = o.z + v[q].z;
-    at = o.w + v[q].w;
-    reinterpret_cast<int4*>(head + per * tid)[q] = o;
+    head[1024 * q + tid] = o;
   }
 }
 
-__global__ void __launch_bounds__(256) k_chamfer_scatter(ChamferSet a, ChamferSet b) {
+__global__ void __launch_bounds__(256) k_chamfer_scatter(ChamferSet a, ChamferSet b,
+                                                         const ChamferGrid* grid) {
+  if (use_all_pairs(grid)) return;
   const long k = (long)blockIdx.x * 256 + threadIdx.x;
   if (k >= (long)a.n + b.n) return;
   const ChamferSet& s = k < a.n ? a : b;
@@ -357,21 +428,33 @@ __global__ void __launch_bounds__(256) k_chamfer_scatter(ChamferSet a, ChamferSe
       make_float4(s.p[i], s.p[(size_t)s.n + i], s.p[2 * (size_t)s.n + i], __int_as_float(i));
 }
 
-// Bounding boxes of the blocks, one wavefront each (NaN coordinates are left out: such a
-// point is never selected).
-__global__ void __launch_bounds__(256) k_chamfer_boxes(ChamferSet a, ChamferSet b) {
+__device__ __forceinline__ bool finite3(const float4& p) {
+  return isfinite(p.x) && isfinite(p.y) && isfinite(p.z);
+}
+
+// Bounding boxes of the blocks, one wavefront each. A point with a coordinate that is not finite
+// is left out: its distance is NaN or infinite, and neither is ever selected.
+__global__ void __launch_bounds__(256) k_chamfer_boxes(ChamferSet a, ChamferSet b,
+                                                       const ChamferGrid* grid) {
+  if (use_all_pairs(grid)) return;
   const int w = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (w >= a.nblk + b.nblk) return;
   const ChamferSet& s = w < a.nblk ? a : b;
   const int k = w < a.nblk ? w : w - a.nblk;
   const float4 p = s.sorted[min(k * kChPts + lane, s.n - 1)];
+  const bool fin = finite3(p);
   float lo[3] = {p.x, p.y, p.z}, hi[3] = {p.x, p.y, p.z};
 #pragma unroll
-  for (int r = 0; r < 3; ++r)
+  for (int r = 0; r < 3; ++r) {
+    if (!fin) {
+      lo[r] = INFINITY;
+      hi[r] = -INFINITY;
+    }
     for (int o = 32; o > 0; o >>= 1) {
       lo[r] = fminf(lo[r], __shfl_xor(lo[r], o));
       hi[r] = fmaxf(hi[r], __shfl_xor(hi[r], o));
     }
+  }
   if (lane == 0)
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
@@ -395,9 +478,18 @@ __device__ __forceinline__ float lane_f(float v, int l) {
 // rest; the best points of all four meet in LDS after every block. Distances and indices
 // are compared as one 64-bit number (distances are not negative, and NaN is above
 // infinity). A block's points travel while the one before is searched.
-__global__ void __launch_bounds__(256) k_chamfer_near(ChamferSet a, ChamferSet b) {
-  __shared__ unsigned long long s_best[kChPts];
-  __shared__ float4 s_pts[4][kChPts];
+// Sets that are not worth sorting are searched plainly in the same launch, their tiles in the
+// same LDS (13505 by 13440 equal points: 84 us, with k_chamfer_nn alone 74).
+__global__ void __launch_bounds__(256) k_chamfer_near(ChamferSet a, ChamferSet b, ChamferPairs pairs,
+                                                      const ChamferGrid* grid, int* bad) {
+  __shared__ __align__(16) float s_tile[3][kChTilePlain];
+  if (use_all_pairs(grid)) {
+    all_pairs<kChTilePlain>(pairs, s_tile, bad);
+    return;
+  }
+  float4 (*s_pts)[kChPts] = reinterpret_cast<float4 (*)[kChPts]>(&s_tile[0][0]);   // [4]
+  unsigned long long* s_best = reinterpret_cast<unsigned long long*>(s_pts + 4);   // [kChPts]
+  static_assert(sizeof(s_tile) >= 4 * kChPts * sizeof(float4) + kChPts * 8, "both in one tile");
   const bool second = (int)blockIdx.x >= a.nblk * a.split;
   const ChamferSet& Q = second ? b : a;
   const ChamferSet& D = second ? a : b;
@@ -441,7 +533,9 @@ __global__ void __launch_bounds__(256) k_chamfer_near(ChamferSet a, ChamferSet b
     atomicMin(&s_best[lane], best);
     best = min(best, *(volatile unsigned long long*)&s_best[lane]);
   };
-  auto reach = [&] { return __uint_as_float((unsigned)(best >> 32)); };
+  // a query that is not finite finds nothing, and needs no block
+  const bool fin = finite3(q);
+  auto reach = [&] { return fin ? __uint_as_float((unsigned)(best >> 32)) : -1.0f; };
   // the nearest of this wavefront's blocks
   float near = INFINITY;
   int first = -1;
@@ -545,13 +639,18 @@ static ChamferSorted chamfer_sorted(const ChamferLayout& L, int ng, int nm) {
   return S;
 }
 
-// Pairs from which on the sorted search is the faster one (sorted against all pairs, us:
-// 1.0e8 pairs 60, 50; 65536 by 1600 75, 55; 60000 by 4000 82, 99; 2.6e8 65, 109; 9e8 87, 325;
-// 65536 by 40000 139, 878).
+// Pairs from which on the sorted search is the faster one (sorted against all pairs, us, with
+// the calls' gaps: 1.0e8 pairs 60, 50; 65536 by 1600 75, 55; 65536 by 2753 80, 83; 13505 by
+// 13440 62, 83; 30000 by 30000 86, 333; 65536 by 40000 134, 900).
 constexpr double kChSortedPairs = 1.8e8;
 
+// The sort takes time with the points, so the smaller set must not be too small either (2
+// million by 100: sorted 858, all pairs 474; 500000 by 1000 264, 190; 300000 by 2000 196, 241).
+constexpr double kChSortedMean = 1400.0;
+
 static bool chamfer_wants_sorted(int ng, int nm) {
-  return (double)ng * (double)nm >= kChSortedPairs;
+  const double pairs = (double)ng * (double)nm;
+  return pairs >= kChSortedPairs && pairs >= kChSortedMean * ((double)ng + (double)nm);
 }
 
 }  // namespace phisft
@@ -579,6 +678,16 @@ sim_status sim_chamfer(const float* g, int32_t n_g, const float* m, int32_t n_m,
   auto* pg = reinterpret_cast<double*>(w + L.part_g);
   auto* pm = reinterpret_cast<double*>(w + L.part_m);
   int* bad = reinterpret_cast<int*>(w + L.bad);
+  ChamferPairs pairs{{{g, m, n_g, n_m, cdiv(n_g, kChBlockQ), bg}, {m, g, n_m, n_g, cdiv(n_m, kChBlockQ), bm}},
+                     0, 0, 0};
+  auto split = [&](int tile) {   // smaller tiles until there are workgroups for every CU
+    for (;; tile /= 2) {
+      pairs.ntile = tile;
+      pairs.nb0 = (long)pairs.p[0].qblocks * cdiv(n_m, tile);
+      pairs.nb = pairs.nb0 + (long)pairs.p[1].qblocks * cdiv(n_g, tile);
+      if (tile == kChTileMin || pairs.nb >= kChGrid) break;
+    }
+  };
   const ChamferSorted S = chamfer_sorted(L, n_g, n_m);
   if (chamfer_wants_sorted(n_g, n_m) && workspace_bytes >= S.total) {
     ChamferSet set[2];
@@ -594,36 +703,27 @@ sim_status sim_chamfer(const float* g, int32_t n_g, const float* m, int32_t n_m,
       t.best = k == 0 ? bg : bm;
       t.split = std::min(kChSplit, std::max(1, kChNearGrid / t.nblk));
     }
-    const ChamferGrid gr{reinterpret_cast<unsigned*>(w + S.lim), bad};
     const ChamferSet &a = set[0], &b = set[1];
     const dim3 th(256), pts(cdiv((long)n_g + n_m, 256));
-    hipLaunchKernelGGL(k_chamfer_clear, dim3(kChCells / 256), th, 0, st, a, b, gr);
-    hipLaunchKernelGGL(k_chamfer_bounds, dim3(pts.x < 256 ? pts.x : 256), th, 0, st, a, b, gr);
-    hipLaunchKernelGGL(k_chamfer_count, pts, th, 0, st, a, b, gr);
-    hipLaunchKernelGGL(k_chamfer_scan, dim3(2), dim3(1024), 0, st, a, b);
-    hipLaunchKernelGGL(k_chamfer_scatter, pts, th, 0, st, a, b);
-    hipLaunchKernelGGL(k_chamfer_boxes, dim3(cdiv((long)a.nblk + b.nblk, 4)), th, 0, st, a, b);
+    ChamferGrid* grid = reinterpret_cast<ChamferGrid*>(w + S.lim);
+    split(kChTilePlain);
+    const int nclear = std::min(std::max(pts.x / 16, 32u), 512u);
+    hipLaunchKernelGGL(k_chamfer_start, dim3(nclear + 2), dim3(kChSample), 0, st, a, b, grid, bad);
+    hipLaunchKernelGGL(k_chamfer_count, dim3(L.nbg + L.nbm), th, 0, st, a, b, grid, L.nbg, bad);
+    hipLaunchKernelGGL(k_chamfer_scan, dim3(2), dim3(1024), 0, st, a, b, grid);
+    hipLaunchKernelGGL(k_chamfer_scatter, pts, th, 0, st, a, b, grid);
+    hipLaunchKernelGGL(k_chamfer_boxes, dim3(cdiv((long)a.nblk + b.nblk, 4)), th, 0, st, a, b, grid);
     hipLaunchKernelGGL(k_chamfer_near, dim3(a.nblk * a.split + b.nblk * b.split), th, 0,
-                       st, a, b);
+                       st, a, b, pairs, grid, bad);
   } else {
-    ChamferPass p0{g, m, n_g, n_m, cdiv(n_g, kChBlockQ), bg};
-    ChamferPass p1{m, g, n_m, n_g, cdiv(n_m, kChBlockQ), bm};
-    // smaller tiles until there are workgroups for every CU
-    int tile = kChTile;
-    long nb0, nb1;
-    for (;; tile /= 2) {
-      nb0 = (long)p0.qblocks * cdiv(n_m, tile);
-      nb1 = (long)p1.qblocks * cdiv(n_g, tile);
-      if (tile == kChTileMin || nb0 + nb1 >= kChGrid) break;
-    }
-    if (nb0 + nb1 > 0x7fffffffL) return SIM_E_INVALID;
+    split(kChTile);
+    if (pairs.nb > 0x7fffffffL) return SIM_E_INVALID;
     // the two packed-minimum arrays are contiguous up to alignment padding, which the
     // fill covers as well (it lies inside the workspace)
     const long nfill = (long)(L.part_g - L.best_g) / 8;
     hipLaunchKernelGGL(k_chamfer_init, dim3(cdiv(nfill, kChThreads)), dim3(kChThreads), 0, st, bg,
                        nfill, bad);
-    hipLaunchKernelGGL(k_chamfer_nn, dim3((unsigned)(nb0 + nb1)), dim3(kChThreads), 0, st, p0, p1,
-                       (int)nb0, tile, bad);
+    hipLaunchKernelGGL(k_chamfer_nn, dim3((unsigned)pairs.nb), dim3(kChThreads), 0, st, pairs, bad);
   }
   hipLaunchKernelGGL(k_chamfer_unpack, dim3(L.nbg + L.nbm), dim3(kChThreads), 0, st,
                      ChamferOut{bg, n_g, d_g, i_g, pg}, ChamferOut{bm, n_m, d_m, i_m, pm}, L.nbg);
