@@ -211,13 +211,14 @@ typedef struct {
                                when that fits 16 GB, else not at all (rebuilt in the
                                adjoint); with checkpointing see coarse_keep_all;
                                handles solved directly keep factors instead           */
-  int32_t autotune;         /* 1: sim_create times every feasible solver launch shape
-                               (rows per workgroup; matrix rows in registers, on one or
-                               two wavefront teams, in LDS or streamed; rows of the
-                               coarse inverse in LDS or streamed; one or two workgroups
-                               per CU) on the step system of the rest state and keeps
-                               the fastest; 0 (default): fewest co-resident launches,
-                               then the matrix homes in the order registers (two teams
+  int32_t autotune;         /* 1: sim_create times every feasible launch shape of the
+                               iterative solver, also of handles solved directly (rows
+                               per workgroup; matrix rows in registers, on one or two
+                               wavefront teams, in LDS or streamed; rows of the coarse
+                               inverse in LDS or streamed; one or two workgroups per CU),
+                               on the step system of the rest state and keeps the
+                               fastest; 0 (default): fewest co-resident launches, then
+                               the matrix homes in the order registers (two teams
                                first), LDS, streamed, then larger workgroups           */
   int32_t graph;            /* 1: sim_rollout and sim_adjoint capture their launches
                                into a HIP graph (on a stream of the handle) and launch
@@ -254,8 +255,10 @@ typedef struct {
                                  residual ||b - A Delta v|| unless a solve stopped at
                                  cg_max_iter: then the recursive estimate) */
   int32_t device_status;      /* sticky device status (sim_status value) */
-  int32_t rows_per_block;     /* solver launch shape in use */
-  int32_t blocks;             /* solver workgroups per launch */
+  int32_t rows_per_block;     /* launch shape of the iterative solver (of handles solved
+                                 directly: should it take a solve over), also in the
+                                 fields about its launches, rows and tuning below */
+  int32_t blocks;             /* its workgroups per launch */
   int32_t solver_matrix_home; /* sim_matrix_home of the launch shape in use (never AUTO) */
   int32_t solver_launches_per_solve; /* batches split into sets of co-resident sheets */
   int64_t nnz_blocks;         /* non-zero 3x3 blocks of the system matrix */

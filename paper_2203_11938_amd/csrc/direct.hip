@@ -19,7 +19,7 @@
 // a pivot sweep and three hand-offs between workgroups, not the arithmetic (1.3 GFLOP).
 // A forward and adjoint of 60 steps on that sheet took 140 ms with the iterative solver
 // (100 to 300 iterations of 5 to 12 us a solve) and take 45 ms with this one; 40 steps of a
-// 17x17 sheet 66 and 10.8 ms, 30 forward and adjoint steps of a 200x200 sheet 434 and 209 ms.
+// 17x17 sheet 66 and 10.8 ms, 30 forward and adjoint steps of a 200x200 sheet 440 and 211 ms.
 // Workgroups take the tasks in a topological order and wait on per-front counters, so the
 // only tasks ever waited for have been taken by workgroups that run (one of each queue is
 // enough: the order within every queue is part of one order of all tasks, and a workgroup
@@ -28,8 +28,9 @@
 // is written once per launch, on cache lines of its own, with write-through stores, and
 // read only after its counter, so ordinary cached loads see it. All waits are bounded: a
 // time-out ends the launch, the residual test fails and the iterative solver takes over.
-// Every sum has a fixed order, so results do not depend on which workgroup ran what,
-// nor on the other sheets of a batch.
+// Every sum has a fixed order, so results do not depend on which workgroup ran what, nor, in
+// a handle that is solved directly, on the other sheets of its batch (whether it is, is
+// decided for all its sheets together: by their memory, and by the time either solver takes).
 
 #include <hip/hip_runtime.h>
 

@@ -406,8 +406,9 @@ bool want_direct(const sim_t* s, const sim_options& o) {
 
 // Time of a factorisation with one solve, us: the chain of fronts of the largest sheet and
 // its tasks, beside which the other sheets' tasks run, and the residual and the empty
-// launches after it. Within 15 % of the times measured on 17x17 (0.13 ms) to 300x300
-// (8.5 ms) sheets and on batches of up to 64 sheets of 64x64 (6.3 ms).
+// launches after it. Within 20 % of the times measured on 17x17 (0.13 ms) to 300x300
+// (8.5 ms) sheets and on batches of up to 64 sheets of 64x64 (6.3 ms); up to 1.5 times too
+// long on batches of small sheets, which need far more iterations than that at 1e-7.
 double direct_us(const HostLayout& L, const DsPlan& P) {
   int tiles = 0, most = 0;
   for (int l = 0; l < P.levels(); ++l) {

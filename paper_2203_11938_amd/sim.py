@@ -246,18 +246,18 @@ class Simulator:
     """A handle of the library over one or several sheets (batched when several).
 
     ``dt`` is the step h [s]; ``precision`` "fp32" or "fp64"; ``cg_tol`` the
-    relative residual at which each CG solve stops; ``checkpoint_every`` k > 0
+    relative residual that each step's solve meets; ``checkpoint_every`` k > 0
     keeps every k-th state and recomputes the rest in the adjoint; ``membrane``
     selects the system matrix's membrane block ("exact" Hessian or "tension");
     ``coarse_size`` sets the vertices per aggregate of the solver's coarse space
-    (0: block-Jacobi only); ``autotune`` times the feasible solver launch shapes at
-    creation and keeps the fastest; ``graph`` captures rollout and adjoint into HIP
+    (0: block-Jacobi only); ``autotune`` times the iterative solver's feasible launch
+    shapes at creation and keeps the fastest; ``graph`` captures rollout and adjoint into HIP
     graphs that later calls with the same arrays replay; ``matrix_home`` pins where
     the solver keeps its matrix rows ("streamed", "lds" or "registers"; None: the
     library's choice); ``air_density`` is the aerodynamic force's rho_air [kg/m^3]
     (acting in rollouts given a wind velocity); ``coarse_keep_all`` keeps every
-    step's coarse operators under checkpointing (faster, memory not bounded by the
-    checkpoint interval); ``material_model`` "wang" selects the anisotropic
+    step's factors or coarse operators under checkpointing (faster, memory not bounded
+    by the checkpoint interval); ``material_model`` "wang" selects the anisotropic
     strain-dependent material (material arrays of 40 entries per sheet).
     """
 
