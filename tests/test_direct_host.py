@@ -21,8 +21,6 @@ def lib(tmp_path_factory):
     out = str(tmp_path_factory.mktemp("direct") / "libdirect_check.so")
     subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-I" + CSRC,
                     os.path.join(HERE, "host", "direct_check.cpp"),
-                    os.path.join(HERE, "host", "wait_check.cpp"),
-                    os.path.join(HERE, "host", "plan_check.cpp"),
                     os.path.join(CSRC, "direct_prep.cpp"), "-o", out], check=True)
     return ctypes.CDLL(out)
 
@@ -66,22 +64,7 @@ def stacked(n):
     return np.zeros_like(rest), tris
 
 
-def comb(teeth, width, length, spine):
-    """A sheet with slits: the fronts above the teeth have more than two children."""
-    cols, rows = teeth * width, spine + length
-    rest = np.array([(i, j, 0.0) for j in range(rows) for i in range(cols)])
-    tris = []
-    for j in range(rows - 1):
-        for i in range(cols - 1):
-            if j < spine - 1 or (i + 1) % width:
-                a, c = j * cols + i, (j + 1) * cols + i
-                tris += [(a, a + 1, c + 1), (a, c + 1, c)]
-    return rest, np.array(tris)
-
-
 MESHES = {
-    "slits": lambda: [comb(4, 6, 16, 4)],
-    "more slits": lambda: [comb(7, 6, 18, 4), comb(3, 4, 9, 3)],
     "triangle": lambda: [(np.eye(3), np.array([[0, 1, 2]]))],
     "one front": lambda: [W.grid_sheet(4)],
     "pieces at the cut size": lambda: [W.grid_sheet(n) for n in (5, 6, 8)],
@@ -132,25 +115,3 @@ def test_plan_solves_the_system(lib, name):
     # backward-stable elimination: eps times the condition number, with room for the
     # explicit pivot inverses
     assert np.abs(x.T.ravel() - ref).max() <= 64 * np.finfo(float).eps * cond * np.abs(ref).max()
-
-
-def test_waits_hand_over_their_own_outcome(lib):
-    """A wavefront may read a wait's outcome late, when wavefront 0 is already through with
-    the next wait: with one word it then reads that one's; with the words the solver uses
-    in turn, never."""
-    assert lib.wait_check(1) > 0
-    assert lib.wait_check(0) == 0
-
-
-@pytest.mark.parametrize("shape", [(4, 6, 16, 4), (7, 6, 18, 4), (4, 8, 24, 6)])
-def test_slits_give_fronts_of_more_than_two_children(lib, shape):
-    rest, tris = comb(*shape)
-    adj = neighbours(len(rest), tris)
-    ell = np.full((max(map(len, adj)), len(rest)), -1, np.int32)
-    for i, a in enumerate(adj):
-        ell[:len(a), i] = sorted(a)
-    P = lambda a: a.ctypes.data_as(ctypes.c_void_p)
-    more = ctypes.c_int()
-    rest = np.ascontiguousarray(rest, np.float64)
-    assert lib.plan_children(len(rest), len(ell), P(ell), P(rest), ctypes.byref(more)) >= 3
-    assert more.value > 0
